@@ -53,15 +53,15 @@ struct Adjoint {
         asm volatile("" : "+v"(r));
         return r;
     }
-    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int j, float (&r)[8]) {
-        r[0] = a.x[j];
-        r[1] = a.y[j];
-        r[2] = a.z[j];
-        r[3] = a.m[j];
-        r[4] = (float)a.gx[j];
-        r[5] = (float)a.gy[j];
-        r[6] = (float)a.gz[j];
-        r[7] = a.gp ? (float)a.gp[j] : 0.0f;
+    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int b, unsigned j, float (&r)[8]) {
+        r[0] = (a.x + b)[j];
+        r[1] = (a.y + b)[j];
+        r[2] = (a.z + b)[j];
+        r[3] = (a.m + b)[j];
+        r[4] = (float)(a.gx + b)[j];
+        r[5] = (float)(a.gy + b)[j];
+        r[6] = (float)(a.gz + b)[j];
+        r[7] = a.gp ? (float)(a.gp + b)[j] : 0.0f;
     }
     // Massless, cotangent-free particle at the origin: every term below is zero.
     static __device__ __forceinline__ void pad_j(float (&r)[8]) {
@@ -75,6 +75,11 @@ struct Adjoint {
         for (int c = 3; c < 8; ++c) r[c] = 0.0f;
     }
 
+    template <bool MASS>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+                                                      float (&acc)[kOut]) {
+        pair<MASS>(j, i, eps2, acc);
+    }
     template <bool MASS>
     static __device__ __forceinline__ void pair(const float *j, const IState &k, float eps2,
                                                 float (&acc)[5]) {
@@ -138,19 +143,24 @@ struct AdjointTile {
                 Adjoint::negated(m), (float)a.gx[i], (float)a.gy[i], (float)a.gz[i],
                 a.gp ? -(float)a.gp[i] : -0.0f};
     }
-    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &c, int j, float (&r)[8]) {
-        r[0] = (float)(a.x[j] - c.cx);
-        r[1] = (float)(a.y[j] - c.cy);
-        r[2] = (float)(a.z[j] - c.cz);
-        r[3] = a.m[j];
-        r[4] = (float)a.gx[j];
-        r[5] = (float)a.gy[j];
-        r[6] = (float)a.gz[j];
-        r[7] = a.gp ? (float)a.gp[j] : 0.0f;
+    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &c, int b, unsigned j, float (&r)[8]) {
+        r[0] = (float)((a.x + b)[j] - c.cx);
+        r[1] = (float)((a.y + b)[j] - c.cy);
+        r[2] = (float)((a.z + b)[j] - c.cz);
+        r[3] = (a.m + b)[j];
+        r[4] = (float)(a.gx + b)[j];
+        r[5] = (float)(a.gy + b)[j];
+        r[6] = (float)(a.gz + b)[j];
+        r[7] = a.gp ? (float)(a.gp + b)[j] : 0.0f;
     }
     static __device__ __forceinline__ void pad_j(float (&r)[8]) { Adjoint::pad_j(r); }
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { Adjoint::null_j(r); }
+    template <bool MASS>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+                                                      float (&acc)[kOut]) {
+        pair<MASS>(j, i, eps2, acc);
+    }
     template <bool MASS>
     static __device__ __forceinline__ void pair(const float *j, const IState &k, float eps2,
                                                 float (&acc)[5]) {

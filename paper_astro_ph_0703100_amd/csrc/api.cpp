@@ -112,6 +112,58 @@ nbody_status get_workspace(const nbody_opts &o, size_t need, hipStream_t s, void
     return NBODY_OK;
 }
 
+int wave_ipl(int kernel, int precision, int64_t blocks, int ipl) {
+    if (ipl) return std::min(ipl, kernel == KERNEL_FORCE || kernel == KERNEL_BATCHED ? 4 : 2);
+    const int most = kernel == KERNEL_FORCE ? 4 : 2;
+    // More i's per lane save LDS reads (and with them power, which bounds the large
+    // systems), fewer leave more waves to spread over the chip.  Force, pair kernel +
+    // finalize, ipl 1 / 2 / 4: N = 20011 (49000 blocks) 122.2 / 123.6 / - us, 32768
+    // (131072 blocks) 298.8 / 293.1 / 300 us, 131072 (2^21 blocks) - / 4491 / 4380 us.
+    // PLAIN, whose segments are given: N = 65536 1175 / 1149 / 1175 us, 131072 4660 /
+    // 4470 / 4730 us.  Batches of small systems pay for padded i's too: 2048 clusters of 256
+    // to 16384 particles 18.25 / 17.61 / 17.86 ms.
+    if (precision == NBODY_PLAIN) return blocks >= 200000 ? 2 : 1;
+    return std::min(blocks >= 1000000 ? 4 : blocks >= 100000 ? 2 : 1, most);
+}
+
+// Launch of the grid engine for a shape whose ipl, jt and nseg are chosen: what the result
+// depends on (the FP32 blocks of min(jt, 128) j's; PLAIN: the segments) stays, the rest is
+// split for the chip.  ipl: asked for, or 0; nseg_asked: c->nseg is the caller's.
+void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ipl, bool nseg_asked,
+                       TileCfg *c) {
+    c->bj = std::min(c->jt, kBlockJ);
+    const int64_t nb = std::max<int64_t>(1, (nj + c->bj - 1) / c->bj);
+    const int64_t nb128 = std::max<int64_t>(1, (nj + 127) / 128);
+    c->wi = wave_ipl(kernel, precision, (ni + 63) / 64 * nb128, ipl);
+    c->wseg = c->nseg;
+    c->wseg_len = c->seg_len;
+    c->wpb = 4;
+    if (precision == NBODY_PLAIN) {
+        // Waves share nothing there: blocks of one wave leave their SIMD as soon as they end
+        // (N = 10007, 40 segments: 33.0 us, with 4 waves per block 36.9 us).
+        c->wpb = 1;
+        return;
+    }
+    if (nseg_asked) return;
+    // j's per wave, in blocks of 128: at most 3, 4 and 6 for ipl 1, 2 and 4 (short waves keep
+    // the last ones busy together, longer ones cost less to start: N = 16384 with 2 / 3 / 4
+    // blocks 83.9 / 82.3 / 84.2 us), fewer where there would be under 4 waves per SIMD.
+    const int64_t waves1 = (ni + 64 * c->wi - 1) / (64 * c->wi) * nb128;  // with one block each
+    const int64_t most = c->wi == 1 ? 3 : c->wi == 2 ? 4 : 6;
+    const int64_t per = std::max<int64_t>(1, std::min(most, waves1 / 4000));
+    int64_t seg = (nb128 + 4 * per - 1) / (4 * per);
+    if (nb128 <= 16 * (per + 1)) {
+        // The waves of one block cover every j: one launch, no partial sums.  A block of j's
+        // more per wave costs about as much as the finalize's launch (5 us).
+        c->wpb = (int)std::min<int64_t>(16, (nb128 + per - 1) / per);
+        seg = 1;
+    }
+    seg = std::min<int64_t>(seg, c->nseg);
+    const int64_t len = (nb + seg - 1) / seg;
+    c->wseg_len = (int)(len * c->bj);
+    c->wseg = (int)((nb + len - 1) / len);
+}
+
 // Launch shape for ni i-particles against nj j-particles: explicit options first, then
 // the tuning table (its j-split only when the two sets have the same size, the shape it
 // was measured on), then a default that gives every compute unit several blocks.
@@ -228,6 +280,8 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
     const int64_t per = jtiles > 0 ? (jtiles + nseg - 1) / nseg : 1;  // tiles per segment
     c.seg_len = (int)(per * c.jt);
     c.nseg = jtiles > 0 ? (int)((jtiles + per - 1) / per) : 1;
+    choose_wave_shape(kernel, ni, nj, precision, o.ipl ? o.ipl : (t.ipl > 1 ? t.ipl : 0),
+                      o.nseg > 0, &c);
     *cfg = c;
     return NBODY_OK;
 }
@@ -297,13 +351,13 @@ nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, floa
                             double *pot, const nbody_opts &o, const TileCfg &cfg, void *ws,
                             double *kick_v, double kick_h, hipStream_t s) {
     const float e2 = eps * eps;
-    PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.seg_len, e2, ws, cfg.npad};
-    FinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot, acc, pot, kick_v,
-                    kick_h};
+    PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.wseg_len, e2, ws, cfg.npad};
+    FinalizeArgs fa{ws, cfg.sym ? cfg.nseg : cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+                    acc, pot, kick_v, kick_h};
     if (cfg.jl > 1) return launch_pair_split(cfg, o.precision, pot != nullptr, pa, fa, s);
     if (cfg.sym) return launch_pair_sym(cfg, o.precision, pot != nullptr, pa, fa, s);
-    nbody_status st = launch_pair(cfg, o.precision, pot != nullptr, pa, s);
-    if (st) return st;
+    nbody_status st = launch_pair(cfg, o.precision, pot != nullptr, pa, fa, s);
+    if (st || cfg.wseg == 1) return st;
     return launch_finalize(o.precision, fa, s);
 }
 
@@ -319,11 +373,12 @@ nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, f
         double *centres = reinterpret_cast<double *>(ws.x32);
         if ((st = launch_tile_centres(n, itile, pos64, centres, s))) return st;
         const float e2 = eps * eps;
-        TilePairArgs ta{pos64, pos64 + n, pos64 + 2 * n, mass, (int)n, cfg.seg_len, e2,
+        TilePairArgs ta{pos64, pos64 + n, pos64 + 2 * n, mass, (int)n, cfg.wseg_len, e2,
                         ws.part, cfg.npad, centres, itile};
-        if ((st = launch_pair_tile(cfg, o.precision, pot != nullptr, ta, s))) return st;
-        FinalizeArgs fa{ws.part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+        FinalizeArgs fa{ws.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,     pot,      kick_v,   kick_h};
+        st = launch_pair_tile(cfg, o.precision, pot != nullptr, ta, fa, s);
+        if (st || cfg.wseg == 1) return st;
         return launch_finalize(o.precision, fa, s);
     }
     if (o.centre == NBODY_CENTRE_SYSTEM) {
@@ -433,9 +488,10 @@ nbody_status nbody_force_ij(int64_t ni, const float *pos_i, const float *eps_i, 
     void *ws = nullptr;
     if ((st = get_workspace(o, partial_bytes(cfg, o.precision), s, &ws))) return st;
     IJPairArgs a{pos_i, pos_i + ni, pos_i + 2 * ni, eps_i, pos_j, pos_j + nj, pos_j + 2 * nj,
-                 mass_j, (int)ni, (int)nj, cfg.seg_len, e2, ws, cfg.npad};
-    if ((st = launch_pair_ij(cfg, o.precision, pot != nullptr, a, s))) return st;
-    FinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, pot, nullptr, 0.0};
+                 mass_j, (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
+    FinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, pot, nullptr, 0.0};
+    st = launch_pair_ij(cfg, o.precision, pot != nullptr, a, fa, s);
+    if (st || cfg.wseg == 1) return st;
     return launch_finalize(o.precision, fa, s);
 }
 

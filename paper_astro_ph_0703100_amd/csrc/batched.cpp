@@ -2,11 +2,10 @@
 // device tables and scratch, built once from the host offsets) and the batched force
 // and leapfrog entry points.
 //
-// Work items: each system with N_k particles is cut into ceil(N_k / (256 IPL))
-// i-tiles and S_k j-segments of about kItemJ j's; an item is one (i-tile, segment)
-// pair of one system.  Items are sorted by decreasing cost (i-lanes x j's, including
-// padding) and handed to the persistent kernel's blocks through an atomic ticket, so
-// large systems start first and small ones fill the tail.
+// Work items: each system with N_k particles is cut into groups of 64 * wi i's and
+// S_k j-segments of about kItemJ j's; an item is one (group, segment) pair of one system.
+// Items are sorted by decreasing cost (i-lanes x j's, including padding), so large systems
+// start first and small ones fill the tail.
 #include <algorithm>
 #include <cmath>
 #include <new>
@@ -21,7 +20,10 @@ struct nbody_plan {
     int64_t total = 0;
     nbody_opts opts{};
     int ipl = 4, jt = 256;
+    int wi = 1;          // i-records per lane of the launch
+    int waves = 4;       // waves per work item
     int nitems = 0;
+    bool split = false;  // some system has more than one j-segment
     int64_t padded_pairs = 0;
     int64_t pairs = 0;
     // device tables
@@ -31,13 +33,11 @@ struct nbody_plan {
     int64_t *part_base = nullptr;
     int32_t *npad = nullptr;
     int32_t *nseg = nullptr;
-    unsigned int *counter = nullptr;
     // scratch
     void *part = nullptr;
     size_t part_bytes = 0;
     float *x32 = nullptr;
     double *centre = nullptr;
-    int grid[2] = {0, 0};  // persistent blocks, without / with the potential
 };
 
 namespace nbody {
@@ -48,7 +48,7 @@ constexpr int64_t kItemJ = 4096;  // target j's per work item
 void free_plan(nbody_plan *p) {
     if (!p) return;
     void *ptrs[] = {p->items, p->offsets, p->sys_of, p->part_base, p->npad,
-                    p->nseg,  p->counter, p->part,   p->x32,       p->centre};
+                    p->nseg,  p->part,    p->x32,    p->centre};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     delete p;
@@ -69,19 +69,6 @@ nbody_status dev_copy(T **dst, const std::vector<T> &src) {
     return NBODY_OK;
 }
 
-// Persistent grid for one kernel variant: resident blocks per CU x CUs.
-nbody_status persistent_grid(const nbody_plan *p, bool with_pot, int *grid) {
-    const void *fn = nullptr;
-    nbody_status st = batched_pair_kernel(p->ipl, p->jt, p->opts.precision, with_pot, &fn);
-    if (st) return st;
-    int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kTPB, 0);
-    if (e != hipSuccess) return hip_error(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-    if (per_cu < 1) per_cu = 1;
-    *grid = per_cu * device_info().cus;
-    return NBODY_OK;
-}
-
 nbody_status check_plan_call(const nbody_plan *p, const void *pos, const float *mass,
                              const float *eps, const double *acc) {
     if (!p) return set_error(NBODY_EINVAL, "plan must not be NULL");
@@ -93,17 +80,17 @@ nbody_status check_plan_call(const nbody_plan *p, const void *pos, const float *
     return NBODY_OK;
 }
 
-// Persistent pair kernel + batched finalize on FP32 positions.
+// Pair kernel (+ batched finalize of the split systems) on FP32 positions.
 nbody_status batched_core(const nbody_plan *p, const float *pos, const float *mass,
                           const float *eps, double *acc, double *pot, double *kick_v,
                           double kick_h, hipStream_t s) {
-    const bool with_pot = pot != nullptr;
-    const int grid = p->grid[with_pot];
     const int64_t n = p->total;
     PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, 0, 0.0f, p->part, 0};
-    BatchSched sc{p->items, p->nitems, p->counter, eps, p->part};
-    nbody_status st = launch_batched_pair(p->ipl, p->jt, p->opts.precision, with_pot, grid, pa, sc, s);
-    if (st) return st;
+    FinalizeArgs out{nullptr, 1, 0, (int)n, mass, 0.0f, 0, acc, pot, kick_v, kick_h};
+    BatchSched sc{p->items, p->nitems, eps, p->part};
+    nbody_status st = launch_batched_pair(p->wi, p->jt, p->waves, p->opts.precision, pot != nullptr,
+                                          pa, out, sc, s);
+    if (st || !p->split) return st;
     BatchFinalizeArgs fa{p->part, n,   p->sys_of, p->offsets, p->part_base, p->npad, p->nseg,
                          acc,     pot, kick_v,    kick_h};
     return launch_batched_finalize(p->opts.precision, fa, s);
@@ -192,23 +179,50 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
         return hip_error(e, "hipGetDevice");
     }
 
-    // Items and the partial-sum layout.
-    const int64_t itile = (int64_t)kTPB * ipl;
+    // i-records per lane: asked for, else by the work (pieces of 64 i's x 128 j's), as for
+    // one system.
+    int64_t blocks1 = 0, largest = 0;
+    for (int32_t k = 0; k < nsys; ++k) {
+        const int64_t n = h_offsets[k + 1] - h_offsets[k];
+        blocks1 += (n + 63) / 64 * ((n + 127) / 128);
+        largest = std::max(largest, n);
+    }
+    p->wi = wave_ipl(KERNEL_BATCHED, o.precision, blocks1, o.ipl ? o.ipl : (te.ipl > 1 ? te.ipl : 0));
+    // Waves per item: 4, and as many as the largest segment has FP32 blocks, up to 16, where
+    // there is too little work to keep 4 waves per SIMD busy with longer runs.
+    p->waves = 4;
+    if (o.precision == NBODY_PLAIN) {
+        p->waves = 1;
+    } else if (!o.ipl && !o.jtile && blocks1 < 50000) {
+        const int64_t nb = (std::min(largest, kItemJ) + 127) / 128;
+        p->waves = (int)std::max<int64_t>(4, std::min<int64_t>(16, nb));
+    }
+
+    // j's per item.  With an open shape, and enough work to fill the chip with long items, the
+    // largest systems of 2^14 particles stay whole as well: no partial sums, no finalize.
+    const bool open_shape = !o.ipl && !o.jtile && o.precision != NBODY_PLAIN;
+    const int64_t item_j = open_shape && blocks1 >= 1000000 ? 4 * kItemJ : kItemJ;
+
+    // The partial-sum layout, then the items: (system, j-segment) pairs in decreasing order
+    // of their length, ties in creation order, and the groups of i's of each.
+    struct Segment {
+        int32_t sys, j0, nj;
+        int64_t part;
+    };
+    const int64_t itile = (int64_t)64 * p->wi;
     const int wo = 4 * (o.precision == NBODY_PLAIN ? 1 : 2);  // words per (i, segment)
-    const int64_t tiles_per_seg = std::max<int64_t>(1, kItemJ / jt);
-    std::vector<BatchItem> items;
-    std::vector<int64_t> cost, base(std::max(nsys, 1)), offs(h_offsets, h_offsets + nsys + 1);
+    const int64_t tiles_per_seg = std::max<int64_t>(1, item_j / jt);
+    std::vector<Segment> segments;
+    std::vector<int64_t> base(std::max(nsys, 1)), offs(h_offsets, h_offsets + nsys + 1);
     std::vector<int32_t> npad(std::max(nsys, 1)), nseg(std::max(nsys, 1)), sys_of((size_t)total);
-    int64_t words = 0;
+    int64_t words = 0, nitems = 0;
     for (int32_t k = 0; k < nsys; ++k) {
         const int64_t off = h_offsets[k], n = h_offsets[k + 1] - off;
-        for (int64_t q = 0; q < n; ++q) sys_of[(size_t)(off + q)] = k;
+        std::fill_n(sys_of.begin() + off, n, k);
         base[k] = words;
-        if (n == 0) {
-            npad[k] = 0;
-            nseg[k] = 0;
-            continue;
-        }
+        npad[k] = 0;
+        nseg[k] = 0;
+        if (n == 0) continue;
         const int64_t t = (n + itile - 1) / itile;
         const int64_t jtiles = (n + jt - 1) / jt;
         int64_t segs = (jtiles + tiles_per_seg - 1) / tiles_per_seg;
@@ -217,31 +231,37 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
         const int64_t seg_len = per * jt;
         npad[k] = (int32_t)(t * itile);
         nseg[k] = (int32_t)segs;
-        for (int64_t ti = 0; ti < t; ++ti)
-            for (int64_t si = 0; si < segs; ++si) {
-                BatchItem w;
-                w.sys = k;
-                w.i0 = (int32_t)(off + ti * itile);
-                w.ni = (int32_t)std::min(itile, n - ti * itile);
-                w.j0 = (int32_t)(off + si * seg_len);
-                w.nj = (int32_t)std::min(seg_len, n - si * seg_len);
-                w.col0 = (int32_t)(ti * itile);
-                w.part = words + si * wo * (t * itile);
-                w.npad = (int32_t)(t * itile);
-                w.pad_ = 0;
-                items.push_back(w);
-                cost.push_back(itile * ((w.nj + jt - 1) / jt) * jt);
-                p->padded_pairs += cost.back();
-            }
-        words += segs * wo * t * itile;
+        p->split = p->split || segs > 1;
+        for (int64_t si = 0; si < segs; ++si)
+            segments.push_back({k, (int32_t)(off + si * seg_len),
+                                (int32_t)std::min(seg_len, n - si * seg_len),
+                                words + si * wo * (t * itile)});
+        nitems += segs * t;
+        if (segs > 1) words += segs * wo * t * itile;
         p->pairs += n * n;
     }
-    // Decreasing cost; ties in creation order (system, i-tile, segment).
-    std::vector<int32_t> order(items.size());
-    for (size_t q = 0; q < order.size(); ++q) order[q] = (int32_t)q;
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return cost[a] > cost[b]; });
-    std::vector<BatchItem> sorted(items.size());
-    for (size_t q = 0; q < order.size(); ++q) sorted[q] = items[order[q]];
+    std::stable_sort(segments.begin(), segments.end(),
+                     [](const Segment &a, const Segment &b) { return a.nj > b.nj; });
+    std::vector<BatchItem> sorted;
+    sorted.reserve((size_t)nitems);
+    for (const Segment &sg : segments) {
+        const int32_t k = sg.sys;
+        const int64_t off = h_offsets[k], n = h_offsets[k + 1] - off;
+        for (int64_t c = 0; c < n; c += itile) {
+            BatchItem w;
+            w.sys = k;
+            w.i0 = (int32_t)(off + c);
+            w.ni = (int32_t)std::min(itile, n - c);
+            w.j0 = sg.j0;
+            w.nj = sg.nj;
+            w.col0 = (int32_t)c;
+            w.part = sg.part;
+            w.npad = npad[k];
+            w.whole = nseg[k] == 1;
+            sorted.push_back(w);
+            p->padded_pairs += itile * ((sg.nj + 7) / 8 * 8);
+        }
+    }
     p->nitems = (int)sorted.size();
 
     nbody_status st = NBODY_OK;
@@ -255,7 +275,6 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
     if ((st = dev_copy(&p->part_base, base))) return bail(st);
     if ((st = dev_copy(&p->npad, npad))) return bail(st);
     if ((st = dev_copy(&p->nseg, nseg))) return bail(st);
-    if ((st = dev_copy(&p->counter, std::vector<unsigned int>(1, 0u)))) return bail(st);
     p->part_bytes = (size_t)std::max<int64_t>(words, 1) * 4;
     if ((e = hipMalloc(&p->part, p->part_bytes)) != hipSuccess) {
         p->part = nullptr;
@@ -269,8 +288,6 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
         p->centre = nullptr;
         return bail(hip_error(e, "hipMalloc(plan centres)"));
     }
-    for (int pot = 0; pot < 2; ++pot)
-        if ((st = persistent_grid(p, pot != 0, &p->grid[pot]))) return bail(st);
     *out = p;
     return NBODY_OK;
 }
@@ -287,7 +304,7 @@ nbody_status nbody_plan_info(const nbody_plan *plan, int64_t *info) {
     info[0] = plan->nsys;
     info[1] = plan->total;
     info[2] = plan->nitems;
-    info[3] = plan->grid[1];
+    info[3] = plan->nitems;
     info[4] = plan->pairs;
     info[5] = plan->padded_pairs;
     info[6] = plan->ipl;

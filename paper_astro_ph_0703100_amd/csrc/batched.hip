@@ -1,19 +1,50 @@
 // Kernels of the ragged batched path: many independent systems stored back to back
 // (system k owns the global indices [offsets[k], offsets[k+1])).
 //
-//   * pair work: the persistent work-queue launch of the gravity pipeline over the
-//     plan's cost-sorted items (one i-tile x one j-range of one system each);
-//   * finalize: per particle, the fixed-order FP64 sum of its system's segment
-//     partials (no j == i term: the pair kernel left it out) and the optional fused
-//     leapfrog kick;
+//   * pair work: one block per work item of the plan (some i's x one j-range of one
+//     system), in decreasing order of cost, on the wave engine; a system whose j-range is
+//     not split gets its outputs (and the fused leapfrog kick) stored right there;
+//   * finalize: per particle of the other systems, the fixed-order FP64 sum of the
+//     segment partials (no j == i term: the pair kernel left it out) and the kick;
 //   * per-system FP64 centres (one block per system, fixed-order reduction) and the
 //     conversion of FP64 positions to FP32 relative to them.
 #include "gravity.h"
+#include "outputs.h"
+#include "wave_engine.h"
 
 namespace nbody {
 namespace {
 
-__global__ void reset_counter_kernel(unsigned int *counter) { *counter = 0u; }
+// One block per work item, the dispatcher taking them in order: the expensive items start
+// first and the small ones fill the tail.
+template <int IPL, int BJ, int MODE, bool FULL>
+__global__ __launch_bounds__(1024) void batched_pair_kernel(PairArgs a, FinalizeArgs f,
+                                                            BatchSched sc) {
+    constexpr int V = Gravity::kJWords / 4;
+    extern __shared__ float4 lds[];
+    const BatchItem it = sc.items[blockIdx.x];
+    const float e = sc.eps[it.sys];
+    const float eps2 = e * e;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int waves = blockDim.x >> 6;
+    float4 *tl = lds + wave * wave::kStage * V;
+    float hs[IPL][4], ls[IPL][4];
+    double ds[IPL][4];
+    float *part = static_cast<float *>(sc.part) + it.part;
+    if constexpr (MODE == NBODY_PLAIN) {
+        wave::wave_work<Gravity, IPL, BJ, MODE, FULL>(a, tl, it.i0, it.ni, it.j0, it.nj, eps2, hs,
+                                                      ls, ds);
+        wave::store_plain<ForceOut, IPL, FULL>(f, it.i0, it.i0 + it.ni, hs, it.whole, part,
+                                               (size_t)it.npad, (size_t)it.col0);
+    } else {
+        const wave::Run r = wave::block_run<BJ>(it.nj, wave, waves);
+        wave::wave_work<Gravity, IPL, BJ, MODE, FULL>(a, tl, it.i0, it.ni, it.j0 + r.j0, r.nj, eps2,
+                                                      hs, ls, ds);
+        wave::store_sums<ForceOut, IPL, MODE, FULL>(f, reinterpret_cast<double *>(lds), wave,
+                                                    waves, it.i0, it.i0 + it.ni, hs, ls, ds, it.whole,
+                                                    part, (size_t)it.npad, (size_t)it.col0);
+    }
+}
 
 template <int MODE>
 __global__ __launch_bounds__(256) void batched_finalize_kernel(BatchFinalizeArgs a) {
@@ -21,6 +52,7 @@ __global__ __launch_bounds__(256) void batched_finalize_kernel(BatchFinalizeArgs
     if (p >= a.total) return;
     const int k = a.sys_of[p];
     const int64_t col = p - a.offsets[k];
+    if (a.nseg[k] <= 1) return;  // stored by the pair launch
     const int npad = a.npad[k];
     const void *base = static_cast<const float *>(a.part) + a.part_base[k];
     double r[4];
@@ -72,19 +104,45 @@ __global__ __launch_bounds__(256) void batched_convert_kernel(int64_t total, con
 
 }  // namespace
 
-nbody_status batched_pair_kernel(int ipl, int jt, int precision, bool with_pot, const void **fn) {
-    *fn = reinterpret_cast<const void *>(engine::pick_persistent<Gravity>(ipl, jt, precision, with_pot));
-    return *fn ? NBODY_OK : set_error(NBODY_EUNSUPPORTED, "no batched kernel for this shape");
+namespace {
+
+using BatchFn = void (*)(PairArgs, FinalizeArgs, BatchSched);
+
+template <int IPL>
+BatchFn pick_batched(int jt, int mode, bool full) {
+    switch (mode) {
+        case NBODY_PLAIN:
+            return full ? batched_pair_kernel<IPL, 64, NBODY_PLAIN, true>
+                        : batched_pair_kernel<IPL, 64, NBODY_PLAIN, false>;
+        case NBODY_FP64RED:
+            if (jt == 64)
+                return full ? batched_pair_kernel<IPL, 64, NBODY_FP64RED, true>
+                            : batched_pair_kernel<IPL, 64, NBODY_FP64RED, false>;
+            return full ? batched_pair_kernel<IPL, 128, NBODY_FP64RED, true>
+                        : batched_pair_kernel<IPL, 128, NBODY_FP64RED, false>;
+        case NBODY_COMP:
+            if (jt == 64)
+                return full ? batched_pair_kernel<IPL, 64, NBODY_COMP, true>
+                            : batched_pair_kernel<IPL, 64, NBODY_COMP, false>;
+            return full ? batched_pair_kernel<IPL, 128, NBODY_COMP, true>
+                        : batched_pair_kernel<IPL, 128, NBODY_COMP, false>;
+    }
+    return nullptr;
 }
 
-nbody_status launch_batched_pair(int ipl, int jt, int precision, bool with_pot, int grid,
-                                 const PairArgs &a, const BatchSched &sc, hipStream_t s) {
-    auto fn = engine::pick_persistent<Gravity>(ipl, jt, precision, with_pot);
+}  // namespace
+
+nbody_status launch_batched_pair(int ipl, int jt, int waves, int precision, bool with_pot,
+                                 const PairArgs &a, const FinalizeArgs &f, const BatchSched &sc,
+                                 hipStream_t s) {
+    const BatchFn fn = ipl == 1   ? pick_batched<1>(jt, precision, with_pot)
+                       : ipl == 2 ? pick_batched<2>(jt, precision, with_pot)
+                       : ipl == 4 ? pick_batched<4>(jt, precision, with_pot)
+                                  : nullptr;
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no batched kernel for this shape");
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, s, sc.counter);
-    NBODY_HIP_CHECK(hipGetLastError());
-    if (sc.nitems <= 0 || grid <= 0) return NBODY_OK;
-    hipLaunchKernelGGL(fn, dim3(grid), dim3(kTPB), 0, s, a, sc);
+    if (sc.nitems <= 0) return NBODY_OK;
+    hipLaunchKernelGGL(fn, dim3((unsigned)sc.nitems), dim3(64 * waves),
+                       wave::lds_bytes<Gravity>(waves), s, a, f, sc);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }

@@ -2,6 +2,7 @@
 // launch), the FP64 finalize, and the FP64-position pre-pass (centre, conversion).
 #include "gravity.h"
 #include "outputs.h"
+#include "wave_engine.h"
 
 namespace nbody {
 namespace {
@@ -110,23 +111,13 @@ nbody_status launch_tile_centres(int64_t n, int itile, const double *pos64, doub
 }
 
 nbody_status launch_pair_tile(const TileCfg &cfg, int precision, bool with_pot,
-                              const TilePairArgs &a, hipStream_t s) {
-    auto fn = engine::pick_tile<GravityTile>(cfg.ipl, cfg.jt, precision, with_pot);
-    if (!fn) return set_error(NBODY_EUNSUPPORTED, "no tile-centre kernel for this shape");
-    if (cfg.itiles <= 0 || cfg.nseg <= 0) return NBODY_OK;
-    hipLaunchKernelGGL(fn, dim3(cfg.itiles, cfg.nseg), dim3(kTPB), 0, s, a);
-    NBODY_HIP_CHECK(hipGetLastError());
-    return NBODY_OK;
+                              const TilePairArgs &a, const FinalizeArgs &f, hipStream_t s) {
+    return wave::launch<GravityTile, ForceOut>(cfg, precision, with_pot, a.n, a, f, s);
 }
 
 nbody_status launch_pair(const TileCfg &cfg, int precision, bool with_pot, const PairArgs &a,
-                         hipStream_t s) {
-    auto fn = engine::pick_tile<Gravity>(cfg.ipl, cfg.jt, precision, with_pot);
-    if (!fn) return set_error(NBODY_EUNSUPPORTED, "no pair kernel for this ipl/jtile/precision");
-    if (cfg.itiles <= 0 || cfg.nseg <= 0) return NBODY_OK;
-    hipLaunchKernelGGL(fn, dim3(cfg.itiles, cfg.nseg), dim3(kTPB), 0, s, a);
-    NBODY_HIP_CHECK(hipGetLastError());
-    return NBODY_OK;
+                         const FinalizeArgs &f, hipStream_t s) {
+    return wave::launch<Gravity, ForceOut>(cfg, precision, with_pot, a.n, a, f, s);
 }
 
 template <int MODE>

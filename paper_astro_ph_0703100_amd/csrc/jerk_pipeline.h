@@ -67,14 +67,14 @@ struct GravityJerk {
     static __device__ __forceinline__ IState load_i(const Args &a, const Ctx &, int i) {
         return {a.x[i], a.y[i], a.z[i], a.vx[i], a.vy[i], a.vz[i]};
     }
-    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int j, float (&r)[8]) {
-        r[0] = a.x[j];
-        r[1] = a.y[j];
-        r[2] = a.z[j];
-        r[3] = a.m[j];
-        r[4] = a.vx[j];
-        r[5] = a.vy[j];
-        r[6] = a.vz[j];
+    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int b, unsigned j, float (&r)[8]) {
+        r[0] = (a.x + b)[j];
+        r[1] = (a.y + b)[j];
+        r[2] = (a.z + b)[j];
+        r[3] = (a.m + b)[j];
+        r[4] = (a.vx + b)[j];
+        r[5] = (a.vy + b)[j];
+        r[6] = (a.vz + b)[j];
         r[7] = 0.0f;
     }
     // A massless particle at rest at the origin: every term carries m = 0.
@@ -85,6 +85,11 @@ struct GravityJerk {
     // The j == i pair: same position and velocity, no mass.
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { r[3] = 0.0f; }
+    template <bool POT>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+                                                      float (&acc)[kOut]) {
+        pair<POT>(j, i, eps2, acc);
+    }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
                                                 float (&acc)[7]) {
@@ -115,19 +120,24 @@ struct GravityJerkTile {
         return {(float)(a.x[i] - c.cx),  (float)(a.y[i] - c.cy),  (float)(a.z[i] - c.cz),
                 (float)(a.vx[i] - c.wx), (float)(a.vy[i] - c.wy), (float)(a.vz[i] - c.wz)};
     }
-    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &c, int j, float (&r)[8]) {
-        r[0] = (float)(a.x[j] - c.cx);
-        r[1] = (float)(a.y[j] - c.cy);
-        r[2] = (float)(a.z[j] - c.cz);
-        r[3] = a.m[j];
-        r[4] = (float)(a.vx[j] - c.wx);
-        r[5] = (float)(a.vy[j] - c.wy);
-        r[6] = (float)(a.vz[j] - c.wz);
+    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &c, int b, unsigned j, float (&r)[8]) {
+        r[0] = (float)((a.x + b)[j] - c.cx);
+        r[1] = (float)((a.y + b)[j] - c.cy);
+        r[2] = (float)((a.z + b)[j] - c.cz);
+        r[3] = (a.m + b)[j];
+        r[4] = (float)((a.vx + b)[j] - c.wx);
+        r[5] = (float)((a.vy + b)[j] - c.wy);
+        r[6] = (float)((a.vz + b)[j] - c.wz);
         r[7] = 0.0f;
     }
     static __device__ __forceinline__ void pad_j(float (&r)[8]) { GravityJerk::pad_j(r); }
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { GravityJerk::null_j(r); }
+    template <bool POT>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+                                                      float (&acc)[kOut]) {
+        pair<POT>(j, i, eps2, acc);
+    }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
                                                 float (&acc)[7]) {
@@ -152,14 +162,14 @@ struct GravityJerkIJ {
     static __device__ __forceinline__ IState load_i(const Args &a, const Ctx &, int i) {
         return {a.xi[i], a.yi[i], a.zi[i], a.vxi[i], a.vyi[i], a.vzi[i]};
     }
-    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int j, float (&r)[8]) {
-        r[0] = a.x[j];
-        r[1] = a.y[j];
-        r[2] = a.z[j];
-        r[3] = a.m[j];
-        r[4] = a.vx[j];
-        r[5] = a.vy[j];
-        r[6] = a.vz[j];
+    static __device__ __forceinline__ void load_j(const Args &a, const Ctx &, int b, unsigned j, float (&r)[8]) {
+        r[0] = (a.x + b)[j];
+        r[1] = (a.y + b)[j];
+        r[2] = (a.z + b)[j];
+        r[3] = (a.m + b)[j];
+        r[4] = (a.vx + b)[j];
+        r[5] = (a.vy + b)[j];
+        r[6] = (a.vz + b)[j];
         r[7] = 0.0f;
     }
     static __device__ __forceinline__ void pad_j(float (&r)[8]) {
@@ -168,6 +178,11 @@ struct GravityJerkIJ {
         for (int c = 3; c < 8; ++c) r[c] = 0.0f;
     }
     static constexpr bool kSelf = false;  // separate sets: every pair is summed
+    template <bool POT>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+                                                      float (&acc)[kOut]) {
+        pair<POT>(j, i, eps2, acc);
+    }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
                                                 float (&acc)[7]) {

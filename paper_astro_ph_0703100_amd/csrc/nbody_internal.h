@@ -48,12 +48,19 @@ inline int partial_words(int precision, int outputs = kForceOutputs) {
 
 // Shape of one force launch.
 struct TileCfg {
-    int ipl = 4;     // i-particles per lane
+    int ipl = 4;     // i-particles per lane of an i-tile (kTPB * ipl particles)
     int jt = 256;    // j-particles per LDS tile
-    int nseg = 1;    // j-segments (grid y)
+    int nseg = 1;    // j-segments the scratch holds (PLAIN: the segments summed)
     int seg_len = 0; // j's per segment, a multiple of jt
-    int itiles = 0;  // i-tiles (grid x)
+    int itiles = 0;  // i-tiles
     int npad = 0;    // itiles * kTPB * ipl
+    // Launch of the grid engine (wave_engine.h): wseg segments of wseg_len j's, wpb waves
+    // per block, each holding 64 * wi i-particles, FP32 blocks of bj j's.
+    int wi = 1;
+    int wpb = 4;
+    int wseg = 1;    // at most nseg
+    int wseg_len = 0;
+    int bj = 128;
     int jl = 1;      // lanes per i-particle's j-range: 1 = grid engine, 8..64 = split engine
                      // (then itiles = blocks of 4 * (64 / jl) * ipl i's, nseg = 1)
     // Symmetric engine (sym = 1; jl = 1): block rows of 512 * ipl particles, nb rows,
@@ -206,25 +213,24 @@ struct JerkFinalizeArgs {
     double *pot;   // [n] or nullptr
 };
 
-// One work item of a ragged batch: an i-tile of one system against a j-range of the
+// One work item (block) of a ragged batch: some i's of one system against a j-range of the
 // same system.  Indices are global (into the concatenated arrays).
 struct BatchItem {
     int32_t sys;    // system index
-    int32_t i0;     // first i of the tile
-    int32_t ni;     // i's in the tile (<= 256 * IPL)
+    int32_t i0;     // first i
+    int32_t ni;     // i's
     int32_t j0;     // first j of the range
     int32_t nj;     // j's in the range
     int32_t col0;   // column of i0 in the system's partial planes (i0 - offset)
     int64_t part;   // word offset of this (system, segment)'s partial planes
-    int32_t npad;   // plane stride of the system (its i-tiles * 256 * IPL)
-    int32_t pad_;
+    int32_t npad;   // plane stride of the system
+    int32_t whole;  // 1: the range is the whole system, so the item stores the outputs
 };
 
-// Work queue of a persistent batched launch.
+// Work items of a batched launch, in decreasing order of cost.
 struct BatchSched {
     const BatchItem *items;
     int nitems;
-    unsigned int *counter;  // ticket, reset to 0 before every launch
     const float *eps;       // per-system softening [nsys]
     void *part;             // partial-sum words
 };
@@ -338,6 +344,9 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
 inline int force_engines(const nbody_opts &o) {
     return o.centre != NBODY_CENTRE_TILE ? kEngineSplit | kEngineSym : 0;
 }
+// i-records per lane of a grid-engine launch (ipl: asked for, or 0) of `blocks` pieces of 64
+// i's x 128 j's.
+int wave_ipl(int kernel, int precision, int64_t blocks, int ipl);
 size_t partial_bytes(const TileCfg &c, int precision, int outputs = kForceOutputs);
 size_t align_up(size_t v, size_t a);
 nbody_status check_common(int64_t n, const void *pos, const void *mass, float eps,
@@ -385,9 +394,10 @@ struct DeviceInfo {
 };
 const DeviceInfo &device_info();
 
-// Launchers (force.hip).
+// Launchers (force.hip).  A grid-engine launch with cfg.wseg == 1 stores the outputs (f)
+// itself; otherwise the finalize follows.
 nbody_status launch_pair(const TileCfg &cfg, int precision, bool with_pot, const PairArgs &a,
-                         hipStream_t s);
+                         const FinalizeArgs &f, hipStream_t s);
 nbody_status launch_finalize(int precision, const FinalizeArgs &a, hipStream_t s);
 // Split engine (cfg.jl > 1): pair sums and outputs in one launch (force_split.hip,
 // vjp_split.hip); the finalize arguments say what is stored.
@@ -399,7 +409,7 @@ nbody_status launch_vjp_split(const TileCfg &cfg, int precision, const VjpArgs &
 nbody_status launch_pair_sym(const TileCfg &cfg, int precision, bool with_pot,
                              const PairArgs &a, const FinalizeArgs &f, hipStream_t s);
 nbody_status launch_pair_ij(const TileCfg &cfg, int precision, bool with_pot, const IJPairArgs &a,
-                            hipStream_t s);
+                            const FinalizeArgs &f, hipStream_t s);
 // fp32(x - c) with c the FP64 mean of all positions (two kernels: block partial sums,
 // then a fused fixed-order final sum and conversion); scratch holds the partials.
 nbody_status launch_centred_convert(int64_t n, const double *pos64, double *scratch,
@@ -417,7 +427,7 @@ size_t centre_scratch_bytes();
 nbody_status launch_tile_centres(int64_t n, int itile, const double *pos64, double *centres,
                                  hipStream_t s);
 nbody_status launch_pair_tile(const TileCfg &cfg, int precision, bool with_pot,
-                              const TilePairArgs &a, hipStream_t s);
+                              const TilePairArgs &a, const FinalizeArgs &f, hipStream_t s);
 // Morton (Z-order) permutation of FP64 positions (morton.hip).
 nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, void *scratch,
                                  hipStream_t s);
@@ -445,10 +455,12 @@ nbody_status launch_adj_drift_kick(int64_t count, double *vbar, const double *xb
 nbody_status launch_adj_drift_kick_centre(int64_t n, double *vbar, const double *xbar, double *abar,
                                           double dt, double h, const double *next,
                                           double *centre_part, hipStream_t s);
-// Ragged batches (batched.hip).
-nbody_status batched_pair_kernel(int ipl, int jt, int precision, bool with_pot, const void **fn);
-nbody_status launch_batched_pair(int ipl, int jt, int precision, bool with_pot, int grid,
-                                 const PairArgs &a, const BatchSched &sc, hipStream_t s);
+// Ragged batches (batched.hip).  The pair launch stores the outputs (f) of the systems whose
+// items are whole, and partial sums of the others.  Blocks of `waves` waves share an item's
+// 64 * ipl i's and split its j's (PLAIN, whose sums stay one chain: one wave).
+nbody_status launch_batched_pair(int ipl, int jt, int waves, int precision, bool with_pot,
+                                 const PairArgs &a, const FinalizeArgs &f, const BatchSched &sc,
+                                 hipStream_t s);
 nbody_status launch_batched_finalize(int precision, const BatchFinalizeArgs &a, hipStream_t s);
 nbody_status launch_system_centres(int nsys, const int64_t *offsets, int64_t total,
                                    const double *pos64, double *centre, hipStream_t s);

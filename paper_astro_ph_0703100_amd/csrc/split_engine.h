@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kTPB) void split_kernel(typename Op::Args a, typena
             const int j = t * JT + jj;
             if (jj < JT) {
                 if (j < nj)
-                    Op::load_j(a, ctx, j, stage[p]);
+                    Op::load_j(a, ctx, 0, (unsigned)j, stage[p]);
                 else
                     Op::pad_j(stage[p]);
             }

@@ -36,7 +36,8 @@
 //   struct Ctx;                              // per-block context (e.g. a reference centre)
 //   static Ctx make_ctx(const Args&, int i0);
 //   static IState load_i(const Args&, const Ctx&, int i);
-//   static void load_j(const Args&, const Ctx&, int j, float (&r)[kJWords]);
+//   static void load_j(const Args&, const Ctx&, int b, unsigned j, float (&r)[kJWords]);
+//                                            // record b + j (b uniform over the wave)
 //   static void pad_j(float (&r)[kJWords]);  // a record that adds exactly zero
 //   static constexpr bool kSelf;             // i- and j-sets are one set (j == i exists)
 //   static void null_j(float (&r)[kJWords]); // (kSelf only) turns a j-record into one at
@@ -202,7 +203,7 @@ __device__ __forceinline__ void block_work(const typename Op::Args &a, float4 (*
             const int j = j0 + t * JT + jj;
             if (jj < JT) {
                 if (j < j1)
-                    Op::load_j(a, ctx, j, stage[q]);
+                    Op::load_j(a, ctx, 0, (unsigned)j, stage[q]);
                 else
                     Op::pad_j(stage[q]);
             }
@@ -294,28 +295,6 @@ __global__ __launch_bounds__(kTPB) void tile_kernel(typename Op::Args a) {
     constexpr int WO = Op::kOut * words_per_out<MODE>();
     void *out = static_cast<float *>(a.part) + (size_t)blockIdx.y * WO * plane;
     block_work<Op, IPL, JT, MODE, FULL>(a, tile, i0, ni, j0, nj, a.eps2, out, plane, (size_t)i0);
-}
-
-// Persistent launch over a list of work items (ragged batches of independent
-// systems).  Each block takes the next item from an atomic ticket until the list is
-// exhausted; items are sorted by decreasing cost so the tail is short.  Every item
-// writes its own partial slots, so results do not depend on which block ran it.
-template <class Op, int IPL, int JT, int MODE, bool FULL>
-__global__ __launch_bounds__(kTPB) void persistent_kernel(typename Op::Args a, BatchSched sc) {
-    __shared__ float4 tile[2][JT * (Op::kJWords / 4)];
-    __shared__ int s_item;
-    for (;;) {
-        if (threadIdx.x == 0) s_item = (int)atomicAdd(sc.counter, 1u);
-        __syncthreads();
-        const int it = s_item;
-        __syncthreads();  // all lanes hold `it` before lane 0 can overwrite s_item
-        if (it >= sc.nitems) break;
-        const BatchItem w = sc.items[it];
-        const float e = sc.eps[w.sys];
-        void *out = static_cast<float *>(sc.part) + w.part;
-        block_work<Op, IPL, JT, MODE, FULL>(a, tile, w.i0, w.ni, w.j0, w.nj, e * e, out,
-                                            (size_t)w.npad, (size_t)w.col0);
-    }
 }
 
 // Fixed-order sums of the segment partials.  Segment s holds, per output c, the words
@@ -449,46 +428,6 @@ TileFn<Op> pick_tile(int ipl, int jt, int mode, bool full) {
         case 2: return pick_jt<Op, 2>(jt, mode, full);
         case 4: return pick_jt<Op, 4>(jt, mode, full);
         case 8: return pick_jt<Op, 8>(jt, mode, full);
-    }
-    return nullptr;
-}
-
-template <class Op>
-using PersistFn = void (*)(typename Op::Args, BatchSched);
-
-template <class Op, int IPL, int JT, int MODE>
-PersistFn<Op> ppick_full(bool full) {
-    return full ? persistent_kernel<Op, IPL, JT, MODE, true> : persistent_kernel<Op, IPL, JT, MODE, false>;
-}
-
-template <class Op, int IPL, int JT>
-PersistFn<Op> ppick_mode(int mode, bool full) {
-    switch (mode) {
-        case NBODY_PLAIN: return ppick_full<Op, IPL, JT, NBODY_PLAIN>(full);
-        case NBODY_FP64RED: return ppick_full<Op, IPL, JT, NBODY_FP64RED>(full);
-        case NBODY_COMP: return ppick_full<Op, IPL, JT, NBODY_COMP>(full);
-    }
-    return nullptr;
-}
-
-template <class Op, int IPL>
-PersistFn<Op> ppick_jt(int jt, int mode, bool full) {
-    switch (jt) {
-        case 64: return ppick_mode<Op, IPL, 64>(mode, full);
-        case 128: return ppick_mode<Op, IPL, 128>(mode, full);
-        case 256: return ppick_mode<Op, IPL, 256>(mode, full);
-        case 512: return ppick_mode<Op, IPL, 512>(mode, full);
-    }
-    return nullptr;
-}
-
-template <class Op>
-PersistFn<Op> pick_persistent(int ipl, int jt, int mode, bool full) {
-    switch (ipl) {
-        case 1: return ppick_jt<Op, 1>(jt, mode, full);
-        case 2: return ppick_jt<Op, 2>(jt, mode, full);
-        case 4: return ppick_jt<Op, 4>(jt, mode, full);
-        case 8: return ppick_jt<Op, 8>(jt, mode, full);
     }
     return nullptr;
 }
