@@ -31,12 +31,12 @@ nbody_status vjp_f32_core(int64_t n, const float *pos, const float *mass, float 
                           const TileCfg &cfg, void *part, hipStream_t s) {
     const float e2 = eps * eps;
     VjpArgs va{pos,   pos + n, pos + 2 * n, mass, g_acc, g_acc + n, g_acc + 2 * n,
-               g_pot, (int)n,  cfg.seg_len, e2,   part,  cfg.npad};
-    VjpFinalizeArgs fa{part,      cfg.nseg, cfg.npad,           (int)n, g_pot,
+               g_pot, (int)n,  cfg.wseg_len, e2,  part,  cfg.npad};
+    VjpFinalizeArgs fa{part,      cfg.wseg, cfg.npad,           (int)n, g_pot,
                        grad_pos,  grad_mass, accumulate ? 1 : 0, g_acc};
     if (cfg.jl > 1) return launch_vjp_split(cfg, o.precision, va, grad_mass != nullptr, fa, s);
-    nbody_status st = launch_vjp(cfg, o.precision, va, grad_mass != nullptr, s);
-    if (st) return st;
+    nbody_status st = launch_vjp(cfg, o.precision, va, grad_mass != nullptr, fa, s);
+    if (st || cfg.wseg == 1) return st;
     return launch_vjp_finalize(o.precision, fa, s);
 }
 
@@ -56,10 +56,11 @@ nbody_status vjp_f64_core(int64_t n, const double *pos64, const float *mass, flo
         if ((st = launch_tile_centres(n, itile, pos64, centres, s))) return st;
         const float e2 = eps * eps;
         VjpTileArgs va{pos64, pos64 + n, pos64 + 2 * n, mass, g_acc, g_acc + n, g_acc + 2 * n,
-                       g_pot, (int)n, cfg.seg_len, e2, ws.part, cfg.npad, centres, itile};
-        if ((st = launch_vjp_tile(cfg, o.precision, va, grad_mass != nullptr, s))) return st;
-        VjpFinalizeArgs fa{ws.part,  cfg.nseg, cfg.npad,           (int)n, g_pot,
+                       g_pot, (int)n, cfg.wseg_len, e2, ws.part, cfg.npad, centres, itile};
+        VjpFinalizeArgs fa{ws.part,  cfg.wseg, cfg.npad,           (int)n, g_pot,
                            grad_pos, grad_mass, accumulate ? 1 : 0, g_acc};
+        st = launch_vjp_tile(cfg, o.precision, va, grad_mass != nullptr, fa, s);
+        if (st || cfg.wseg == 1) return st;
         return launch_vjp_finalize(o.precision, fa, s);
     }
     if (o.centre == NBODY_CENTRE_SYSTEM) {

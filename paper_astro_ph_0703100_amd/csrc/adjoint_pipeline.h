@@ -28,11 +28,55 @@ namespace nbody {
 
 namespace {
 
+// Adjoint::pair instruction by instruction (so bitwise the same result), in the order and
+// with the s_nop that gfx950 runs fastest (see gravity_pair_timed).
+#define NBODY_ADJOINT_PAIR(MASS_INSTR)                                                        \
+    asm("v_sub_f32 %[dx], %[jx], %[xi]\n\t"                                                   \
+        "v_sub_f32 %[dy], %[jy], %[yi]\n\t"                                                   \
+        "v_sub_f32 %[dz], %[jz], %[zi]\n\t"                                                   \
+        "v_fma_f32 %[t], %[dx], %[dx], %[e2]\n\t"                                             \
+        "v_fmac_f32 %[t], %[dy], %[dy]\n\t"                                                   \
+        "v_fmac_f32 %[t], %[dz], %[dz]\n\t"                                                   \
+        "v_mul_f32 %[gd], %[jgx], %[dx]\n\t"                                                  \
+        "v_fmac_f32 %[gd], %[jgy], %[dy]\n\t"                                                 \
+        "v_fmac_f32 %[gd], %[jgz], %[dz]\n\t"                                                 \
+        "v_mul_f32 %[w], %[gxi], %[dx]\n\t"                                                   \
+        "v_fmac_f32 %[w], %[gyi], %[dy]\n\t"                                                  \
+        "v_fmac_f32 %[w], %[gzi], %[dz]\n\t"                                                  \
+        "v_mul_f32 %[w], %[jm], %[w]\n\t"                                                     \
+        "v_fmac_f32 %[w], %[nmi], %[gd]\n\t"                                                  \
+        "v_mul_f32 %[q], %[jm], %[npi]\n\t"                                                   \
+        "v_fmac_f32 %[q], %[nmi], %[jp]\n\t"                                                  \
+        "s_nop 0\n\t"                                                                         \
+        "v_rsq_f32 %[t], %[t]\n\t"                                                            \
+        "s_nop 0\n\t"                                                                         \
+        "v_mul_f32 %[u], %[t], %[t]\n\t"                                                      \
+        "v_mul_f32 %[r3], %[t], %[u]\n\t"                                                     \
+        "v_mul_f32 %[u], 0x40400000, %[u]\n\t"                                                \
+        "v_fmac_f32 %[q], %[u], %[w]\n\t"                                                     \
+        "v_mul_f32 %[w], %[mi], %[r3]\n\t"                                                    \
+        "v_mul_f32 %[q], %[r3], %[q]\n\t"                                                     \
+        "v_fmac_f32 %[ax], %[w], %[jgx]\n\t"                                                  \
+        "v_fmac_f32 %[ay], %[w], %[jgy]\n\t"                                                  \
+        "v_fmac_f32 %[az], %[w], %[jgz]\n\t"                                                  \
+        "v_fmac_f32 %[bk], %[jm], %[r3]\n\t"                                                  \
+        "v_fmac_f32 %[ax], %[q], %[dx]\n\t"                                                   \
+        "v_fmac_f32 %[ay], %[q], %[dy]\n\t"                                                   \
+        "v_fmac_f32 %[az], %[q], %[dz]\n\t" MASS_INSTR                                        \
+        : [ax] "+&v"(acc[0]), [ay] "+&v"(acc[1]), [az] "+&v"(acc[2]), [bk] "+&v"(acc[3]),     \
+          [ms] "+&v"(acc[4]), [dx] "=&v"(dx), [dy] "=&v"(dy), [dz] "=&v"(dz), [t] "=&v"(t),   \
+          [u] "=&v"(u), [r3] "=&v"(r3), [gd] "=&v"(gd), [w] "=&v"(w), [q] "=&v"(q)            \
+        : [jx] "v"(j[0]), [jy] "v"(j[1]), [jz] "v"(j[2]), [jm] "v"(j[3]), [jgx] "v"(j[4]),    \
+          [jgy] "v"(j[5]), [jgz] "v"(j[6]), [jp] "v"(j[7]), [xi] "v"(k.x), [yi] "v"(k.y),     \
+          [zi] "v"(k.z), [mi] "v"(k.m), [nmi] "v"(k.nm), [gxi] "v"(k.gx), [gyi] "v"(k.gy),    \
+          [gzi] "v"(k.gz), [npi] "v"(k.np), [e2] "s"(eps2))
+
 struct Adjoint {
     static constexpr int kJWords = 8;  // x, y, z, m, gx, gy, gz, p
     static constexpr int kOut = 5;     // see above: three position sums, B_k, mass sum
     // 128 j's per compensation step (32 before: 1.8 % slower at N = 16384 and 131072).
     static constexpr int kBlockJ = nbody::kBlockJ;
+    static constexpr int kMaxIpl = 2;
     using Args = VjpArgs;
     struct IState {
         float x, y, z, m, nm, gx, gy, gz, np;  // nm = -m_k, np = -p_k
@@ -75,10 +119,15 @@ struct Adjoint {
         for (int c = 3; c < 8; ++c) r[c] = 0.0f;
     }
 
-    template <bool MASS>
-    static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
+    template <bool MASS, bool MANY>
+    static __device__ __forceinline__ void pair_timed(const float *j, const IState &k, float eps2,
                                                       float (&acc)[kOut]) {
-        pair<MASS>(j, i, eps2, acc);
+        float dx, dy, dz, t, u, r3, gd, w, q;
+        if constexpr (MASS)
+            NBODY_ADJOINT_PAIR("v_fmac_f32 %[ms], %[gd], %[r3]\n\t"
+                               "v_fmac_f32 %[ms], %[jp], %[t]\n\t");
+        else
+            NBODY_ADJOINT_PAIR("");
     }
     template <bool MASS>
     static __device__ __forceinline__ void pair(const float *j, const IState &k, float eps2,
@@ -119,6 +168,8 @@ struct Adjoint {
     }
 };
 
+#undef NBODY_ADJOINT_PAIR
+
 // The same on FP64 positions relative to the block's i-tile centre: i's and staged j's
 // are converted as fp32(x - c_I) while loaded (for j == k the two conversions are the
 // same operation, so d = 0 exactly and the null record adds nothing).
@@ -126,6 +177,7 @@ struct AdjointTile {
     static constexpr int kJWords = 8;
     static constexpr int kOut = 5;
     static constexpr int kBlockJ = Adjoint::kBlockJ;
+    static constexpr int kMaxIpl = 2;
     using Args = VjpTileArgs;
     using IState = Adjoint::IState;
     struct Ctx {
@@ -156,10 +208,10 @@ struct AdjointTile {
     static __device__ __forceinline__ void pad_j(float (&r)[8]) { Adjoint::pad_j(r); }
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { Adjoint::null_j(r); }
-    template <bool MASS>
+    template <bool MASS, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[kOut]) {
-        pair<MASS>(j, i, eps2, acc);
+        Adjoint::pair_timed<MASS, MANY>(j, i, eps2, acc);
     }
     template <bool MASS>
     static __device__ __forceinline__ void pair(const float *j, const IState &k, float eps2,

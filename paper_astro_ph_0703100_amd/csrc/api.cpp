@@ -145,16 +145,21 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
         return;
     }
     if (nseg_asked) return;
-    // j's per wave, in blocks of 128: at most 3, 4 and 6 for ipl 1, 2 and 4 (short waves keep
-    // the last ones busy together, longer ones cost less to start: N = 16384 with 2 / 3 / 4
-    // blocks 83.9 / 82.3 / 84.2 us), fewer where there would be under 4 waves per SIMD.
+    // j's per wave, in blocks of 128: up to 3, 8 and 6 for ipl 1, 2 and 4 (short waves keep
+    // the last ones busy together, longer ones cost less to start: N = 16384, ipl 1, force
+    // with 2 / 3 / 4 blocks 83.9 / 82.3 / 84.2 us, jerk 154.7 / 151.4 / 157.1 us; ipl 2, jerk
+    // at N = 32768 with 4 / 6 / 8 blocks 573 / 586 / 589 us, at 131072 9471 / 9432 / 9295
+    // us), fewer where there would be under 4 waves per SIMD.
     const int64_t waves1 = (ni + 64 * c->wi - 1) / (64 * c->wi) * nb128;  // with one block each
-    const int64_t most = c->wi == 1 ? 3 : c->wi == 2 ? 4 : 6;
-    const int64_t per = std::max<int64_t>(1, std::min(most, waves1 / 4000));
+    const int64_t per = c->wi == 1   ? std::max<int64_t>(1, std::min<int64_t>(3, waves1 / 4000))
+                        : c->wi == 2 ? std::max<int64_t>(4, std::min<int64_t>(8, waves1 / 32000))
+                                     : 6;
     int64_t seg = (nb128 + 4 * per - 1) / (4 * per);
-    if (nb128 <= 16 * (per + 1)) {
-        // The waves of one block cover every j: one launch, no partial sums.  A block of j's
-        // more per wave costs about as much as the finalize's launch (5 us).
+    // The waves of one block cover every j: one launch, no partial sums.  One block of j's
+    // more per wave costs the force about as much as the finalize's launch (5 us); a chain of
+    // 128 force-jerk or adjoint pairs takes 7.5 us (N = 3000: 18 us with the finalize, 33 us
+    // in one launch of 2 blocks per wave).
+    if (nb128 <= 16 * (per + (kernel == KERNEL_FORCE ? 1 : 0))) {
         c->wpb = (int)std::min<int64_t>(16, (nb128 + per - 1) / per);
         seg = 1;
     }

@@ -30,17 +30,24 @@ __device__ __forceinline__ void gravity_pair(const float *j, float xi, float yi,
     if (POT) acc[3] = acc[3] - mri;
 }
 
-// The same pair term, instruction by instruction (so bitwise the same result), in the
-// order and with the s_nop that gfx950 runs fastest with several waves on a SIMD.
+// The same pair term, instruction by instruction (so bitwise the same result), in a fixed
+// order with a short s_nop on each side of v_rsq_f32.  Two waves of a SIMD run FP32
+// instructions side by side (measured: 2.07 clocks per wave64 instruction, 4.7 for a lone
+// wave, 4 with a scalar operand, 8.1 for v_rsq_f32), but after v_rsq_f32 they fall out of
+// step unless it is fenced: 13 multiplications and one v_rsq_f32 take 59 clocks as they
+// are, 35 with s_nop 0 or 1 before it (34 is the sum of the parts).  With several records
+// per lane (MANY) s_nop 2 before it and 1 after the pair did best: 36.8 to 37.3 clocks per
+// pair against 39.5 as the compiler orders it.  With one, longer gaps only cost the kernels
+// with few waves (a lone wave: 98 clocks per pair against 86).
 // UNIFORM: eps2 is the same for every lane (a scalar register).
-#define NBODY_GRAVITY_PAIR(POT_INSTR, E2_CONSTRAINT)                                          \
+#define NBODY_GRAVITY_PAIR(POT_INSTR, E2_CONSTRAINT, BEFORE, AFTER)                           \
     asm("v_sub_f32 %[dx], %[jx], %[xi]\n\t"                                                   \
         "v_sub_f32 %[dy], %[jy], %[yi]\n\t"                                                   \
         "v_sub_f32 %[dz], %[jz], %[zi]\n\t"                                                   \
         "v_fma_f32 %[t], %[dx], %[dx], %[e2]\n\t"                                             \
         "v_fmac_f32 %[t], %[dy], %[dy]\n\t"                                                   \
         "v_fmac_f32 %[t], %[dz], %[dz]\n\t"                                                   \
-        "s_nop 2\n\t"                                                                         \
+        BEFORE                                                                                \
         "v_rsq_f32 %[t], %[t]\n\t"                                                            \
         "s_nop 0\n\t"                                                                         \
         "v_mul_f32 %[u], %[jm], %[t]\n\t"                                                     \
@@ -48,25 +55,34 @@ __device__ __forceinline__ void gravity_pair(const float *j, float xi, float yi,
         "v_mul_f32 %[t], %[u], %[t]\n\t"                                                      \
         "v_fmac_f32 %[ax], %[t], %[dx]\n\t"                                                   \
         "v_fmac_f32 %[ay], %[t], %[dy]\n\t"                                                   \
-        "v_fmac_f32 %[az], %[t], %[dz]\n\t" POT_INSTR                                         \
-        "s_nop 1"                                                                             \
-        : [ax] "+v"(acc[0]), [ay] "+v"(acc[1]), [az] "+v"(acc[2]), [ph] "+v"(acc[3]),         \
+        "v_fmac_f32 %[az], %[t], %[dz]\n\t" POT_INSTR AFTER                                   \
+        : [ax] "+&v"(acc[0]), [ay] "+&v"(acc[1]), [az] "+&v"(acc[2]), [ph] "+&v"(acc[3]),     \
           [dx] "=&v"(dx), [dy] "=&v"(dy), [dz] "=&v"(dz), [t] "=&v"(t), [u] "=&v"(u)          \
         : [jx] "v"(j[0]), [jy] "v"(j[1]), [jz] "v"(j[2]), [jm] "v"(j[3]), [xi] "v"(xi),       \
           [yi] "v"(yi), [zi] "v"(zi), [e2] E2_CONSTRAINT(eps2))
 
-template <bool POT, bool UNIFORM>
+template <bool POT, bool UNIFORM, bool MANY>
 __device__ __forceinline__ void gravity_pair_timed(const float *j, float xi, float yi, float zi,
                                                    float eps2, float (&acc)[4]) {
+#define NBODY_POT "v_sub_f32 %[ph], %[ph], %[u]\n\t"
     float dx, dy, dz, t, u;
-    if constexpr (POT && UNIFORM)
-        NBODY_GRAVITY_PAIR("v_sub_f32 %[ph], %[ph], %[u]\n\t", "s");
+    if constexpr (POT && UNIFORM && MANY)
+        NBODY_GRAVITY_PAIR(NBODY_POT, "s", "s_nop 2\n\t", "s_nop 1");
+    else if constexpr (POT && UNIFORM)
+        NBODY_GRAVITY_PAIR(NBODY_POT, "s", "s_nop 0\n\t", "");
+    else if constexpr (UNIFORM && MANY)
+        NBODY_GRAVITY_PAIR("", "s", "s_nop 2\n\t", "s_nop 1");
     else if constexpr (UNIFORM)
-        NBODY_GRAVITY_PAIR("", "s");
+        NBODY_GRAVITY_PAIR("", "s", "s_nop 0\n\t", "");
+    else if constexpr (POT && MANY)
+        NBODY_GRAVITY_PAIR(NBODY_POT, "v", "s_nop 2\n\t", "s_nop 1");
     else if constexpr (POT)
-        NBODY_GRAVITY_PAIR("v_sub_f32 %[ph], %[ph], %[u]\n\t", "v");
+        NBODY_GRAVITY_PAIR(NBODY_POT, "v", "s_nop 0\n\t", "");
+    else if constexpr (MANY)
+        NBODY_GRAVITY_PAIR("", "v", "s_nop 2\n\t", "s_nop 1");
     else
-        NBODY_GRAVITY_PAIR("", "v");
+        NBODY_GRAVITY_PAIR("", "v", "s_nop 0\n\t", "");
+#undef NBODY_POT
 }
 #undef NBODY_GRAVITY_PAIR
 
@@ -107,10 +123,10 @@ struct Gravity {
                                                 float (&acc)[4]) {
         gravity_pair<POT>(j, i.x, i.y, i.z, eps2, acc);
     }
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[4]) {
-        gravity_pair_timed<POT, true>(j, i.x, i.y, i.z, eps2, acc);
+        gravity_pair_timed<POT, true, MANY>(j, i.x, i.y, i.z, eps2, acc);
     }
 };
 
@@ -153,10 +169,10 @@ struct GravityTile {
                                                 float (&acc)[4]) {
         gravity_pair<POT>(j, i.x, i.y, i.z, eps2, acc);
     }
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[4]) {
-        gravity_pair_timed<POT, true>(j, i.x, i.y, i.z, eps2, acc);
+        gravity_pair_timed<POT, true, MANY>(j, i.x, i.y, i.z, eps2, acc);
     }
 };
 
@@ -202,10 +218,10 @@ struct GravityIJ {
                                                 float (&acc)[4]) {
         gravity_pair<POT>(j, i.x, i.y, i.z, i.e2, acc);
     }
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float,
                                                       float (&acc)[4]) {
-        gravity_pair_timed<POT, false>(j, i.x, i.y, i.z, i.e2, acc);
+        gravity_pair_timed<POT, false, MANY>(j, i.x, i.y, i.z, i.e2, acc);
     }
 };
 

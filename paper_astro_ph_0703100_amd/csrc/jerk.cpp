@@ -11,10 +11,8 @@
 namespace nbody {
 namespace {
 
-constexpr int kJerkOut = 7;
-
 size_t jerk_partial_bytes(const TileCfg &c, int precision) {
-    const size_t words = (size_t)(precision == NBODY_PLAIN ? 1 : 2) * kJerkOut;
+    const size_t words = (size_t)(precision == NBODY_PLAIN ? 1 : 2) * kJerkOutputs;
     return align_up((size_t)c.nseg * words * (size_t)c.npad * 4, 256);
 }
 
@@ -57,11 +55,11 @@ nbody_status jerk_core(int64_t n, const float *pos, const float *vel, const floa
                        const TileCfg &cfg, void *part, hipStream_t s) {
     const float e2 = eps * eps;
     JerkArgs a{pos, pos + n, pos + 2 * n, mass, vel, vel + n, vel + 2 * n,
-               (int)n, cfg.seg_len, e2, part, cfg.npad};
-    nbody_status st = launch_jerk(cfg, o.precision, pot != nullptr, a, s);
-    if (st) return st;
-    JerkFinalizeArgs fa{part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+               (int)n, cfg.wseg_len, e2, part, cfg.npad};
+    JerkFinalizeArgs fa{part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,  jerk,     pot};
+    nbody_status st = launch_jerk(cfg, o.precision, pot != nullptr, a, fa, s);
+    if (st || cfg.wseg == 1) return st;
     return launch_jerk_finalize(o.precision, fa, s);
 }
 
@@ -81,10 +79,11 @@ nbody_status jerk_f64_core(int64_t n, const double *pos64, const double *vel64, 
         if ((st = launch_tile_centres(n, itile, vel64, cv, s))) return st;
         const float e2 = eps * eps;
         JerkTileArgs a{pos64, pos64 + n, pos64 + 2 * n, mass, vel64, vel64 + n, vel64 + 2 * n,
-                       (int)n, cfg.seg_len, e2, w.part, cfg.npad, cx, cv, itile};
-        if ((st = launch_jerk_tile(cfg, o.precision, pot != nullptr, a, s))) return st;
-        JerkFinalizeArgs fa{w.part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+                       (int)n, cfg.wseg_len, e2, w.part, cfg.npad, cx, cv, itile};
+        JerkFinalizeArgs fa{w.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                             acc,    jerk,     pot};
+        st = launch_jerk_tile(cfg, o.precision, pot != nullptr, a, fa, s);
+        if (st || cfg.wseg == 1) return st;
         return launch_jerk_finalize(o.precision, fa, s);
     }
     if (o.centre == NBODY_CENTRE_SYSTEM) {
@@ -239,9 +238,10 @@ nbody_status nbody_force_jerk_ij(int64_t ni, const float *pos_i, const float *ve
     if ((st = get_workspace(o, jerk_partial_bytes(cfg, o.precision), s, &ws))) return st;
     JerkIJArgs a{pos_i, pos_i + ni, pos_i + 2 * ni, vel_i, vel_i + ni, vel_i + 2 * ni,
                  pos_j, pos_j + nj, pos_j + 2 * nj, mass_j, vel_j, vel_j + nj, vel_j + 2 * nj,
-                 (int)ni, (int)nj, cfg.seg_len, e2, ws, cfg.npad};
-    if ((st = launch_jerk_ij(cfg, o.precision, pot != nullptr, a, s))) return st;
-    JerkFinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, jerk, pot};
+                 (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
+    JerkFinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, jerk, pot};
+    st = launch_jerk_ij(cfg, o.precision, pot != nullptr, a, fa, s);
+    if (st || cfg.wseg == 1) return st;
     return launch_jerk_finalize(o.precision, fa, s);
 }
 

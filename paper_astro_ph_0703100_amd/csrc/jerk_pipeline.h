@@ -50,12 +50,65 @@ __device__ __forceinline__ void jerk_pair(const float *j, float xi, float yi, fl
     if (POT) acc[6] = acc[6] - mri;
 }
 
+// The same pair term, instruction by instruction (so bitwise the same result), in the order
+// and with the s_nop that gfx950 runs fastest (see gravity_pair_timed).
+#define NBODY_JERK_PAIR(POT_INSTR)                                                            \
+    asm("v_sub_f32 %[dx], %[jx], %[xi]\n\t"                                                   \
+        "v_sub_f32 %[dy], %[jy], %[yi]\n\t"                                                   \
+        "v_sub_f32 %[dz], %[jz], %[zi]\n\t"                                                   \
+        "v_fma_f32 %[t], %[dx], %[dx], %[e2]\n\t"                                             \
+        "v_fmac_f32 %[t], %[dy], %[dy]\n\t"                                                   \
+        "v_fmac_f32 %[t], %[dz], %[dz]\n\t"                                                   \
+        "v_sub_f32 %[wx], %[jvx], %[vxi]\n\t"                                                 \
+        "v_sub_f32 %[wy], %[jvy], %[vyi]\n\t"                                                 \
+        "v_sub_f32 %[wz], %[jvz], %[vzi]\n\t"                                                 \
+        "v_mul_f32 %[q], %[dx], %[wx]\n\t"                                                    \
+        "v_fmac_f32 %[q], %[dy], %[wy]\n\t"                                                   \
+        "v_fmac_f32 %[q], %[dz], %[wz]\n\t"                                                   \
+        "s_nop 0\n\t"                                                                         \
+        "v_rsq_f32 %[t], %[t]\n\t"                                                            \
+        "s_nop 0\n\t"                                                                         \
+        "v_mul_f32 %[u], %[t], %[t]\n\t"                                                      \
+        "v_mul_f32 %[t], %[jm], %[t]\n\t"                                                     \
+        "v_mul_f32 %[q], %[q], %[u]\n\t"                                                      \
+        "v_mul_f32 %[u], %[t], %[u]\n\t"                                                      \
+        "v_mul_f32 %[q], 0x40400000, %[q]\n\t"                                                \
+        "v_fma_f32 %[wx], -%[q], %[dx], %[wx]\n\t"                                            \
+        "v_fma_f32 %[wy], -%[q], %[dy], %[wy]\n\t"                                            \
+        "v_fma_f32 %[wz], -%[q], %[dz], %[wz]\n\t"                                            \
+        "v_fmac_f32 %[ax], %[u], %[dx]\n\t"                                                   \
+        "v_fmac_f32 %[ay], %[u], %[dy]\n\t"                                                   \
+        "v_fmac_f32 %[az], %[u], %[dz]\n\t"                                                   \
+        "v_fmac_f32 %[bx], %[u], %[wx]\n\t"                                                   \
+        "v_fmac_f32 %[by], %[u], %[wy]\n\t"                                                   \
+        "v_fmac_f32 %[bz], %[u], %[wz]\n\t" POT_INSTR                                         \
+        : [ax] "+&v"(acc[0]), [ay] "+&v"(acc[1]), [az] "+&v"(acc[2]), [bx] "+&v"(acc[3]),     \
+          [by] "+&v"(acc[4]), [bz] "+&v"(acc[5]), [ph] "+&v"(acc[6]), [dx] "=&v"(dx),         \
+          [dy] "=&v"(dy), [dz] "=&v"(dz), [wx] "=&v"(wx), [wy] "=&v"(wy), [wz] "=&v"(wz),     \
+          [t] "=&v"(t), [u] "=&v"(u), [q] "=&v"(q)                                            \
+        : [jx] "v"(j[0]), [jy] "v"(j[1]), [jz] "v"(j[2]), [jm] "v"(j[3]), [jvx] "v"(j[4]),    \
+          [jvy] "v"(j[5]), [jvz] "v"(j[6]), [xi] "v"(xi), [yi] "v"(yi), [zi] "v"(zi),         \
+          [vxi] "v"(vxi), [vyi] "v"(vyi), [vzi] "v"(vzi), [e2] "s"(eps2))
+
+template <bool POT>
+__device__ __forceinline__ void jerk_pair_timed(const float *j, float xi, float yi, float zi,
+                                                float vxi, float vyi, float vzi, float eps2,
+                                                float (&acc)[7]) {
+    float dx, dy, dz, wx, wy, wz, t, u, q;
+    if constexpr (POT)
+        NBODY_JERK_PAIR("v_sub_f32 %[ph], %[ph], %[t]\n\t");
+    else
+        NBODY_JERK_PAIR("");
+}
+#undef NBODY_JERK_PAIR
+
 struct GravityJerk {
     static constexpr int kJWords = 8;
     static constexpr int kOut = 7;  // ax, ay, az, jx, jy, jz, phi
     // 14 two-sum operations per block of 128 pairs (64 before: 1.6 % slower, and at
     // 256-j tiles the four unrolled blocks took 85 VGPRs, 5 waves per SIMD).
     static constexpr int kBlockJ = nbody::kBlockJ;
+    static constexpr int kMaxIpl = 2;
     using Args = JerkArgs;
     struct IState {
         float x, y, z, vx, vy, vz;
@@ -85,10 +138,10 @@ struct GravityJerk {
     // The j == i pair: same position and velocity, no mass.
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { r[3] = 0.0f; }
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[kOut]) {
-        pair<POT>(j, i, eps2, acc);
+        jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
@@ -105,6 +158,7 @@ struct GravityJerkTile {
     static constexpr int kJWords = 8;
     static constexpr int kOut = 7;
     static constexpr int kBlockJ = GravityJerk::kBlockJ;
+    static constexpr int kMaxIpl = 2;
     using Args = JerkTileArgs;
     using IState = GravityJerk::IState;
     struct Ctx {
@@ -133,10 +187,10 @@ struct GravityJerkTile {
     static __device__ __forceinline__ void pad_j(float (&r)[8]) { GravityJerk::pad_j(r); }
     static constexpr bool kSelf = true;
     static __device__ __forceinline__ void null_j(float (&r)[8]) { GravityJerk::null_j(r); }
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[kOut]) {
-        pair<POT>(j, i, eps2, acc);
+        jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
@@ -153,6 +207,7 @@ struct GravityJerkIJ {
     static constexpr int kJWords = 8;
     static constexpr int kOut = 7;
     static constexpr int kBlockJ = GravityJerk::kBlockJ;
+    static constexpr int kMaxIpl = 2;
     using Args = JerkIJArgs;
     using IState = GravityJerk::IState;
     struct Ctx {};
@@ -178,10 +233,10 @@ struct GravityJerkIJ {
         for (int c = 3; c < 8; ++c) r[c] = 0.0f;
     }
     static constexpr bool kSelf = false;  // separate sets: every pair is summed
-    template <bool POT>
+    template <bool POT, bool MANY>
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[kOut]) {
-        pair<POT>(j, i, eps2, acc);
+        jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
     template <bool POT>
     static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,

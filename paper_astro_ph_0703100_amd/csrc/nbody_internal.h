@@ -39,6 +39,8 @@ constexpr int kBlockJ = 128;
 // position sums, the sum that multiplies the particle's own cotangent, the mass sum).
 constexpr int kForceOutputs = 4;
 constexpr int kVjpOutputs = 5;
+// Outputs per particle of the force-jerk-potential pipeline (a, jerk, phi).
+constexpr int kJerkOutputs = 7;
 
 // Words (4-byte) of partial sums written per i-particle and j-segment for `outputs`
 // outputs (compensated: hi and lo; FP64-reduced: one double).
@@ -466,25 +468,26 @@ nbody_status launch_system_centres(int nsys, const int64_t *offsets, int64_t tot
                                    const double *pos64, double *centre, hipStream_t s);
 nbody_status launch_batched_convert(int64_t total, const double *pos64, const int32_t *sys_of,
                                     const double *centre, float *pos32, hipStream_t s);
-// Force-jerk-potential kernels and their FP64 finalize (jerk.hip, jerk_tile.hip, jerk_ij.hip).
+// Force-jerk-potential kernels and their FP64 finalize (jerk.hip, jerk_tile.hip, jerk_ij.hip);
+// with cfg.wseg == 1 the pair launch stores the outputs itself, as for the force.
 nbody_status launch_jerk(const TileCfg &cfg, int precision, bool with_pot, const JerkArgs &a,
-                         hipStream_t s);
+                         const JerkFinalizeArgs &f, hipStream_t s);
 nbody_status launch_jerk_finalize(int precision, const JerkFinalizeArgs &a, hipStream_t s);
 nbody_status launch_jerk_tile(const TileCfg &cfg, int precision, bool with_pot,
-                              const JerkTileArgs &a, hipStream_t s);
+                              const JerkTileArgs &a, const JerkFinalizeArgs &f, hipStream_t s);
 nbody_status launch_jerk_ij(const TileCfg &cfg, int precision, bool with_pot, const JerkIJArgs &a,
-                            hipStream_t s);
+                            const JerkFinalizeArgs &f, hipStream_t s);
 // Fourth-order Hermite predictor and corrector (hermite.hip).
 nbody_status launch_hermite_predict(int64_t n, const double *x, const double *v, const double *a,
                                     const double *j, double dt, double *xp, double *vp,
                                     hipStream_t s);
 nbody_status launch_hermite_correct(int64_t n, double *x, double *v, double *a, double *j,
                                     const double *a1, const double *j1, double dt, hipStream_t s);
-// Adjoint pair kernels and their FP64 finalize (vjp.hip, vjp_tile.hip).
+// Adjoint pair kernels and their FP64 finalize (vjp.hip, vjp_tile.hip), likewise.
 nbody_status launch_vjp(const TileCfg &cfg, int precision, const VjpArgs &a, bool with_mass,
-                        hipStream_t s);
+                        const VjpFinalizeArgs &f, hipStream_t s);
 nbody_status launch_vjp_tile(const TileCfg &cfg, int precision, const VjpTileArgs &a,
-                             bool with_mass, hipStream_t s);
+                             bool with_mass, const VjpFinalizeArgs &f, hipStream_t s);
 nbody_status launch_vjp_finalize(int precision, const VjpFinalizeArgs &a, hipStream_t s);
 
 }  // namespace nbody

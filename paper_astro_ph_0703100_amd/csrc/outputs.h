@@ -28,6 +28,28 @@ struct ForceOut {
     }
 };
 
+// Force, jerk and potential: slots 0-2 the acceleration, 3-5 the jerk, 6 the potential
+// (optionally with the j == i term -m_i / eps, formed in FP64).  Slot c stores output c.
+struct JerkOut {
+    using Args = JerkFinalizeArgs;
+    static constexpr int kOutputs = kJerkOutputs;
+    // Store slots: 7, or 6 without the last output (no potential).
+    static constexpr int stores(bool full) { return full ? 7 : 6; }
+    template <class Sum>
+    static __device__ __forceinline__ void put(const Args &a, int i, int c, Sum sum) {
+        double r = sum(c);
+        const size_t n = (size_t)a.n;
+        if (c == 6) {
+            if (a.include_self) r -= (double)a.m[i] / (double)a.eps;
+            a.pot[i] = r;
+        } else if (c < 3) {
+            a.acc[c * n + i] = r;
+        } else {
+            a.jerk[(c - 3) * n + i] = r;
+        }
+    }
+};
+
 // Adjoint: slots 0, 1, 2 are dL/dx_i = sum(c) - g_i,c * sum(3) (g_i the particle's own
 // cotangent, as the FP32 value the pair kernel sees), slot 3 dL/dm_i = -sum(4); with
 // accumulate set both are added to what the arrays hold.

@@ -159,142 +159,10 @@ __device__ __forceinline__ void tile_pass(const float4 *tl, const typename Op::I
     }
 }
 
-// One block's work: the i-tile [i0, i0 + ni) (ni <= 256 * IPL) against the j-range
-// [j0, j0 + nj), partial sums written to planes out[word * plane + col0 + lane-slot].
-// `tile` is the block's LDS staging area; every lane of the block must call this
-// with the same arguments (it contains barriers).
-template <class Op, int IPL, int JT, int MODE, bool FULL>
-__device__ __forceinline__ void block_work(const typename Op::Args &a, float4 (*tile)[JT * (Op::kJWords / 4)],
-                                           int i0, int ni, int j0, int nj, float eps2, void *out,
-                                           size_t plane, size_t col0) {
-    constexpr int W = Op::kJWords;
-    constexpr int NO = Op::kOut;
-    constexpr int LPT = (JT + kTPB - 1) / kTPB;  // j-records staged per lane
-    static_assert(W % 4 == 0, "j-records are whole float4s");
-    const int tid = threadIdx.x;
-    const typename Op::Ctx ctx = Op::make_ctx(a, i0);
-
-    typename Op::IState is[IPL];
-#pragma unroll
-    for (int k = 0; k < IPL; ++k) {
-        const int r = k * kTPB + tid;
-        is[k] = Op::load_i(a, ctx, i0 + (r < ni ? r : ni - 1));
-    }
-
-    float hs[IPL][NO], ls[IPL][NO];
-    double ds[IPL][NO];
-#pragma unroll
-    for (int k = 0; k < IPL; ++k)
-#pragma unroll
-        for (int c = 0; c < NO; ++c) {
-            hs[k][c] = 0.0f;
-            ls[k][c] = 0.0f;
-            ds[k][c] = 0.0;
-        }
-
-    const int j1 = j0 + nj;
-    const int ntiles = nj > 0 ? (nj + JT - 1) / JT : 0;
-
-    float stage[LPT][W];
-    auto fetch = [&](int t) {
-#pragma unroll
-        for (int q = 0; q < LPT; ++q) {
-            const int jj = q * kTPB + tid;
-            const int j = j0 + t * JT + jj;
-            if (jj < JT) {
-                if (j < j1)
-                    Op::load_j(a, ctx, 0, (unsigned)j, stage[q]);
-                else
-                    Op::pad_j(stage[q]);
-            }
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < LPT; ++q) {
-            const int jj = q * kTPB + tid;
-            if (jj < JT)
-#pragma unroll
-                for (int v = 0; v < W / 4; ++v)
-                    tile[buf][jj * (W / 4) + v] =
-                        make_float4(stage[q][4 * v], stage[q][4 * v + 1], stage[q][4 * v + 2],
-                                    stage[q][4 * v + 3]);
-        }
-    };
-
-    // Global index of the lane's k-th own particle (padding lanes of the last i-tile
-    // get indices >= n, whose j-slots hold padding records or nothing).
-    int own[IPL];
-#pragma unroll
-    for (int k = 0; k < IPL; ++k) own[k] = i0 + k * kTPB + tid;
-
-    if (ntiles > 0) {
-        fetch(0);
-        store(0);
-    }
-    __syncthreads();
-    __builtin_amdgcn_s_waitcnt(kWaitVmem);
-    for (int t = 0; t < ntiles; ++t) {
-        const int buf = t & 1;
-        if (t + 1 < ntiles) fetch(t + 1);
-        const int jt0 = j0 + t * JT;
-        int self[IPL];
-#pragma unroll
-        for (int k = 0; k < IPL; ++k) self[k] = own[k] - jt0;
-        if constexpr (Op::kSelf) {
-            // Uniform over the block: does this tile hold any of the block's own i's?
-            if (jt0 < i0 + kTPB * IPL && i0 < jt0 + JT)
-                tile_pass<Op, IPL, JT, MODE, FULL, true>(tile[buf], is, eps2, hs, ls, ds, self);
-            else
-                tile_pass<Op, IPL, JT, MODE, FULL, false>(tile[buf], is, eps2, hs, ls, ds, self);
-        } else {
-            tile_pass<Op, IPL, JT, MODE, FULL, false>(tile[buf], is, eps2, hs, ls, ds, self);
-        }
-        if (t + 1 < ntiles) store(buf ^ 1);
-        __syncthreads();
-    }
-
-#pragma unroll
-    for (int k = 0; k < IPL; ++k) {
-        const size_t i = col0 + k * kTPB + tid;
-        if constexpr (MODE == NBODY_FP64RED) {
-            double *p = static_cast<double *>(out) + i;
-#pragma unroll
-            for (int c = 0; c < NO; ++c) p[c * plane] = ds[k][c];
-        } else if constexpr (MODE == NBODY_COMP) {
-            float *p = static_cast<float *>(out) + i;
-#pragma unroll
-            for (int c = 0; c < NO; ++c) {
-                p[c * plane] = hs[k][c];
-                p[(NO + c) * plane] = ls[k][c];
-            }
-        } else {
-            float *p = static_cast<float *>(out) + i;
-#pragma unroll
-            for (int c = 0; c < NO; ++c) p[c * plane] = hs[k][c];
-        }
-    }
-}
-
 // Words (4 bytes) of partial sums per output, i-particle and segment.
 template <int MODE>
 constexpr int words_per_out() {
     return MODE == NBODY_PLAIN ? 1 : 2;
-}
-
-// Grid launch: blockIdx.x = i-tile, blockIdx.y = j-segment of a.seg_len j's.  Partial
-// planes [seg][word][npad].
-template <class Op, int IPL, int JT, int MODE, bool FULL>
-__global__ __launch_bounds__(kTPB) void tile_kernel(typename Op::Args a) {
-    __shared__ float4 tile[2][JT * (Op::kJWords / 4)];
-    const int i0 = blockIdx.x * (kTPB * IPL);
-    const int ni = min(kTPB * IPL, Op::n_i(a) - i0);
-    const int j0 = blockIdx.y * a.seg_len;
-    const int nj = max(0, min(a.seg_len, Op::n_j(a) - j0));
-    const size_t plane = (size_t)a.npad;
-    constexpr int WO = Op::kOut * words_per_out<MODE>();
-    void *out = static_cast<float *>(a.part) + (size_t)blockIdx.y * WO * plane;
-    block_work<Op, IPL, JT, MODE, FULL>(a, tile, i0, ni, j0, nj, a.eps2, out, plane, (size_t)i0);
 }
 
 // Fixed-order sums of the segment partials.  Segment s holds, per output c, the words
@@ -389,47 +257,6 @@ __device__ __forceinline__ void sum_partials(const void *part, int nseg, size_t 
         }
 #pragma unroll
     for (int c = 0; c < NO; ++c) r[c] = (double)acc[c];
-}
-
-// Launch-shape dispatch over the template parameters.
-template <class Op>
-using TileFn = void (*)(typename Op::Args);
-
-template <class Op, int IPL, int JT, int MODE>
-TileFn<Op> pick_full(bool full) {
-    return full ? tile_kernel<Op, IPL, JT, MODE, true> : tile_kernel<Op, IPL, JT, MODE, false>;
-}
-
-template <class Op, int IPL, int JT>
-TileFn<Op> pick_mode(int mode, bool full) {
-    switch (mode) {
-        case NBODY_PLAIN: return pick_full<Op, IPL, JT, NBODY_PLAIN>(full);
-        case NBODY_FP64RED: return pick_full<Op, IPL, JT, NBODY_FP64RED>(full);
-        case NBODY_COMP: return pick_full<Op, IPL, JT, NBODY_COMP>(full);
-    }
-    return nullptr;
-}
-
-template <class Op, int IPL>
-TileFn<Op> pick_jt(int jt, int mode, bool full) {
-    switch (jt) {
-        case 64: return pick_mode<Op, IPL, 64>(mode, full);
-        case 128: return pick_mode<Op, IPL, 128>(mode, full);
-        case 256: return pick_mode<Op, IPL, 256>(mode, full);
-        case 512: return pick_mode<Op, IPL, 512>(mode, full);
-    }
-    return nullptr;
-}
-
-template <class Op>
-TileFn<Op> pick_tile(int ipl, int jt, int mode, bool full) {
-    switch (ipl) {
-        case 1: return pick_jt<Op, 1>(jt, mode, full);
-        case 2: return pick_jt<Op, 2>(jt, mode, full);
-        case 4: return pick_jt<Op, 4>(jt, mode, full);
-        case 8: return pick_jt<Op, 8>(jt, mode, full);
-    }
-    return nullptr;
 }
 
 }  // namespace engine

@@ -2,6 +2,7 @@
 // partial sums.
 #include "adjoint_pipeline.h"
 #include "outputs.h"
+#include "wave_engine.h"
 
 namespace nbody {
 namespace {
@@ -24,15 +25,9 @@ __global__ __launch_bounds__(256) void vjp_finalize_kernel(VjpFinalizeArgs a) {
 }  // namespace
 
 nbody_status launch_vjp(const TileCfg &cfg, int precision, const VjpArgs &a, bool with_mass,
-                        hipStream_t s) {
-    auto fn = engine::pick_tile<Adjoint>(cfg.ipl, cfg.jt, precision, with_mass);
-    if (!fn) return set_error(NBODY_EUNSUPPORTED, "no VJP kernel for this ipl/jtile/precision");
-    if (cfg.itiles <= 0 || cfg.nseg <= 0) return NBODY_OK;
-    hipLaunchKernelGGL(fn, dim3(cfg.itiles, cfg.nseg), dim3(kTPB), 0, s, a);
-    NBODY_HIP_CHECK(hipGetLastError());
-    return NBODY_OK;
+                        const VjpFinalizeArgs &f, hipStream_t s) {
+    return wave::launch<Adjoint, VjpOut>(cfg, precision, with_mass, a.n, a, f, s);
 }
-
 
 template <int MODE>
 void launch_vjp_finalize_mode(dim3 grid, bool deep, const VjpFinalizeArgs &a, hipStream_t s) {

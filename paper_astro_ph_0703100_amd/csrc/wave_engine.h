@@ -76,9 +76,9 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
                     const bool own = j0 + u == d0 + k * 64 + lane;
 #pragma unroll
                     for (int w = 0; w < W; ++w) z[w] = own ? z[w] : jr[w];
-                    Op::template pair_timed<FULL>(z, is[k], eps2, acc[k]);
+                    Op::template pair_timed<FULL, (IPL > 1)>(z, is[k], eps2, acc[k]);
                 } else {
-                    Op::template pair_timed<FULL>(jr, is[k], eps2, acc[k]);
+                    Op::template pair_timed<FULL, (IPL > 1)>(jr, is[k], eps2, acc[k]);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);

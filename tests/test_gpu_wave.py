@@ -11,7 +11,7 @@ from bounds import check_acc, check_pot
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from paper_astro_ph_0703100_amd import api, ics  # noqa: E402
+from paper_astro_ph_0703100_amd import _lib, api, ics  # noqa: E402
 
 DEV = "cuda"
 EPS = 0.02
@@ -100,3 +100,35 @@ def test_batched_open_shape(precision, sizes):
         ref = oracle.force_all(x64, m64, float(eps[k]))
         ab = magnitudes(x64, m64, float(eps[k]))
         check(acc[:, s], pot[s], ref, ab, precision, n)
+
+
+@pytest.mark.parametrize("n", [1, 64, 129, 1000, 2048, 2049, 5000, 17000])
+def test_jerk_and_adjoint_splits_agree(n):
+    # One launch (few j's) or segments and a finalize, 1 or 2 i's per lane: the FP32 blocks are
+    # the same, so the results differ by the rounding of FP64 sums of them, at most a few
+    # 2^-47 of the sum of magnitudes.
+    x, m = sphere(n, 6)
+    rng = np.random.default_rng(n)
+    p, mm = torch.from_numpy(x).to(DEV), torch.from_numpy(m).to(DEV)
+    v = torch.from_numpy(rng.standard_normal((3, n)).astype(np.float32)).to(DEV)
+    ref = api.force_jerk(p, v, mm, EPS)
+    k = max(1, n // 3)
+    pi, vi = p[:, :k].contiguous(), v[:, :k].contiguous()
+    ref_ij = api.force_jerk_ij(pi, vi, p, v, mm, EPS)
+    p64 = p.double()
+    g = torch.from_numpy(rng.standard_normal((3, n))).to(DEV)
+    gp = torch.from_numpy(rng.standard_normal(n)).to(DEV)
+
+    def vjp(**kw):
+        gx, gm = torch.empty_like(g), torch.empty_like(gp)
+        _lib.nbody_force_vjp_f64(n, p64.data_ptr(), mm.data_ptr(), EPS, g.data_ptr(), gp.data_ptr(),
+                                 gx.data_ptr(), gm.data_ptr(), api.make_opts(**kw), api.stream_ptr())
+        return gx, gm
+
+    ref_vjp = vjp()
+    for ipl, nseg in ((1, 1), (2, 3), (4, 16)):
+        kw = {"ipl": ipl, "jtile": 128, "nseg": nseg}
+        for a, b in zip(ref + ref_ij + ref_vjp,
+                        api.force_jerk(p, v, mm, EPS, **kw)
+                        + api.force_jerk_ij(pi, vi, p, v, mm, EPS, **kw) + vjp(**kw)):
+            assert float((a - b).abs().max()) <= 1e-11 * max(float(a.abs().max()), 1e-300)
