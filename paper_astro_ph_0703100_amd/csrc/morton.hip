@@ -2,22 +2,60 @@
 // therefore the i-tiles of the pair kernels - are spatially compact.  That is what
 // makes per-i-tile reference centres (NBODY_CENTRE_TILE) pay off.
 //
-// Steps: FP64 bounding box (two-stage min/max), a 64-bit word per particle holding
-// the interleaved quantised coordinates in its high bits and the particle index in its
-// low bits, a bitonic sort of the words (padded to a power of two with ~0), and the
-// index bits of the sorted words as the permutation.  Ties in the key are broken by
-// index, so the order is unique.
+// Every particle gets a 64-bit word: the interleaved quantised coordinates in its high
+// bits and its index in the low bits; the index bits of the sorted words are the
+// permutation.  Ties in the key are broken by index, so the order is unique.
+//
+//   * up to kSmall particles: one block does it all in LDS (bounding box, words, bitonic
+//     network), one launch;
+//   * above: a stable radix sort of the key bits alone, from the least significant digit
+//     (the words start in index order, so ties stay in it).  Each pass is three launches:
+//     digit counts of every tile, prefix sums of the counts over the tiles (one block per
+//     digit), and the scatter, which ranks a tile's words by digit with wave ballots,
+//     puts them in that order in LDS and writes each digit's run contiguously.
+//
+// Bound: 16 bytes read and written per word and pass, 6 passes of 7 bits at 2^20
+// particles, but at that size the launches cost more than the traffic.  2^20 particles:
+// see the design notes for the times; the bitonic network in global memory this replaced
+// took 210 launches.
+#include <utility>
+
 #include "nbody_internal.h"
 
 namespace nbody {
 namespace {
 
 constexpr int kBoxBlocks = 256;
+constexpr int kSmall = 8192;       // words one block sorts in LDS (64 KB)
+constexpr int kSmallThreads = 1024;
+constexpr int kTile = 4096;        // words per block of the radix passes
+constexpr int kTileThreads = 512;  // 8 waves, 8 rows of 64 words each
+constexpr int kRows = kTile / kTileThreads;
+constexpr int kWaves = kTileThreads / 64;
+constexpr int kMaxDigits = 256;
 
-__global__ __launch_bounds__(256) void box_partial_kernel(int64_t n, const double *pos, double *part) {
-    __shared__ double lo[3][256], hi[3][256];
+// Lowest and highest coordinates in lo/hi [3][threads] reduced to slot 0 of each.
+template <int THREADS>
+__device__ __forceinline__ void reduce_box(double (*lo)[THREADS], double (*hi)[THREADS]) {
+    __syncthreads();
+    for (int w = THREADS / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                lo[c][threadIdx.x] = fmin(lo[c][threadIdx.x], lo[c][threadIdx.x + w]);
+                hi[c][threadIdx.x] = fmax(hi[c][threadIdx.x], hi[c][threadIdx.x + w]);
+            }
+        __syncthreads();
+    }
+}
+
+// This thread's box of the particles first, first + stride, ...
+template <int THREADS>
+__device__ __forceinline__ void thread_box(int64_t n, const double *pos, int64_t first,
+                                           int64_t stride, double (*lo)[THREADS],
+                                           double (*hi)[THREADS]) {
     double l[3] = {INFINITY, INFINITY, INFINITY}, h[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    for (int64_t i = first; i < n; i += stride)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             const double v = pos[c * n + i];
@@ -29,131 +67,354 @@ __global__ __launch_bounds__(256) void box_partial_kernel(int64_t n, const doubl
         lo[c][threadIdx.x] = l[c];
         hi[c][threadIdx.x] = h[c];
     }
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                lo[c][threadIdx.x] = fmin(lo[c][threadIdx.x], lo[c][threadIdx.x + w]);
-                hi[c][threadIdx.x] = fmax(hi[c][threadIdx.x], hi[c][threadIdx.x + w]);
-            }
-        __syncthreads();
-    }
+}
+
+__global__ __launch_bounds__(256) void box_partial_kernel(int64_t n, const double *pos, double *part) {
+    __shared__ double lo[3][256], hi[3][256];
+    thread_box<256>(n, pos, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256, lo, hi);
+    reduce_box<256>(lo, hi);
     if (threadIdx.x < 3) {
         part[6 * blockIdx.x + threadIdx.x] = lo[threadIdx.x][0];
         part[6 * blockIdx.x + 3 + threadIdx.x] = hi[threadIdx.x][0];
     }
 }
 
-__global__ __launch_bounds__(256) void box_final_kernel(const double *part, double *box) {
-    __shared__ double lo[3][kBoxBlocks], hi[3][kBoxBlocks];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        lo[c][threadIdx.x] = part[6 * threadIdx.x + c];
-        hi[c][threadIdx.x] = part[6 * threadIdx.x + 3 + c];
-    }
-    __syncthreads();
-    for (int w = kBoxBlocks / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                lo[c][threadIdx.x] = fmin(lo[c][threadIdx.x], lo[c][threadIdx.x + w]);
-                hi[c][threadIdx.x] = fmax(hi[c][threadIdx.x], hi[c][threadIdx.x + w]);
-            }
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) {
-        box[threadIdx.x] = lo[threadIdx.x][0];
-        box[3 + threadIdx.x] = hi[threadIdx.x][0];
-    }
+// Moves bit b of the low 21 bits of v to bit 3b, by doubling the gaps between groups of
+// bits (v has at most 21 significant bits; higher ones are dropped).
+__device__ __forceinline__ uint64_t spread3(uint64_t v) {
+    v &= 0x1fffffull;
+    v = (v | (v << 32)) & 0x001f00000000ffffull;
+    v = (v | (v << 16)) & 0x001f0000ff0000ffull;
+    v = (v | (v << 8)) & 0x100f00f00f00f00full;
+    v = (v | (v << 4)) & 0x10c30c30c30c30c3ull;
+    v = (v | (v << 2)) & 0x1249249249249249ull;
+    return v;
 }
 
-// Spreads the low `bits` bits of v so that bit b moves to bit 3b.
-__device__ __forceinline__ uint64_t spread3(uint64_t v, int bits) {
-    uint64_t r = 0;
-    for (int b = 0; b < bits; ++b) r |= ((v >> b) & 1ull) << (3 * b);
-    return r;
-}
-
-__global__ __launch_bounds__(256) void key_kernel(int64_t n, int64_t npow, const double *pos,
-                                                 const double *box, int qbits, int ibits,
-                                                 uint64_t *words) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= npow) return;
-    if (i >= n) {
-        words[i] = ~0ull;
-        return;
-    }
-    const double top = (double)((1ull << qbits) - 1);
+// Word of particle i: coordinates quantised to qbits in the box, interleaved, then the
+// index in ibits.
+__device__ __forceinline__ uint64_t particle_word(int64_t n, int64_t i, const double *pos,
+                                                  const double (&lo)[3], const double (&hi)[3],
+                                                  int qbits, int ibits) {
+    const uint64_t low = (1ull << qbits) - 1;
+    const double top = (double)low;
     uint64_t key = 0;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const double span = box[3 + c] - box[c];
-        double q = span > 0.0 ? (pos[c * n + i] - box[c]) / span * top : 0.0;
+        const double span = hi[c] - lo[c];
+        double q = span > 0.0 ? (pos[c * n + i] - lo[c]) / span * top : 0.0;
         q = q < 0.0 ? 0.0 : (q > top ? top : q);
-        key |= spread3((uint64_t)q, qbits) << (2 - c);
+        key |= spread3((uint64_t)q & low) << (2 - c);
     }
-    words[i] = (key << ibits) | (uint64_t)i;
+    return (key << ibits) | (uint64_t)i;
 }
 
-// One compare-exchange stage of the bitonic network (block k, distance j).
-__global__ __launch_bounds__(256) void bitonic_kernel(uint64_t *a, int64_t half, int64_t j, int64_t k) {
-    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (t >= half) return;
-    const int64_t i = 2 * j * (t / j) + (t % j);
-    const int64_t l = i + j;
-    const bool up = (i & k) == 0;
-    const uint64_t x = a[i], y = a[l];
-    if ((x > y) == up) {
-        a[i] = y;
-        a[l] = x;
+// Up to kSmall particles in one block: npow (a power of two >= n) words in LDS.
+__global__ __launch_bounds__(kSmallThreads) void small_kernel(int n, int npow, const double *pos,
+                                                             int qbits, int ibits, int32_t *perm) {
+    extern __shared__ uint64_t words[];
+    // The box reduction comes first, in the same memory.
+    double(*lo)[kSmallThreads] = reinterpret_cast<double(*)[kSmallThreads]>(words);
+    double(*hi)[kSmallThreads] = lo + 3;
+    const int t = threadIdx.x;
+    thread_box<kSmallThreads>(n, pos, t, kSmallThreads, lo, hi);
+    reduce_box<kSmallThreads>(lo, hi);
+    double l[3], h[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        l[c] = lo[c][0];
+        h[c] = hi[c][0];
+    }
+    __syncthreads();
+    for (int i = t; i < npow; i += kSmallThreads)
+        words[i] = i < n ? particle_word(n, i, pos, l, h, qbits, ibits) : ~0ull;
+    __syncthreads();
+    for (int k = 2; k <= npow; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int p = t; p < npow / 2; p += kSmallThreads) {
+                const int i = 2 * p - (p & (j - 1));  // p with a zero inserted at bit log2 j
+                const uint64_t x = words[i], y = words[i + j];
+                if ((x > y) == ((i & k) == 0)) {
+                    words[i] = y;
+                    words[i + j] = x;
+                }
+            }
+            __syncthreads();
+        }
+    const uint64_t mask = (1ull << ibits) - 1;
+    for (int i = t; i < n; i += kSmallThreads) perm[i] = (int32_t)(words[i] & mask);
+}
+
+// Lanes of the wave that hold a word (valid) with this lane's digit.
+__device__ __forceinline__ unsigned long long peers(unsigned d, int bits, bool valid) {
+    unsigned long long m = __ballot(valid);
+    for (int b = 0; b < bits; ++b) {
+        const bool one = (d >> b) & 1u;
+        const unsigned long long v = __ballot(one);
+        m &= one ? v : ~v;
+    }
+    return m;
+}
+
+// The tile's digit counts into counts[digit][tile].
+__device__ __forceinline__ void tile_counts(const uint64_t (&w)[kRows], const bool (&valid)[kRows],
+                                            int shift, int bits, unsigned *sh, unsigned *counts,
+                                            int tiles) {
+    const unsigned digits = 1u << bits;
+    for (unsigned d = threadIdx.x; d < digits; d += kTileThreads) sh[d] = 0;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const unsigned d = (unsigned)(w[r] >> shift) & (digits - 1);
+        const unsigned long long m = peers(d, bits, valid[r]);
+        if (valid[r] && lane == __ffsll((long long)m) - 1) atomicAdd(&sh[d], (unsigned)__popcll(m));
+    }
+    __syncthreads();
+    for (unsigned d = threadIdx.x; d < digits; d += kTileThreads)
+        counts[(size_t)d * tiles + blockIdx.x] = sh[d];
+}
+
+// Index of row r's word of this lane: a wave holds kRows consecutive rows of 64.
+__device__ __forceinline__ int64_t word_index(int r) {
+    return (int64_t)blockIdx.x * kTile + (threadIdx.x >> 6) * (kRows * 64) + r * 64 + (threadIdx.x & 63);
+}
+
+// Final reduction of the box (by every block, in the same order), the words of the block's
+// tile, and the first digit's counts.
+__global__ __launch_bounds__(kTileThreads) void word_kernel(int64_t n, const double *pos,
+                                                           const double *part, int qbits, int ibits,
+                                                           int bits, uint64_t *words,
+                                                           unsigned *counts, int tiles) {
+    __shared__ double lo[3][kTileThreads], hi[3][kTileThreads];
+    __shared__ unsigned sh[kMaxDigits];
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        lo[c][t] = t < kBoxBlocks ? part[6 * t + c] : INFINITY;
+        hi[c][t] = t < kBoxBlocks ? part[6 * t + 3 + c] : -INFINITY;
+    }
+    reduce_box<kTileThreads>(lo, hi);
+    double l[3], h[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        l[c] = lo[c][0];
+        h[c] = hi[c][0];
+    }
+    uint64_t w[kRows];
+    bool valid[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t i = word_index(r);
+        valid[r] = i < n;
+        w[r] = 0;
+        if (valid[r]) {
+            w[r] = particle_word(n, i, pos, l, h, qbits, ibits);
+            words[i] = w[r];
+        }
+    }
+    tile_counts(w, valid, ibits, bits, sh, counts, tiles);
+}
+
+__global__ __launch_bounds__(kTileThreads) void count_kernel(int64_t n, const uint64_t *words,
+                                                            int shift, int bits, unsigned *counts,
+                                                            int tiles) {
+    __shared__ unsigned sh[kMaxDigits];
+    uint64_t w[kRows];
+    bool valid[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t i = word_index(r);
+        valid[r] = i < n;
+        w[r] = valid[r] ? words[i] : 0;
+    }
+    tile_counts(w, valid, shift, bits, sh, counts, tiles);
+}
+
+// Exclusive prefix sum of v over the block's threads (256); total in `sum`.
+__device__ __forceinline__ unsigned block_prefix(unsigned v, unsigned *sh, unsigned *sum) {
+    const int t = threadIdx.x;
+    sh[t] = v;
+    __syncthreads();
+    for (int d = 1; d < 256; d <<= 1) {
+        const unsigned o = t >= d ? sh[t - d] : 0;
+        __syncthreads();
+        sh[t] += o;
+        __syncthreads();
+    }
+    const unsigned incl = sh[t];
+    *sum = sh[255];
+    __syncthreads();
+    return incl - v;
+}
+
+// Block d: counts[d][0 .. tiles) to exclusive prefix sums, and the digit's total.
+__global__ __launch_bounds__(256) void scan_kernel(unsigned *counts, unsigned *totals, int tiles) {
+    __shared__ unsigned sh[256];
+    unsigned *row = counts + (size_t)blockIdx.x * tiles;
+    unsigned run = 0;
+    for (int b = 0; b < tiles; b += 256) {
+        const int q = b + threadIdx.x;
+        const unsigned v = q < tiles ? row[q] : 0;
+        unsigned sum;
+        const unsigned pre = block_prefix(v, sh, &sum);
+        if (q < tiles) row[q] = run + pre;
+        run += sum;
+    }
+    if (threadIdx.x == 0) totals[blockIdx.x] = run;
+}
+
+// Stable scatter of the tile by the digit; the last pass writes the permutation instead.
+template <bool LAST>
+__global__ __launch_bounds__(kTileThreads) void scatter_kernel(int64_t n, const uint64_t *in,
+                                                              int shift, int bits,
+                                                              const unsigned *counts,
+                                                              const unsigned *totals, int tiles,
+                                                              uint64_t *out, int32_t *perm,
+                                                              uint64_t mask) {
+    __shared__ uint64_t sorted[kTile];
+    __shared__ unsigned hist[kWaves][kMaxDigits];  // per wave, then the wave's first local slot
+    __shared__ unsigned scan[2][kMaxDigits];
+    __shared__ unsigned dest[kMaxDigits];          // output slot - local slot of each digit's
+                                                   // words (modulo 2^32)
+    const unsigned digits = 1u << bits;
+    const int t = threadIdx.x;
+    const int lane = t & 63;
+    const int wave = t >> 6;
+    for (int v = 0; v < kWaves; ++v)
+        for (int q = t; q < kMaxDigits; q += kTileThreads) hist[v][q] = 0;
+
+    uint64_t w[kRows];
+    bool valid[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t i = word_index(r);
+        valid[r] = i < n;
+        w[r] = valid[r] ? in[i] : 0;
+    }
+    __syncthreads();
+    // Rank of each word among the wave's words of the same digit, row by row.
+    unsigned dg[kRows], rank[kRows];
+    volatile unsigned *mine = hist[wave];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        dg[r] = (unsigned)(w[r] >> shift) & (digits - 1);
+        const unsigned long long m = peers(dg[r], bits, valid[r]);
+        const unsigned before = mine[dg[r]];
+        rank[r] = before + (unsigned)__popcll(m & ((1ull << lane) - 1));
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (valid[r] && lane == __ffsll((long long)m) - 1) mine[dg[r]] = before + (unsigned)__popcll(m);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    }
+    __syncthreads();
+    // Digit t: its count in the tile, and exclusive prefix sums over the digits of the
+    // tile's counts (local slots) and of the totals (output slots).
+    unsigned own = 0, total = 0;
+    if (t < (int)digits) {
+        for (int v = 0; v < kWaves; ++v) own += hist[v][t];
+        total = totals[t];
+    }
+    if (t < kMaxDigits) {
+        scan[0][t] = own;
+        scan[1][t] = total;
+    }
+    __syncthreads();
+    for (int d = 1; d < kMaxDigits; d <<= 1) {
+        unsigned a = 0, b = 0;
+        if (t < kMaxDigits && t >= d) {
+            a = scan[0][t - d];
+            b = scan[1][t - d];
+        }
+        __syncthreads();
+        if (t < kMaxDigits) {
+            scan[0][t] += a;
+            scan[1][t] += b;
+        }
+        __syncthreads();
+    }
+    if (t < (int)digits) {
+        unsigned slot = scan[0][t] - own;
+        dest[t] = scan[1][t] - total + counts[(size_t)t * tiles + blockIdx.x] - slot;
+        for (int v = 0; v < kWaves; ++v) {
+            const unsigned c = hist[v][t];
+            hist[v][t] = slot;
+            slot += c;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+        if (valid[r]) sorted[hist[wave][dg[r]] + rank[r]] = w[r];
+    __syncthreads();
+    const int64_t left = n - (int64_t)blockIdx.x * kTile;
+    const int cnt = left < kTile ? (int)left : kTile;
+    for (int q = t; q < cnt; q += kTileThreads) {
+        const uint64_t v = sorted[q];
+        const unsigned o = dest[(unsigned)(v >> shift) & (digits - 1)] + (unsigned)q;
+        if constexpr (LAST)
+            perm[o] = (int32_t)(v & mask);
+        else
+            out[o] = v;
     }
 }
 
-__global__ __launch_bounds__(256) void perm_kernel(int64_t n, const uint64_t *words, uint64_t mask,
-                                                  int32_t *perm) {
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= n) return;
-    perm[r] = (int32_t)(words[r] & mask);
-}
-
-int64_t pow2_at_least(int64_t n) {
-    int64_t p = 1;
-    while (p < n) p <<= 1;
-    return p;
-}
+int tiles_of(int64_t n) { return (int)((n + kTile - 1) / kTile); }
 
 }  // namespace
 
 size_t morton_scratch_bytes(int64_t n) {
-    return sizeof(uint64_t) * (size_t)pow2_at_least(n > 1 ? n : 1) +
-           sizeof(double) * (6 * kBoxBlocks + 8);
+    if (n <= kSmall) return 256;
+    return 2 * sizeof(uint64_t) * (size_t)n + sizeof(double) * 6 * kBoxBlocks +
+           sizeof(unsigned) * kMaxDigits * ((size_t)tiles_of(n) + 1);
 }
 
 nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, void *scratch,
                                  hipStream_t s) {
     if (n <= 0) return NBODY_OK;
-    const int64_t npow = pow2_at_least(n);
-    uint64_t *words = static_cast<uint64_t *>(scratch);
-    double *part = reinterpret_cast<double *>(words + npow);
-    double *box = part + 6 * kBoxBlocks;
     int ibits = 0;
     while ((int64_t(1) << ibits) < n) ++ibits;
     const int qbits = (64 - ibits) / 3;
+    if (n <= kSmall) {
+        int npow = 1;
+        while (npow < n) npow <<= 1;
+        // At least the box reduction's six doubles per thread.
+        size_t lds = sizeof(uint64_t) * (size_t)npow;
+        if (lds < sizeof(double) * 6 * kSmallThreads) lds = sizeof(double) * 6 * kSmallThreads;
+        hipLaunchKernelGGL(small_kernel, dim3(1), dim3(kSmallThreads), lds, s, (int)n, npow, pos64,
+                           qbits, ibits, perm);
+        NBODY_HIP_CHECK(hipGetLastError());
+        return NBODY_OK;
+    }
+    uint64_t *words = static_cast<uint64_t *>(scratch);
+    uint64_t *other = words + n;
+    double *part = reinterpret_cast<double *>(other + n);
+    unsigned *totals = reinterpret_cast<unsigned *>(part + 6 * kBoxBlocks);
+    unsigned *counts = totals + kMaxDigits;
+    const int tiles = tiles_of(n);
+    const int key_bits = 3 * qbits;
+    const int passes = (key_bits + 7) / 8;
+    const int bits = (key_bits + passes - 1) / passes;  // digits of 6 to 8 bits
+    const uint64_t mask = (1ull << ibits) - 1;
+    const dim3 grid((unsigned)tiles), block(kTileThreads);
     hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(256), 0, s, n, pos64, part);
-    hipLaunchKernelGGL(box_final_kernel, dim3(1), dim3(kBoxBlocks), 0, s, (const double *)part, box);
-    hipLaunchKernelGGL(key_kernel, dim3((unsigned)((npow + 255) / 256)), dim3(256), 0, s, n, npow,
-                       pos64, (const double *)box, qbits, ibits, words);
-    NBODY_HIP_CHECK(hipGetLastError());
-    const int64_t half = npow / 2;
-    const dim3 grid((unsigned)((half + 255) / 256 > 0 ? (half + 255) / 256 : 1));
-    for (int64_t k = 2; k <= npow; k <<= 1)
-        for (int64_t j = k >> 1; j > 0; j >>= 1)
-            hipLaunchKernelGGL(bitonic_kernel, grid, dim3(256), 0, s, words, half, j, k);
-    NBODY_HIP_CHECK(hipGetLastError());
-    const uint64_t mask = ibits >= 64 ? ~0ull : ((1ull << ibits) - 1);
-    hipLaunchKernelGGL(perm_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n,
-                       (const uint64_t *)words, mask, perm);
+    hipLaunchKernelGGL(word_kernel, grid, block, 0, s, n, pos64, (const double *)part, qbits, ibits,
+                       bits, words, counts, tiles);
+    for (int p = 0; p < passes; ++p) {
+        const int shift = ibits + p * bits;
+        if (p)
+            hipLaunchKernelGGL(count_kernel, grid, block, 0, s, n, (const uint64_t *)words, shift,
+                               bits, counts, tiles);
+        hipLaunchKernelGGL(scan_kernel, dim3(1u << bits), dim3(256), 0, s, counts, totals, tiles);
+        if (p + 1 == passes)
+            hipLaunchKernelGGL(scatter_kernel<true>, grid, block, 0, s, n, (const uint64_t *)words,
+                               shift, bits, (const unsigned *)counts, (const unsigned *)totals,
+                               tiles, other, perm, mask);
+        else
+            hipLaunchKernelGGL(scatter_kernel<false>, grid, block, 0, s, n, (const uint64_t *)words,
+                               shift, bits, (const unsigned *)counts, (const unsigned *)totals,
+                               tiles, other, perm, mask);
+        std::swap(words, other);
+    }
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }

@@ -125,3 +125,28 @@ def test_leapfrog_with_tile_centres_matches_oracle():
     assert np.abs(x.cpu().numpy().T - xo).max() < 1e-9
     assert np.abs(v.cpu().numpy().T - vo).max() < 1e-7
     assert rel_errors(acc.cpu().numpy().T, ao)["rel_rms"] < 1e-6
+
+
+@pytest.mark.parametrize("n", [2, 3, 64, 1025, 4097, 8191, 8192, 8193, 12288, 16385, 70000])
+@pytest.mark.parametrize("kind", ["sphere", "ties", "line"])
+def test_morton_order_of_every_sort_path(n, kind):
+    # One block in LDS up to 8192 particles, the radix passes above; many equal keys, and a
+    # degenerate box (two coordinates constant).
+    pos, _, _ = ics.plummer(n, seed=91, velocities=False)
+    if kind == "ties":
+        pos = np.round(pos)
+    if kind == "line":
+        pos = pos * np.array([1.0, 0.0, 0.0]) + np.array([0.0, 2.0, -3.0])
+    x = torch.from_numpy(np.ascontiguousarray(pos.T)).to(DEV)
+    perm = api.morton_order(x).cpu().numpy()
+    ib = max(1, int(np.ceil(np.log2(n))))
+    qb = (64 - ib) // 3
+    lo, span = pos.min(0), np.ptp(pos, axis=0)
+    top = float((1 << qb) - 1)
+    q = np.where(span > 0, (pos - lo) / np.where(span > 0, span, 1.0) * top, 0.0)
+    q = np.clip(q, 0, top).astype(np.uint64)
+    key = np.zeros(n, dtype=np.uint64)
+    for b in range(qb):
+        for c in range(3):
+            key |= ((q[:, c] >> np.uint64(b)) & np.uint64(1)) << np.uint64(3 * b + 2 - c)
+    np.testing.assert_array_equal(perm, np.argsort(key, kind="stable"))
