@@ -24,11 +24,21 @@ size_t vjp_f64_bytes(int64_t n, const TileCfg &cfg, int precision) {
     return f64_scratch_bytes(n, cfg, precision, kVjpOutputs);
 }
 
+// The drift-kick update that follows an adjoint evaluation when another one comes, for the
+// finalize launch (see VjpFinalizeArgs).
+struct ReverseStep {
+    double *vbar, *abar;
+    double dt, h;
+    const double *next;  // checkpoint of the following evaluation
+    double *centre_part;
+};
+
 // Adjoint pair kernel + FP64 finalize on FP32 positions.
 nbody_status vjp_f32_core(int64_t n, const float *pos, const float *mass, float eps,
                           const double *g_acc, const double *g_pot, double *grad_pos,
                           double *grad_mass, bool accumulate, const nbody_opts &o,
-                          const TileCfg &cfg, void *part, hipStream_t s) {
+                          const TileCfg &cfg, void *part, hipStream_t s,
+                          const ReverseStep *step = nullptr) {
     const float e2 = eps * eps;
     VjpArgs va{pos,   pos + n, pos + 2 * n, mass, g_acc, g_acc + n, g_acc + 2 * n,
                g_pot, (int)n,  cfg.wseg_len, e2,  part,  cfg.npad};
@@ -37,7 +47,12 @@ nbody_status vjp_f32_core(int64_t n, const float *pos, const float *mass, float 
     if (cfg.jl > 1) return launch_vjp_split(cfg, o.precision, va, grad_mass != nullptr, fa, s);
     nbody_status st = launch_vjp(cfg, o.precision, va, grad_mass != nullptr, fa, s);
     if (st || cfg.wseg == 1) return st;
-    return launch_vjp_finalize(o.precision, fa, s);
+    if (!step) return launch_vjp_finalize(o.precision, fa, s);
+    fa.vbar = step->vbar;
+    fa.abar = step->abar;
+    fa.step_dt = step->dt;
+    fa.step_h = step->h;
+    return launch_vjp_finalize_step(o.precision, fa, step->next, step->centre_part, s);
 }
 
 // Centre + FP32 conversion, then the adjoint on the converted positions.
@@ -47,7 +62,7 @@ nbody_status vjp_f64_core(int64_t n, const double *pos64, const float *mass, flo
                           const double *g_acc, const double *g_pot, double *grad_pos,
                           double *grad_mass, bool accumulate, const nbody_opts &o,
                           const TileCfg &cfg, const F64Scratch &ws, hipStream_t s,
-                          bool centre_ready = false) {
+                          bool centre_ready = false, const ReverseStep *step = nullptr) {
     nbody_status st;
     if (o.centre == NBODY_CENTRE_TILE) {
         // Per-i-tile centres in the FP32-position area (unused in this mode).
@@ -71,7 +86,7 @@ nbody_status vjp_f64_core(int64_t n, const double *pos64, const float *mass, flo
         if ((st = launch_convert(n, pos64, nullptr, ws.x32, s))) return st;
     }
     return vjp_f32_core(n, ws.x32, mass, eps, g_acc, g_pot, grad_pos, grad_mass, accumulate, o,
-                        cfg, ws.part, s);
+                        cfg, ws.part, s, step);
 }
 
 }  // namespace
@@ -166,6 +181,21 @@ nbody_status nbody_leapfrog_adjoint(int64_t n, const double *traj, const float *
     // over the checkpoint the next adjoint evaluation reads.
     const bool fused = o.centre == NBODY_CENTRE_SYSTEM;
     bool ready = false;
+    // Where the evaluation has a finalize launch, that one does the update (3 launches per
+    // step instead of 4); a pair launch that stores the outputs cannot, as its other blocks
+    // still read abar.
+    if (fused && !stores_outputs(cfg) && n <= kStepCentre) {
+        for (int32_t t = nsteps; t >= 0; --t) {
+            const ReverseStep step{vbar, abar, dt, t > 1 ? dt : h,
+                                   t > 0 ? traj + (size_t)(t - 1) * n3 : nullptr,
+                                   lay.centre_scratch};
+            if ((st = vjp_f64_core(n, traj + (size_t)t * n3, mass, eps, abar, nullptr, xbar, mbar,
+                                   true, o, cfg, lay, s, ready, t > 0 ? &step : nullptr)))
+                return st;
+            ready = true;
+        }
+        return NBODY_OK;
+    }
     for (int32_t t = nsteps - 1; t >= 0; --t) {
         const double *x1 = traj + (size_t)(t + 1) * n3;
         if ((st = vjp_f64_core(n, x1, mass, eps, abar, nullptr, xbar, mbar, true, o, cfg, lay, s,

@@ -354,22 +354,28 @@ F64Scratch f64_scratch_layout(void *ws, int64_t n, const TileCfg &cfg, int preci
 // Pair kernel + FP64 reduction on FP32 structure-of-arrays positions.
 nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, float eps, double *acc,
                             double *pot, const nbody_opts &o, const TileCfg &cfg, void *ws,
-                            double *kick_v, double kick_h, hipStream_t s) {
+                            double *kick_v, double kick_h, hipStream_t s, const NextDrift *next) {
     const float e2 = eps * eps;
     PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.wseg_len, e2, ws, cfg.npad};
     FinalizeArgs fa{ws, cfg.sym ? cfg.nseg : cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                     acc, pot, kick_v, kick_h};
+    if (next) {
+        fa.drift_x = next->x;
+        fa.drift_dt = next->dt;
+        fa.checkpoint = next->checkpoint;
+    }
     if (cfg.jl > 1) return launch_pair_split(cfg, o.precision, pot != nullptr, pa, fa, s);
     if (cfg.sym) return launch_pair_sym(cfg, o.precision, pot != nullptr, pa, fa, s);
     nbody_status st = launch_pair(cfg, o.precision, pot != nullptr, pa, fa, s);
     if (st || cfg.wseg == 1) return st;
-    return launch_finalize(o.precision, fa, s);
+    return next && next->centre_part ? launch_finalize_step(o.precision, fa, next->centre_part, s)
+                                     : launch_finalize(o.precision, fa, s);
 }
 
 nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, float eps,
                             double *acc, double *pot, const nbody_opts &o, const TileCfg &cfg,
                             const F64Scratch &ws, double *kick_v, double kick_h, hipStream_t s,
-                            bool centre_ready) {
+                            bool centre_ready, const NextDrift *next) {
     nbody_status st;
     if (o.centre == NBODY_CENTRE_TILE) {
         // Per-i-tile centres (3 doubles per tile fit in the FP32-position area, which this
@@ -393,7 +399,7 @@ nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, f
     } else {
         if ((st = launch_convert(n, pos64, nullptr, ws.x32, s))) return st;
     }
-    return force_f32_core(n, ws.x32, mass, eps, acc, pot, o, cfg, ws.part, kick_v, kick_h, s);
+    return force_f32_core(n, ws.x32, mass, eps, acc, pot, o, cfg, ws.part, kick_v, kick_h, s, next);
 }
 
 }  // namespace nbody

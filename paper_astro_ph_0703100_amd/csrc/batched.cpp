@@ -24,6 +24,7 @@ struct nbody_plan {
     int waves = 4;       // waves per work item
     int nitems = 0;
     bool split = false;  // some system has more than one j-segment
+    int64_t largest = 0; // particles of the largest system
     int64_t padded_pairs = 0;
     int64_t pairs = 0;
     // device tables
@@ -44,6 +45,9 @@ namespace nbody {
 namespace {
 
 constexpr int64_t kItemJ = 4096;  // target j's per work item
+// Largest system whose kick, drift, centre and conversion one block does in one launch: 16
+// particles per thread and pass (about 5 us, against 3 launches).
+constexpr int64_t kBlockSystem = 4096;
 
 void free_plan(nbody_plan *p) {
     if (!p) return;
@@ -101,6 +105,12 @@ nbody_status batched_f64_core(const nbody_plan *p, const double *pos64, const fl
                               double kick_h, hipStream_t s) {
     nbody_status st;
     const double *cen = nullptr;
+    if (p->opts.centre == NBODY_CENTRE_SYSTEM && p->largest <= kBlockSystem) {
+        if ((st = launch_system_step(p->nsys, p->offsets, p->total, const_cast<double *>(pos64),
+                                     nullptr, nullptr, 0.0, 0.0, p->x32, s)))
+            return st;
+        return batched_core(p, p->x32, mass, eps, acc, pot, kick_v, kick_h, s);
+    }
     if (p->opts.centre == NBODY_CENTRE_SYSTEM) {
         if ((st = launch_system_centres(p->nsys, p->offsets, p->total, pos64, p->centre, s))) return st;
         cen = p->centre;
@@ -117,6 +127,15 @@ nbody_status enqueue_batched_steps(const nbody_plan *p, double *x, double *v, co
         if ((st = batched_f64_core(p, x, m, eps, acc, nsteps == 0 ? pot : nullptr, nullptr, 0.0, s)))
             return st;
     for (int32_t t = 0; t < nsteps; ++t) {
+        if (p->opts.centre == NBODY_CENTRE_SYSTEM && p->largest <= kBlockSystem) {
+            if ((st = launch_system_step(p->nsys, p->offsets, p->total, x, v, acc, 0.5 * dt, dt,
+                                         p->x32, s)))
+                return st;
+            if ((st = batched_core(p, p->x32, m, eps, acc, t + 1 == nsteps ? pot : nullptr, v,
+                                   0.5 * dt, s)))
+                return st;
+            continue;
+        }
         if ((st = launch_kick_drift(p->total, x, v, acc, 0.5 * dt, dt, s))) return st;
         if ((st = batched_f64_core(p, x, m, eps, acc, t + 1 == nsteps ? pot : nullptr, v, 0.5 * dt, s)))
             return st;
@@ -181,7 +200,8 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
 
     // i-records per lane: asked for, else by the work (pieces of 64 i's x 128 j's), as for
     // one system.
-    int64_t blocks1 = 0, largest = 0;
+    int64_t blocks1 = 0;
+    int64_t &largest = p->largest;
     for (int32_t k = 0; k < nsys; ++k) {
         const int64_t n = h_offsets[k + 1] - h_offsets[k];
         blocks1 += (n + 63) / 64 * ((n + 127) / 128);

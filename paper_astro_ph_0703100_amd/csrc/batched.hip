@@ -91,6 +91,44 @@ __global__ __launch_bounds__(256) void system_centre_kernel(const int64_t *offse
     if (threadIdx.x < 3) centre[3 * k + threadIdx.x] = e > b ? sh[threadIdx.x][0] / (double)(e - b) : 0.0;
 }
 
+// One block per system: the leapfrog's first kick and drift (v not null), the FP64 centre in
+// the order of system_centre_kernel, and the conversion relative to it.
+__global__ __launch_bounds__(256) void system_step_kernel(const int64_t *offsets, int64_t total,
+                                                         double *x, double *v, const double *a,
+                                                         double h, double dt, float *out) {
+    __shared__ double sh[3][256];
+    const int64_t b = offsets[blockIdx.x], e = offsets[blockIdx.x + 1];
+    double s[3] = {0.0, 0.0, 0.0};
+    for (int64_t p = b + threadIdx.x; p < e; p += 256)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int64_t q = c * total + p;
+            double xx = x[q];
+            if (v) {
+                const double vv = v[q] + h * a[q];
+                v[q] = vv;
+                xx = xx + dt * vv;
+                x[q] = xx;
+            }
+            s[c] += xx;
+        }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
+        __syncthreads();
+    }
+    for (int64_t p = b + threadIdx.x; p < e; p += 256)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const int64_t q = c * total + p;
+            out[q] = (float)(x[q] - sh[c][0] / (double)(e - b));
+        }
+}
+
 __global__ __launch_bounds__(256) void batched_convert_kernel(int64_t total, const double *pos,
                                                              const int32_t *sys_of,
                                                              const double *centre, float *out) {
@@ -164,6 +202,16 @@ nbody_status launch_system_centres(int nsys, const int64_t *offsets, int64_t tot
                                    const double *pos64, double *centre, hipStream_t s) {
     if (nsys <= 0) return NBODY_OK;
     hipLaunchKernelGGL(system_centre_kernel, dim3(nsys), dim3(256), 0, s, offsets, total, pos64, centre);
+    NBODY_HIP_CHECK(hipGetLastError());
+    return NBODY_OK;
+}
+
+nbody_status launch_system_step(int nsys, const int64_t *offsets, int64_t total, double *x, double *v,
+                                const double *a, double h, double dt, float *pos32,
+                                hipStream_t s) {
+    if (nsys <= 0) return NBODY_OK;
+    hipLaunchKernelGGL(system_step_kernel, dim3(nsys), dim3(256), 0, s, offsets, total, x, v, a, h,
+                       dt, pos32);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }

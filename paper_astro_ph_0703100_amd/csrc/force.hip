@@ -24,6 +24,22 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
     });
 }
 
+// The same between two leapfrog steps: block (b, c) holds component c of the particles
+// [256 b, 256 b + 256), so after the drift it also sums its part of the centre's first stage.
+// Grid: (kCentreBlocks, 3).
+template <int MODE, int BATCH>
+__global__ __launch_bounds__(256) void finalize_step_kernel(FinalizeArgs a, double *centre_part) {
+    __shared__ double sh[256];
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int c = blockIdx.y;
+    double x = 0.0;
+    if (i < a.n)
+        x = ForceOut::store(a, (size_t)c * a.n + i,
+                            engine::sum_partial_output<kForceOutputs, MODE, BATCH>(
+                                a.part, a.nseg, (size_t)a.npad, i, c));
+    engine::tree_sum_256(x, sh, centre_part + 3 * blockIdx.x + c);
+}
+
 // Two-stage fixed-order FP64 mean of the positions [3][n]: kCentreBlocks partial
 // sums, then their fixed-order sum.  Deterministic for a given n.
 
@@ -65,6 +81,106 @@ __global__ __launch_bounds__(256) void centred_convert_kernel(int64_t n, const d
     if (i >= n) return;
 #pragma unroll
     for (int c = 0; c < 3; ++c) out[c * n + i] = (float)(pos[c * n + i] - sh[c][0] / (double)n);
+}
+
+// The second stage and conversion of two arrays (blockIdx.y).
+__global__ __launch_bounds__(256) void centred_convert2_kernel(int64_t n, const double *a,
+                                                              const double *a_part, float *a_out,
+                                                              const double *b,
+                                                              const double *b_part, float *b_out) {
+    __shared__ double sh[3][kCentreBlocks];
+    const double *pos = blockIdx.y ? b : a;
+    const double *part = blockIdx.y ? b_part : a_part;
+    float *out = blockIdx.y ? b_out : a_out;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = part[threadIdx.x * 3 + c];
+    __syncthreads();
+    for (int w = kCentreBlocks / 2; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
+        __syncthreads();
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[c * n + i] = (float)(pos[c * n + i] - sh[c][0] / (double)n);
+}
+
+// v + (value of lane + W, for the lanes below W), the tree step of distance W inside a wave.
+template <int W>
+__device__ __forceinline__ double tree_step(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)b, hi = (int)(b >> 32);
+    auto join = [](int l, int h) {
+        return __longlong_as_double((long long)(((unsigned long long)(unsigned)h << 32) | (unsigned)l));
+    };
+    if constexpr (W == 32) {
+        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return join(l[0], h[0]) + join(l[1], h[1]);
+    } else if constexpr (W == 16) {
+        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return join(l[0], h[0]) + join(l[1], h[1]);
+    } else {
+        constexpr int kCtrl = W == 8 ? 0x128 :  // row_ror 8
+                              W == 4 ? 0x12C :  // row_ror 12: lane l receives lane l + 4
+                              W == 2 ? 0x4E :   // quad_perm [2, 3, 0, 1]
+                                       0xB1;    // quad_perm [1, 0, 3, 2]
+        return v + join(__builtin_amdgcn_mov_dpp(lo, kCtrl, 0xF, 0xF, false),
+                        __builtin_amdgcn_mov_dpp(hi, kCtrl, 0xF, 0xF, false));
+    }
+}
+
+// Centre and conversion in one launch, for few particles (kSelfCentre): each block adds the
+// whole centre in the order of the two stages, a wave taking 256 particles (one first-stage
+// block) at a time with its lanes holding what would be four threads.  Reading every position
+// per block costs less than the launch of a separate first stage (N = 2048: about 3 us).
+__global__ __launch_bounds__(256) void self_centred_convert_kernel(int64_t n, const double *a,
+                                                                  float *a_out, const double *b,
+                                                                  float *b_out) {
+    __shared__ double sh[3][32];
+    const double *pos = blockIdx.y ? b : a;
+    float *out = blockIdx.y ? b_out : a_out;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int chunks = (int)((n + 255) / 256);  // at most 32
+    for (int q = wave; q < chunks; q += 4) {
+        double v[3][4];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int64_t i = q * 256 + k * 64 + lane;
+                v[c][k] = i < n ? pos[c * n + i] : 0.0;
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            double s = (v[c][0] + v[c][2]) + (v[c][1] + v[c][3]);  // distances 128, then 64
+            s = tree_step<32>(s);
+            s = tree_step<16>(s);
+            s = tree_step<8>(s);
+            s = tree_step<4>(s);
+            s = tree_step<2>(s);
+            s = tree_step<1>(s);
+            if (lane == 0) sh[c][q] = s;
+        }
+    }
+    __syncthreads();
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        // The other first-stage blocks hold zeros: the tree's distances above 16 add nothing.
+        double s = lane < chunks ? sh[c][lane & 31] : 0.0;
+        s = tree_step<16>(s);
+        s = tree_step<8>(s);
+        s = tree_step<4>(s);
+        s = tree_step<2>(s);
+        s = tree_step<1>(s);
+        const double centre = __shfl(s, 0) / (double)n;
+        if (i < n) out[c * n + i] = (float)(pos[c * n + i] - centre);
+    }
 }
 
 __global__ __launch_bounds__(256) void convert_kernel(int64_t n, const double *pos,
@@ -143,11 +259,36 @@ nbody_status launch_finalize(int precision, const FinalizeArgs &a, hipStream_t s
     return NBODY_OK;
 }
 
+template <int MODE>
+void launch_finalize_step_mode(bool deep, const FinalizeArgs &a, double *centre_part,
+                               hipStream_t s) {
+    const dim3 grid(kCentreBlocks, 3);
+    if (deep)
+        hipLaunchKernelGGL((finalize_step_kernel<MODE, 8>), grid, dim3(256), 0, s, a, centre_part);
+    else
+        hipLaunchKernelGGL((finalize_step_kernel<MODE, 1>), grid, dim3(256), 0, s, a, centre_part);
+}
+
+nbody_status launch_finalize_step(int precision, const FinalizeArgs &a, double *centre_part,
+                                  hipStream_t s) {
+    if (a.n <= 0) return NBODY_OK;
+    const bool deep = engine::finalize_batch(a.n, 3) > 1;
+    switch (precision) {
+        case NBODY_PLAIN: launch_finalize_step_mode<NBODY_PLAIN>(deep, a, centre_part, s); break;
+        case NBODY_FP64RED: launch_finalize_step_mode<NBODY_FP64RED>(deep, a, centre_part, s); break;
+        case NBODY_COMP: launch_finalize_step_mode<NBODY_COMP>(deep, a, centre_part, s); break;
+        default: return set_error(NBODY_EINVAL, "unknown precision mode");
+    }
+    NBODY_HIP_CHECK(hipGetLastError());
+    return NBODY_OK;
+}
+
 size_t centre_scratch_bytes() { return sizeof(double) * 3 * kCentreBlocks; }
 
 nbody_status launch_centred_convert(int64_t n, const double *pos64, double *scratch,
                                     float *pos32, hipStream_t s) {
     if (n <= 0) return NBODY_OK;
+    if (n <= kSelfCentre) return launch_self_centred_convert(n, pos64, pos32, nullptr, nullptr, s);
     hipLaunchKernelGGL(centre_partial_kernel, dim3(kCentreBlocks), dim3(256), 0, s, n, pos64, scratch);
     NBODY_HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(centred_convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
@@ -161,6 +302,27 @@ nbody_status launch_centred_convert_ready(int64_t n, const double *pos64, const 
     if (n <= 0) return NBODY_OK;
     hipLaunchKernelGGL(centred_convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
                        n, pos64, scratch, pos32);
+    NBODY_HIP_CHECK(hipGetLastError());
+    return NBODY_OK;
+}
+
+nbody_status launch_centred_convert_ready2(int64_t n, const double *a64, const double *a_part,
+                                           float *a32, const double *b64, const double *b_part,
+                                           float *b32, hipStream_t s) {
+    if (n <= 0) return NBODY_OK;
+    hipLaunchKernelGGL(centred_convert2_kernel, dim3((unsigned)((n + 255) / 256), 2), dim3(256), 0, s,
+                       n, a64, a_part, a32, b64, b_part, b32);
+    NBODY_HIP_CHECK(hipGetLastError());
+    return NBODY_OK;
+}
+
+nbody_status launch_self_centred_convert(int64_t n, const double *a64, float *a32, const double *b64,
+                                         float *b32, hipStream_t s) {
+    if (n <= 0) return NBODY_OK;
+    if (n > kSelfCentre) return set_error(NBODY_EINVAL, "too many particles for a one-launch centre");
+    hipLaunchKernelGGL(self_centred_convert_kernel,
+                       dim3((unsigned)((n + 255) / 256), b64 ? 2 : 1), dim3(256), 0, s, n, a64, a32,
+                       b64, b32);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }

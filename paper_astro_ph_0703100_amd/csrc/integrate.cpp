@@ -1,10 +1,11 @@
 // Kick-drift-kick leapfrog on FP64 state and its capture into HIP graphs.
 //
 // One step:  v += (dt/2) a(x);  x += dt v;  a = a(x);  v += (dt/2) a
-// The first kick and the drift are one element-wise kernel; the force evaluation is
-// the FP64-position path (centre, FP32 conversion, pair kernel, FP64 finalize) and
-// the second kick is fused into the finalize.  a(x) carries over from one step to the
-// next, so each step costs one force evaluation.
+// The first kick and the drift of the first step are one element-wise kernel; the force
+// evaluation is the FP64-position path (centre, FP32 conversion, pair kernel, FP64
+// finalize) and the second kick is fused into the finalize, with the next step's first kick
+// and drift where it pays (below).  a(x) carries over from one step to the next, so each
+// step costs one force evaluation.
 #include <cmath>
 #include <functional>
 #include <new>
@@ -43,6 +44,32 @@ nbody_status enqueue_steps(int64_t n, double *x, double *v, const float *m, floa
             return st;
     }
     if (traj && (st = launch_copy_f64((int64_t)n3, x, traj, s))) return st;
+    // Between two steps, the launch that stores a(x) also starts the next step: nothing reads
+    // the FP64 positions during it (the pairs read the FP32 copies, except with per-tile
+    // centres).  The centre of the new positions is then summed by that launch (finalize) or
+    // by the conversion (few particles).  At most 65536 particles: above, the element-wise
+    // launches are under 1 % of a step.  N = 2048: 3 -> 2 launches, 16384: 4 -> 3.
+    const bool stored = stores_outputs(cfg);
+    const bool chain = o.centre == NBODY_CENTRE_SYSTEM && !cfg.sym &&
+                       n <= (stored ? kSelfCentre : kStepCentre);
+    if (chain) {
+        for (int32_t t = 0; t < nsteps; ++t) {
+            if (t == 0) {
+                double *checkpoint = traj ? traj + n3 : nullptr;
+                st = stored ? launch_kick_drift(n, x, v, acc, 0.5 * dt, dt, s, checkpoint)
+                            : launch_kick_drift_centre(n, x, v, acc, 0.5 * dt, dt, checkpoint,
+                                                       ws.centre_scratch, s);
+                if (st) return st;
+            }
+            const bool last = t + 1 == nsteps;
+            const NextDrift next{x, dt, traj && !last ? traj + (size_t)(t + 2) * n3 : nullptr,
+                                 ws.centre_scratch};
+            if ((st = force_f64_core(n, x, m, eps, acc, last ? pot : nullptr, o, cfg, ws, v,
+                                     0.5 * dt, s, !stored, last ? nullptr : &next)))
+                return st;
+        }
+        return NBODY_OK;
+    }
     for (int32_t t = 0; t < nsteps; ++t) {
         double *checkpoint = traj ? traj + (size_t)(t + 1) * n3 : nullptr;
         // With the system centre, the kick-drift also sums the new positions for it.

@@ -50,17 +50,44 @@ nbody_status check_jerk(int64_t n, const void *pos, const void *vel, const void 
     return NBODY_OK;
 }
 
+// A Hermite step's tail (see JerkFinalizeArgs) and where the centres' first stages over the
+// next predicted state go if a finalize launch sums them.
+struct HermiteTail {
+    double *x, *v, *xp, *vp;
+    double dt;
+    double *x_part, *v_part;
+};
+
 nbody_status jerk_core(int64_t n, const float *pos, const float *vel, const float *mass, float eps,
                        double *acc, double *jerk, double *pot, const nbody_opts &o,
-                       const TileCfg &cfg, void *part, hipStream_t s) {
+                       const TileCfg &cfg, void *part, hipStream_t s,
+                       const HermiteTail *tail = nullptr) {
     const float e2 = eps * eps;
     JerkArgs a{pos, pos + n, pos + 2 * n, mass, vel, vel + n, vel + 2 * n,
                (int)n, cfg.wseg_len, e2, part, cfg.npad};
     JerkFinalizeArgs fa{part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,  jerk,     pot};
+    if (tail) {
+        fa.x = tail->x;
+        fa.v = tail->v;
+        fa.xp = tail->xp;
+        fa.vp = tail->vp;
+        fa.dt = tail->dt;
+    }
     nbody_status st = launch_jerk(cfg, o.precision, pot != nullptr, a, fa, s);
     if (st || cfg.wseg == 1) return st;
-    return launch_jerk_finalize(o.precision, fa, s);
+    return tail ? launch_jerk_finalize_step(o.precision, fa, tail->xp ? tail->x_part : nullptr,
+                                            tail->v_part, s)
+                : launch_jerk_finalize(o.precision, fa, s);
+}
+
+// FP32 positions and velocities relative to their FP64 means.
+nbody_status centred_state(int64_t n, const double *pos64, const double *vel64,
+                           const JerkScratch &w, hipStream_t s) {
+    if (n <= kSelfCentre) return launch_self_centred_convert(n, pos64, w.x32, vel64, w.v32, s);
+    nbody_status st = launch_centred_convert(n, pos64, w.cscratch, w.x32, s);
+    if (st) return st;
+    return launch_centred_convert(n, vel64, w.cscratch, w.v32, s);
 }
 
 // One evaluation from FP64 state: centres and FP32 conversion per opts.centre, then
@@ -89,8 +116,7 @@ nbody_status jerk_f64_core(int64_t n, const double *pos64, const double *vel64, 
     if (o.centre == NBODY_CENTRE_SYSTEM) {
         // Positions relative to the FP64 mean position, velocities relative to the FP64
         // mean velocity: differences of the shifted values are what the pairs need.
-        if ((st = launch_centred_convert(n, pos64, w.cscratch, w.x32, s))) return st;
-        if ((st = launch_centred_convert(n, vel64, w.cscratch, w.v32, s))) return st;
+        if ((st = centred_state(n, pos64, vel64, w, s))) return st;
     } else {
         if ((st = launch_convert(n, pos64, nullptr, w.x32, s))) return st;
         if ((st = launch_convert(n, vel64, nullptr, w.v32, s))) return st;
@@ -141,6 +167,30 @@ nbody_status enqueue_hermite(int64_t n, double *x, double *v, const float *m, fl
     nbody_status st;
     if (init && (st = jerk_f64_core(n, x, v, m, eps, acc, jerk, nullptr, o, cfg, h.eval, s)))
         return st;
+    // The launch that adds the new (a, j) also corrects the step and predicts the next one (the
+    // pairs read the FP32 copies of the predicted state); the centres of that are summed there
+    // or, with few particles, by the conversion.  Up to 65536 particles, as in the leapfrog;
+    // N = 4099: 8 -> 3 launches per step.  The velocity centre's first stage goes where a1 is
+    // kept otherwise, which holds it from 256 particles on.
+    const bool stored = stores_outputs(cfg);
+    if (o.centre == NBODY_CENTRE_SYSTEM && nsteps > 0 &&
+        (stored ? n <= kSelfCentre : n >= 256 && n <= kStepCentre)) {
+        if ((st = launch_hermite_predict(n, x, v, acc, jerk, dt, h.xp, h.vp, s))) return st;
+        for (int32_t t = 0; t < nsteps; ++t) {
+            const bool last = t + 1 == nsteps;
+            st = t == 0 || stored
+                     ? centred_state(n, h.xp, h.vp, h.eval, s)
+                     : launch_centred_convert_ready2(n, h.xp, h.eval.cscratch, h.eval.x32, h.vp,
+                                                     h.a1, h.eval.v32, s);
+            if (st) return st;
+            const HermiteTail tail{x,  v, last ? nullptr : h.xp, last ? nullptr : h.vp,
+                                   dt, h.eval.cscratch, h.a1};
+            if ((st = jerk_core(n, h.eval.x32, h.eval.v32, m, eps, acc, jerk, nullptr, o, cfg,
+                                h.eval.part, s, &tail)))
+                return st;
+        }
+        return NBODY_OK;
+    }
     for (int32_t t = 0; t < nsteps; ++t) {
         if ((st = launch_hermite_predict(n, x, v, acc, jerk, dt, h.xp, h.vp, s))) return st;
         if ((st = jerk_f64_core(n, h.xp, h.vp, m, eps, h.a1, h.j1, nullptr, o, cfg, h.eval, s)))

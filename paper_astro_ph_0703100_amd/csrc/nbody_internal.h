@@ -213,6 +213,12 @@ struct JerkFinalizeArgs {
     double *acc;   // [3][n]
     double *jerk;  // [3][n]
     double *pot;   // [n] or nullptr
+    // Hermite step: if x is not null, acc and jerk hold a and j of the step's start, the sums
+    // are those of the predicted state, and the corrector follows (x, v, acc, jerk); with xp
+    // not null also the next step's predictor (xp, vp).
+    double *x = nullptr, *v = nullptr;
+    double *xp = nullptr, *vp = nullptr;
+    double dt = 0.0;
 };
 
 // One work item (block) of a ragged batch: some i's of one system against a j-range of the
@@ -263,6 +269,11 @@ struct FinalizeArgs {
     double *pot;       // [n] or nullptr
     double *kick_v;    // [3][n]: if not null, v += kick_h * a after a is written
     double kick_h;
+    // Leapfrog between two steps: if not null, the next step's first kick (kick_h again) and
+    // drift follow: v += kick_h * a, x += drift_dt * v, and checkpoint = x.
+    double *drift_x = nullptr;
+    double drift_dt = 0.0;
+    double *checkpoint = nullptr;
 };
 
 struct VjpArgs {
@@ -299,6 +310,11 @@ struct VjpFinalizeArgs {
     double *grad_mass;  // [n] or nullptr
     int accumulate;     // 1: add into grad_pos / grad_mass instead of overwriting
     const double *ga;   // dL/da [3][n]: the particle's own cotangent (its FP32 value is used)
+    // Reverse leapfrog between two steps: if not null, vbar += step_dt * grad_pos and
+    // abar (the array ga points to) = step_h * vbar follow.
+    double *vbar = nullptr;
+    double *abar = nullptr;
+    double step_dt = 0.0, step_h = 0.0;
 };
 
 // Thread-local error reporting.
@@ -357,11 +373,26 @@ nbody_opts resolve_opts(const nbody_opts *opts);
 // Argument checks of the FP32-position force entry points (before anything is enqueued).
 nbody_status check_force_f32(int64_t n, const float *pos, const float *mass, float eps,
                              const double *acc, const double *pot, const nbody_opts &o);
+// What follows the second kick when another leapfrog step comes: its first kick and drift
+// (x += dt v, checkpoint = x), and where the centre's first stage over the new x goes if a
+// finalize launch can sum it.
+struct NextDrift {
+    double *x;
+    double dt;
+    double *checkpoint;
+    double *centre_part;
+};
+
+// The pair launch stores the outputs itself (no finalize launch).
+inline bool stores_outputs(const TileCfg &c) { return c.jl > 1 || (!c.sym && c.wseg == 1); }
+
 // Pair kernel + FP64 finalize on FP32 positions [3][n] with the partial sums in `ws`
-// (partial_bytes(cfg, o.precision) bytes); with kick_v set, v += kick_h * a follows.
+// (partial_bytes(cfg, o.precision) bytes); with kick_v set, v += kick_h * a follows, and
+// with `next` the next step's start (not with potentials).
 nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, float eps, double *acc,
                             double *pot, const nbody_opts &o, const TileCfg &cfg, void *ws,
-                            double *kick_v, double kick_h, hipStream_t s);
+                            double *kick_v, double kick_h, hipStream_t s,
+                            const NextDrift *next = nullptr);
 
 // Scratch layout of one FP64-position force evaluation: partial sums, FP32 relative
 // positions [3][n] (or, with per-i-tile centres, the tile centres), and the partials of
@@ -383,7 +414,7 @@ F64Scratch f64_scratch_layout(void *ws, int64_t n, const TileCfg &cfg, int preci
 nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, float eps,
                             double *acc, double *pot, const nbody_opts &o, const TileCfg &cfg,
                             const F64Scratch &ws, double *kick_v, double kick_h, hipStream_t s,
-                            bool centre_ready = false);
+                            bool centre_ready = false, const NextDrift *next = nullptr);
 
 // Records the launches `body` enqueues on a capture stream into g->graph and
 // instantiates g->exec (integrate.cpp).
@@ -401,6 +432,10 @@ const DeviceInfo &device_info();
 nbody_status launch_pair(const TileCfg &cfg, int precision, bool with_pot, const PairArgs &a,
                          const FinalizeArgs &f, hipStream_t s);
 nbody_status launch_finalize(int precision, const FinalizeArgs &a, hipStream_t s);
+// The finalize between two leapfrog steps (a.drift_x set, a.pot not; n <= kStepCentre), with
+// the centre's first stage over the new positions written to centre_part.
+nbody_status launch_finalize_step(int precision, const FinalizeArgs &a, double *centre_part,
+                                  hipStream_t s);
 // Split engine (cfg.jl > 1): pair sums and outputs in one launch (force_split.hip,
 // vjp_split.hip); the finalize arguments say what is stored.
 nbody_status launch_pair_split(const TileCfg &cfg, int precision, bool with_pot,
@@ -422,6 +457,18 @@ nbody_status launch_centred_convert_ready(int64_t n, const double *pos64, const 
                                           float *pos32, hipStream_t s);
 nbody_status launch_convert(int64_t n, const double *pos64, const double *centre, float *pos32,
                             hipStream_t s);
+// launch_centred_convert in one launch, for n <= kSelfCentre: every block sums the centre for
+// itself, in the same order.  With a second pair of arrays, both.
+constexpr int64_t kSelfCentre = 8192;
+nbody_status launch_self_centred_convert(int64_t n, const double *a64, float *a32, const double *b64,
+                                         float *b32, hipStream_t s);
+// launch_centred_convert_ready of two arrays in one launch.
+nbody_status launch_centred_convert_ready2(int64_t n, const double *a64, const double *a_part,
+                                           float *a32, const double *b64, const double *b_part,
+                                           float *b32, hipStream_t s);
+// Largest n whose finalize can also sum the centre's first stage: one particle per thread of
+// its kCentreBlocks blocks.
+constexpr int64_t kStepCentre = (int64_t)kCentreBlocks * 256;
 // Bytes of the centre-reduction scratch (partials of the two-stage FP64 sum).
 size_t centre_scratch_bytes();
 // Per-i-tile FP64 centres (mean position of each tile of `itile` particles) and the pair
@@ -466,6 +513,11 @@ nbody_status launch_batched_pair(int ipl, int jt, int waves, int precision, bool
 nbody_status launch_batched_finalize(int precision, const BatchFinalizeArgs &a, hipStream_t s);
 nbody_status launch_system_centres(int nsys, const int64_t *offsets, int64_t total,
                                    const double *pos64, double *centre, hipStream_t s);
+// Per system in one launch: kick and drift (v += h a, x += dt v; skipped with v null), FP64
+// centre and conversion, for systems small enough for one block each.
+nbody_status launch_system_step(int nsys, const int64_t *offsets, int64_t total, double *x, double *v,
+                                const double *a, double h, double dt, float *pos32,
+                                hipStream_t s);
 nbody_status launch_batched_convert(int64_t total, const double *pos64, const int32_t *sys_of,
                                     const double *centre, float *pos32, hipStream_t s);
 // Force-jerk-potential kernels and their FP64 finalize (jerk.hip, jerk_tile.hip, jerk_ij.hip);
@@ -473,6 +525,10 @@ nbody_status launch_batched_convert(int64_t total, const double *pos64, const in
 nbody_status launch_jerk(const TileCfg &cfg, int precision, bool with_pot, const JerkArgs &a,
                          const JerkFinalizeArgs &f, hipStream_t s);
 nbody_status launch_jerk_finalize(int precision, const JerkFinalizeArgs &a, hipStream_t s);
+// The finalize that ends a Hermite step (a.x set; n <= kStepCentre); with a.xp set, the centres'
+// first stages over the next predicted positions and velocities go to x_part and v_part.
+nbody_status launch_jerk_finalize_step(int precision, const JerkFinalizeArgs &a, double *x_part,
+                                       double *v_part, hipStream_t s);
 nbody_status launch_jerk_tile(const TileCfg &cfg, int precision, bool with_pot,
                               const JerkTileArgs &a, const JerkFinalizeArgs &f, hipStream_t s);
 nbody_status launch_jerk_ij(const TileCfg &cfg, int precision, bool with_pot, const JerkIJArgs &a,
@@ -489,5 +545,9 @@ nbody_status launch_vjp(const TileCfg &cfg, int precision, const VjpArgs &a, boo
 nbody_status launch_vjp_tile(const TileCfg &cfg, int precision, const VjpTileArgs &a,
                              bool with_mass, const VjpFinalizeArgs &f, hipStream_t s);
 nbody_status launch_vjp_finalize(int precision, const VjpFinalizeArgs &a, hipStream_t s);
+// The finalize between two reverse steps (a.vbar set; n <= kStepCentre), with the centre's
+// first stage over `next`, the checkpoint the following evaluation reads.
+nbody_status launch_vjp_finalize_step(int precision, const VjpFinalizeArgs &a, const double *next,
+                                      double *centre_part, hipStream_t s);
 
 }  // namespace nbody

@@ -23,8 +23,23 @@ struct ForceOut {
             a.pot[i] = r;
             return;
         }
-        a.acc[c * (size_t)a.n + i] = r;
-        if (a.kick_v) a.kick_v[c * (size_t)a.n + i] += a.kick_h * r;
+        store(a, c * (size_t)a.n + i, r);
+    }
+    // Acceleration component r at flat index q, with what follows it in a leapfrog step;
+    // returns the drifted coordinate (0 without a drift).
+    static __device__ __forceinline__ double store(const Args &a, size_t q, double r) {
+        a.acc[q] = r;
+        if (!a.kick_v) return 0.0;
+        double v = a.kick_v[q] + a.kick_h * r;
+        double x = 0.0;
+        if (a.drift_x) {
+            v = v + a.kick_h * r;
+            x = a.drift_x[q] + a.drift_dt * v;
+            a.drift_x[q] = x;
+            if (a.checkpoint) a.checkpoint[q] = x;
+        }
+        a.kick_v[q] = v;
+        return x;
     }
 };
 
@@ -37,8 +52,12 @@ struct JerkOut {
     static constexpr int stores(bool full) { return full ? 7 : 6; }
     template <class Sum>
     static __device__ __forceinline__ void put(const Args &a, int i, int c, Sum sum) {
-        double r = sum(c);
         const size_t n = (size_t)a.n;
+        if (a.x) {
+            if (c < 3) step(a, c * n + i, sum(c), sum(c + 3));
+            return;
+        }
+        double r = sum(c);
         if (c == 6) {
             if (a.include_self) r -= (double)a.m[i] / (double)a.eps;
             a.pot[i] = r;
@@ -47,6 +66,28 @@ struct JerkOut {
         } else {
             a.jerk[(c - 3) * n + i] = r;
         }
+    }
+    // The corrector of flat index q, v' = v + (a + a1) dt/2 + (j - j1) dt^2/12 and x' = x +
+    // (v + v') dt/2 + (a - a1) dt^2/12, then (a, j) <- (a1, j1) and the next step's predictor,
+    // x_p = x + v dt + a dt^2/2 + j dt^3/6 and v_p = v + a dt + j dt^2/2 (returned).
+    static __device__ __forceinline__ double2 step(const Args &a, size_t q, double an, double jn) {
+        const double dt = a.dt;
+        const double dt2 = dt * dt;
+        const double a0 = a.acc[q], j0 = a.jerk[q], v0 = a.v[q];
+        const double vn = v0 + (a0 + an) * dt / 2.0 + (j0 - jn) * dt2 / 12.0;
+        const double xn = a.x[q] + (v0 + vn) * dt / 2.0 + (a0 - an) * dt2 / 12.0;
+        a.x[q] = xn;
+        a.v[q] = vn;
+        a.acc[q] = an;
+        a.jerk[q] = jn;
+        double2 p = make_double2(0.0, 0.0);
+        if (a.xp) {
+            p.x = xn + vn * dt + an * dt2 / 2.0 + jn * dt2 * dt / 6.0;
+            p.y = vn + an * dt + jn * dt2 / 2.0;
+            a.xp[q] = p.x;
+            a.vp[q] = p.y;
+        }
+        return p;
     }
 };
 
@@ -63,8 +104,14 @@ struct VjpOut {
         if (c < 3) {
             const double gk = (double)(float)a.ga[(size_t)c * a.n + i];
             const double r = sum(c) - gk * sum(3);
-            double *g = a.grad_pos + (size_t)c * a.n + i;
-            *g = a.accumulate ? *g + r : r;
+            const size_t q = (size_t)c * a.n + i;
+            const double g = a.accumulate ? a.grad_pos[q] + r : r;
+            a.grad_pos[q] = g;
+            if (a.vbar) {
+                const double vb = a.vbar[q] + a.step_dt * g;
+                a.vbar[q] = vb;
+                a.abar[q] = a.step_h * vb;
+            }
             return;
         }
         const double gm = -sum(4);

@@ -22,6 +22,25 @@ __global__ __launch_bounds__(256) void vjp_finalize_kernel(VjpFinalizeArgs a) {
     });
 }
 
+// The same between two reverse leapfrog steps: slots 0-2 also update vbar and abar and sum
+// their part of the centre's first stage over `next`.  Grid: (kCentreBlocks, 4 slots, or 3).
+template <int MODE, int BATCH>
+__global__ __launch_bounds__(256) void vjp_finalize_step_kernel(VjpFinalizeArgs a,
+                                                               const double *next,
+                                                               double *centre_part) {
+    __shared__ double sh[256];
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    const int c = blockIdx.y;
+    if (k < a.n)
+        VjpOut::put(a, k, c, [&](int o) {
+            return engine::sum_partial_output<kVjpOutputs, MODE, BATCH>(a.part, a.nseg,
+                                                                        (size_t)a.npad, k, o);
+        });
+    if (c < 3)
+        engine::tree_sum_256(k < a.n ? next[(size_t)c * a.n + k] : 0.0, sh,
+                             centre_part + 3 * blockIdx.x + c);
+}
+
 }  // namespace
 
 nbody_status launch_vjp(const TileCfg &cfg, int precision, const VjpArgs &a, bool with_mass,
@@ -35,6 +54,37 @@ void launch_vjp_finalize_mode(dim3 grid, bool deep, const VjpFinalizeArgs &a, hi
         hipLaunchKernelGGL((vjp_finalize_kernel<MODE, 8>), grid, dim3(256), 0, s, a);
     else
         hipLaunchKernelGGL((vjp_finalize_kernel<MODE, 1>), grid, dim3(256), 0, s, a);
+}
+
+template <int MODE>
+void launch_vjp_finalize_step_mode(dim3 grid, bool deep, const VjpFinalizeArgs &a,
+                                   const double *next, double *centre_part, hipStream_t s) {
+    if (deep)
+        hipLaunchKernelGGL((vjp_finalize_step_kernel<MODE, 8>), grid, dim3(256), 0, s, a, next, centre_part);
+    else
+        hipLaunchKernelGGL((vjp_finalize_step_kernel<MODE, 1>), grid, dim3(256), 0, s, a, next, centre_part);
+}
+
+nbody_status launch_vjp_finalize_step(int precision, const VjpFinalizeArgs &a, const double *next,
+                                      double *centre_part, hipStream_t s) {
+    if (a.n <= 0) return NBODY_OK;
+    const int outputs = a.grad_mass ? 4 : 3;
+    const dim3 grid(kCentreBlocks, outputs);
+    const bool deep = engine::finalize_batch(a.n, outputs) > 1;
+    switch (precision) {
+        case NBODY_PLAIN:
+            launch_vjp_finalize_step_mode<NBODY_PLAIN>(grid, deep, a, next, centre_part, s);
+            break;
+        case NBODY_FP64RED:
+            launch_vjp_finalize_step_mode<NBODY_FP64RED>(grid, deep, a, next, centre_part, s);
+            break;
+        case NBODY_COMP:
+            launch_vjp_finalize_step_mode<NBODY_COMP>(grid, deep, a, next, centre_part, s);
+            break;
+        default: return set_error(NBODY_EINVAL, "unknown precision mode");
+    }
+    NBODY_HIP_CHECK(hipGetLastError());
+    return NBODY_OK;
 }
 
 nbody_status launch_vjp_finalize(int precision, const VjpFinalizeArgs &a, hipStream_t s) {
