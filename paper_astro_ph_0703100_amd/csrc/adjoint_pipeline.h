@@ -77,6 +77,7 @@ struct Adjoint {
     // 128 j's per compensation step (32 before: 1.8 % slower at N = 16384 and 131072).
     static constexpr int kBlockJ = nbody::kBlockJ;
     static constexpr int kMaxIpl = 2;
+    static constexpr bool kLone = false;
     using Args = VjpArgs;
     struct IState {
         float x, y, z, m, nm, gx, gy, gz, np;  // nm = -m_k, np = -p_k
@@ -178,6 +179,7 @@ struct AdjointTile {
     static constexpr int kOut = 5;
     static constexpr int kBlockJ = Adjoint::kBlockJ;
     static constexpr int kMaxIpl = 2;
+    static constexpr bool kLone = false;
     using Args = VjpTileArgs;
     using IState = Adjoint::IState;
     struct Ctx {

@@ -135,8 +135,10 @@ __device__ __forceinline__ double tree_step(double v) {
 
 // Centre and conversion in one launch, for few particles (kSelfCentre): each block adds the
 // whole centre in the order of the two stages, a wave taking 256 particles (one first-stage
-// block) at a time with its lanes holding what would be four threads.  Reading every position
-// per block costs less than the launch of a separate first stage (N = 2048: about 3 us).
+// block) at a time with its lanes holding what would be four threads, two at a time in flight
+// (the latency of the loads is most of the launch; blocks of 16 waves, which need fewer
+// rounds of them, take longer to start: 16 steps of 2048 particles 180 instead of 172 us).
+// Reading every position per block costs less than the launch of a separate first stage.
 __global__ __launch_bounds__(256) void self_centred_convert_kernel(int64_t n, const double *a,
                                                                   float *a_out, const double *b,
                                                                   float *b_out) {
@@ -146,29 +148,37 @@ __global__ __launch_bounds__(256) void self_centred_convert_kernel(int64_t n, co
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int chunks = (int)((n + 255) / 256);  // at most 32
-    for (int q = wave; q < chunks; q += 4) {
-        double v[3][4];
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double mine[3];
 #pragma unroll
-        for (int c = 0; c < 3; ++c)
+    for (int c = 0; c < 3; ++c) mine[c] = i < n ? pos[c * n + i] : 0.0;
+    for (int q0 = wave; q0 < chunks; q0 += 8) {
+        double v[2][3][4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int64_t i = q * 256 + k * 64 + lane;
-                v[c][k] = i < n ? pos[c * n + i] : 0.0;
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t p = (q0 + 4 * d) * 256 + k * 64 + lane;
+                    v[d][c][k] = p < n ? pos[c * n + p] : 0.0;
+                }
+#pragma unroll
+        for (int d = 0; d < 2; ++d)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                // Distances 128 and 64, then the wave's own.
+                double s = (v[d][c][0] + v[d][c][2]) + (v[d][c][1] + v[d][c][3]);
+                s = tree_step<32>(s);
+                s = tree_step<16>(s);
+                s = tree_step<8>(s);
+                s = tree_step<4>(s);
+                s = tree_step<2>(s);
+                s = tree_step<1>(s);
+                if (lane == 0 && q0 + 4 * d < chunks) sh[c][q0 + 4 * d] = s;
             }
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            double s = (v[c][0] + v[c][2]) + (v[c][1] + v[c][3]);  // distances 128, then 64
-            s = tree_step<32>(s);
-            s = tree_step<16>(s);
-            s = tree_step<8>(s);
-            s = tree_step<4>(s);
-            s = tree_step<2>(s);
-            s = tree_step<1>(s);
-            if (lane == 0) sh[c][q] = s;
-        }
     }
     __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         // The other first-stage blocks hold zeros: the tree's distances above 16 add nothing.
@@ -179,7 +189,7 @@ __global__ __launch_bounds__(256) void self_centred_convert_kernel(int64_t n, co
         s = tree_step<2>(s);
         s = tree_step<1>(s);
         const double centre = __shfl(s, 0) / (double)n;
-        if (i < n) out[c * n + i] = (float)(pos[c * n + i] - centre);
+        if (i < n) out[c * n + i] = (float)(mine[c] - centre);
     }
 }
 

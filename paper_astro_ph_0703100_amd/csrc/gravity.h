@@ -94,6 +94,7 @@ struct Gravity {
     // operations per pair), and the FP32 block error stays far below the pair rounding.
     static constexpr int kBlockJ = 128;
     static constexpr int kMaxIpl = 4;
+    static constexpr bool kLone = true;
     using Args = PairArgs;
     struct IState {
         float x, y, z;
@@ -141,6 +142,7 @@ struct GravityTile {
     static constexpr int kOut = 4;
     static constexpr int kBlockJ = Gravity::kBlockJ;
     static constexpr int kMaxIpl = 4;
+    static constexpr bool kLone = true;
     using Args = TilePairArgs;
     using IState = Gravity::IState;
     struct Ctx {
@@ -186,6 +188,7 @@ struct GravityIJ {
     static constexpr int kOut = 4;
     static constexpr int kBlockJ = Gravity::kBlockJ;
     static constexpr int kMaxIpl = 4;
+    static constexpr bool kLone = true;
     using Args = IJPairArgs;
     struct IState {
         float x, y, z, e2;

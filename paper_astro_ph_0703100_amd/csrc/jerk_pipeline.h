@@ -109,6 +109,7 @@ struct GravityJerk {
     // 256-j tiles the four unrolled blocks took 85 VGPRs, 5 waves per SIMD).
     static constexpr int kBlockJ = nbody::kBlockJ;
     static constexpr int kMaxIpl = 2;
+    static constexpr bool kLone = false;
     using Args = JerkArgs;
     struct IState {
         float x, y, z, vx, vy, vz;
@@ -159,6 +160,7 @@ struct GravityJerkTile {
     static constexpr int kOut = 7;
     static constexpr int kBlockJ = GravityJerk::kBlockJ;
     static constexpr int kMaxIpl = 2;
+    static constexpr bool kLone = false;
     using Args = JerkTileArgs;
     using IState = GravityJerk::IState;
     struct Ctx {
@@ -208,6 +210,7 @@ struct GravityJerkIJ {
     static constexpr int kOut = 7;
     static constexpr int kBlockJ = GravityJerk::kBlockJ;
     static constexpr int kMaxIpl = 2;
+    static constexpr bool kLone = false;
     using Args = JerkIJArgs;
     using IState = GravityJerk::IState;
     struct Ctx {};

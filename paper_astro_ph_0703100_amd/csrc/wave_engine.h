@@ -24,6 +24,12 @@ namespace nbody {
 namespace wave {
 
 constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
+// Waves up to which a launch counts as few (LONE, pipelines with Op::kLone): one per SIMD.
+// One launch of the force on N = 1000 / 2000 / 3000 particles (0.1 / 0.5 / 1.1 waves per
+// SIMD): 6.9 / 7.1 / 8.8 us against 7.4 / 7.6 / 8.6 us; PLAIN, 431 particles against 3452:
+// 10.5 against 11.6 us.  The force-jerk gains under 3 % there and loses 20 % at 1.1 (its
+// interleaved pairs take too many registers), so it has no such variant.
+constexpr int64_t kLoneWaves = 1024;
 
 // Bytes of LDS of a block of `waves` waves: staging, then the cross-wave sums.
 template <class Op>
@@ -88,10 +94,54 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
     }
 }
 
+// The same with one record per lane and few waves on the chip: a lone wave issues an
+// instruction every 4.7 clocks whatever it depends on, so what counts is their number.  Four
+// records are read ahead of their pairs and the compiler interleaves the four pair bodies,
+// which leaves no s_nop (a lone wave: 73 clocks per gravity pair instead of 86).
+template <class Op, bool FULL, bool SELF>
+__device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
+                                          const typename Op::IState (&is)[1], float eps2,
+                                          float (&acc)[1][Op::kOut], int lane, int d0) {
+    constexpr int W = Op::kJWords;
+    constexpr int V = W / 4;
+    constexpr int A = 4;
+    static_assert(kStage % A == 0, "whole groups per stage");
+    float jr[2][A][W];
+    auto read = [&](int h, int j0) {
+#pragma unroll
+        for (int p = 0; p < A; ++p)
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const float4 q = tl[(j0 + p) * V + v];
+                jr[h][p][4 * v] = q.x;
+                jr[h][p][4 * v + 1] = q.y;
+                jr[h][p][4 * v + 2] = q.z;
+                jr[h][p][4 * v + 3] = q.w;
+            }
+    };
+    auto pairs = [&](int h, int j0) {
+#pragma unroll
+        for (int p = 0; p < A; ++p)
+            engine::pair_k<Op, FULL, SELF>(jr[h][p], j0 + p, d0 + lane, is[0], eps2, acc[0]);
+    };
+    read(0, 0);
+#pragma unroll 1
+    for (int j0 = 0; j0 < cnt; j0 += 2 * A) {
+        read(1, j0 + A);
+        __builtin_amdgcn_sched_barrier(0);
+        pairs(0, j0);
+        __builtin_amdgcn_sched_barrier(0);
+        read(0, (j0 + 2 * A) & (kStage - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        pairs(1, j0 + A);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
 // One wave's work: its 64 * IPL i-particles from i0 (ni of them exist) against the
 // j-range [j0, j0 + nj), in FP32 blocks of BJ from j0 on.  All arguments are uniform.
 // Sums: FP64RED ds, COMP hs and ls, PLAIN hs.
-template <class Op, int IPL, int BJ, int MODE, bool FULL>
+template <class Op, int IPL, int BJ, int MODE, bool FULL, bool LONE = false>
 __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl, int i0, int ni,
                                           int j0, int nj, float eps2,
                                           float (&hs)[IPL][Op::kOut], float (&ls)[IPL][Op::kOut],
@@ -155,10 +205,16 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
             const int d0 = i0 - jt0;
             auto pass = [&](auto self) {
                 constexpr bool SELF = decltype(self)::value;
+                auto run = [&](float(&acc)[IPL][NO]) {
+                    if constexpr (LONE)
+                        lone_pass<Op, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
+                    else
+                        stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
+                };
                 if constexpr (MODE == NBODY_PLAIN)
-                    stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, hs, lane, d0);
+                    run(hs);
                 else
-                    stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, bs, lane, d0);
+                    run(bs);
             };
             if constexpr (Op::kSelf) {
                 // Does this stage hold any of the wave's own i's?
@@ -262,8 +318,9 @@ __device__ __forceinline__ void store_sums(const typename Sink::Args &f, double 
 
 // Grid launch: blockIdx.x = group of 64 * IPL i's, blockIdx.y = j-segment of a.seg_len
 // j's (PLAIN: one segment per wave, blockDim.x / 64 of them per block).  Partial planes
-// [segment][word][npad], or, with nseg = 1, the outputs through the Sink.
-template <class Op, class Sink, int IPL, int BJ, int MODE, bool FULL>
+// [segment][word][npad], or, with nseg = 1, the outputs through the Sink.  LONE: for launches
+// of few waves.
+template <class Op, class Sink, int IPL, int BJ, int MODE, bool FULL, bool LONE>
 __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typename Sink::Args f,
                                                     int nseg) {
     constexpr int NO = Op::kOut;
@@ -286,11 +343,11 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
     float hs[IPL][NO], ls[IPL][NO];
     double ds[IPL][NO];
     if constexpr (MODE == NBODY_PLAIN) {
-        wave_work<Op, IPL, BJ, MODE, FULL>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
+        wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
         store_plain<Sink, IPL, FULL>(f, i0, n, hs, nseg == 1, part, plane, (size_t)i0);
     } else {
         const Run r = block_run<BJ>(nj, wave, waves);
-        wave_work<Op, IPL, BJ, MODE, FULL>(a, tl, i0, ni, j0 + r.j0, r.nj, a.eps2, hs, ls, ds);
+        wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0 + r.j0, r.nj, a.eps2, hs, ls, ds);
         store_sums<Sink, IPL, MODE, FULL>(f, reinterpret_cast<double *>(lds), wave, waves, i0, n,
                                           hs, ls, ds, nseg == 1, part, plane, (size_t)i0);
     }
@@ -301,33 +358,36 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
 template <class Op, class Sink>
 using WaveFn = void (*)(typename Op::Args, typename Sink::Args, int);
 
-template <class Op, class Sink, int IPL>
+template <class Op, class Sink, int IPL, bool LONE = false>
 WaveFn<Op, Sink> pick_mode(int bj, int mode, bool full) {
     switch (mode) {
         case NBODY_PLAIN:
-            return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, true>
-                        : wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, false>;
+            return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, true, LONE>
+                        : wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, false, LONE>;
         case NBODY_FP64RED:
             if (bj == 64)
-                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, true>
-                            : wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, false>;
-            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, true>
-                        : wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, false>;
+                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, true, LONE>
+                            : wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, false, LONE>;
+            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, true, LONE>
+                        : wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, false, LONE>;
         case NBODY_COMP:
             if (bj == 64)
-                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, true>
-                            : wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, false>;
-            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, true>
-                        : wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, false>;
+                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, true, LONE>
+                            : wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, false, LONE>;
+            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, true, LONE>
+                        : wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, false, LONE>;
     }
     return nullptr;
 }
 
 template <class Op, class Sink>
-WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full) {
+WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full, bool lone) {
     static_assert(Op::kBlockJ == 128, "FP32 blocks of 64 or 128 j's");
     switch (ipl) {
-        case 1: return pick_mode<Op, Sink, 1>(bj, mode, full);
+        case 1:
+            if constexpr (Op::kLone)
+                if (lone) return pick_mode<Op, Sink, 1, true>(bj, mode, full);
+            return pick_mode<Op, Sink, 1>(bj, mode, full);
         case 2: return pick_mode<Op, Sink, 2>(bj, mode, full);
         case 4:
             if constexpr (Op::kMaxIpl >= 4) return pick_mode<Op, Sink, 4>(bj, mode, full);
@@ -340,11 +400,13 @@ WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full) {
 template <class Op, class Sink>
 nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
                     const typename Op::Args &a, const typename Sink::Args &f, hipStream_t s) {
-    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full);
+    const int64_t groups = (ni + 64 * cfg.wi - 1) / (64 * cfg.wi);
+    const int64_t waves = groups * cfg.wseg * (precision == NBODY_PLAIN ? 1 : cfg.wpb);
+    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full, waves <= kLoneWaves);
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no pair kernel for this ipl/jtile/precision");
     if (ni <= 0 || cfg.wseg <= 0) return NBODY_OK;
     const int per_block = precision == NBODY_PLAIN ? cfg.wpb : 1;  // segments per block
-    const dim3 grid((unsigned)((ni + 64 * cfg.wi - 1) / (64 * cfg.wi)),
+    const dim3 grid((unsigned)groups,
                     (unsigned)((cfg.wseg + per_block - 1) / per_block));
     hipLaunchKernelGGL(fn, grid, dim3(64 * cfg.wpb), lds_bytes<Op>(cfg.wpb), s, a, f, cfg.wseg);
     NBODY_HIP_CHECK(hipGetLastError());
