@@ -134,6 +134,8 @@ NBODY_LF_INIT_ACC = 1
 def load():
     """Load ``libnbody.so`` (built in-tree) and declare its functions."""
     global _lib
+    if _lib is not None:  # set last, once everything below is done
+        return _lib
     with _lock:
         if _lib is None:
             if not os.path.exists(LIB_PATH):
@@ -145,10 +147,14 @@ def load():
                 f = getattr(lib, name)
                 f.restype = res
                 f.argtypes = args
-            _lib = lib
             path = os.environ.get("NBODY_TUNING_FILE", TUNING_PATH)
-            if path and os.path.exists(path):
-                _check(lib.nbody_tune_load(path.encode()), "nbody_tune_load")
+            try:
+                if path and os.path.exists(path):
+                    st = lib.nbody_tune_load(path.encode())
+                    if st != NBODY_OK:
+                        raise NBodyError(st, "nbody_tune_load", lib.nbody_last_error().decode())
+            finally:
+                _lib = lib
     return _lib
 
 

@@ -16,7 +16,7 @@ from __future__ import annotations
 import torch
 
 from . import _lib
-from .api import _check_pos, make_opts, stream_ptr
+from .api import _call_opts, _check_pos, stream_ptr
 
 __all__ = ["ForceFn", "RolloutFn", "force", "rollout"]
 
@@ -24,7 +24,17 @@ __all__ = ["ForceFn", "RolloutFn", "force", "rollout"]
 def _mass32(mass: torch.Tensor, n: int) -> torch.Tensor:
     if not mass.is_cuda or mass.shape != (n,):
         raise ValueError("mass must be a CUDA tensor of shape [%d]" % n)
-    return mass.detach().to(torch.float32).contiguous()
+    m = mass.detach()
+    if m.dtype is not torch.float32:
+        m = m.to(torch.float32)
+    return m.contiguous()
+
+
+def _f64(g: torch.Tensor) -> torch.Tensor:
+    """``g`` as a contiguous float64 tensor (itself where it is one already)."""
+    if g.dtype is not torch.float64:
+        g = g.to(torch.float64)
+    return g.contiguous()
 
 
 class ForceFn(torch.autograd.Function):
@@ -36,7 +46,7 @@ class ForceFn(torch.autograd.Function):
         m32 = _mass32(mass, n)
         acc = torch.empty((3, n), dtype=torch.float64, device=pos64.device)
         pot = torch.empty(n, dtype=torch.float64, device=pos64.device)
-        opts = make_opts(precision=precision, centre=centre)
+        opts = _call_opts(precision, {}, centre)
         _lib.nbody_force_f64(n, pos64.data_ptr(), m32.data_ptr(), float(eps), acc.data_ptr(),
                              pot.data_ptr(), opts, stream_ptr())
         ctx.save_for_backward(pos64, m32)
@@ -49,18 +59,18 @@ class ForceFn(torch.autograd.Function):
         n = pos64.shape[1]
         dev = pos64.device
         ga = (g_acc if g_acc is not None else torch.zeros((3, n), dtype=torch.float64, device=dev))
-        ga = ga.to(torch.float64).contiguous()
-        gp = g_pot.to(torch.float64).contiguous() if g_pot is not None else None
+        ga = _f64(ga)
+        gp = _f64(g_pot) if g_pot is not None else None
         grad_pos = torch.empty((3, n), dtype=torch.float64, device=dev)
         grad_mass = (torch.empty(n, dtype=torch.float64, device=dev)
                      if ctx.needs_input_grad[1] else None)
-        opts = make_opts(precision=ctx.precision, centre=ctx.centre)
+        opts = _call_opts(ctx.precision, {}, ctx.centre)
         _lib.nbody_force_vjp_f64(n, pos64.data_ptr(), m32.data_ptr(), float(ctx.eps),
                                  ga.data_ptr(), gp.data_ptr() if gp is not None else None,
                                  grad_pos.data_ptr(),
                                  grad_mass.data_ptr() if grad_mass is not None else None,
                                  opts, stream_ptr())
-        if grad_mass is not None:
+        if grad_mass is not None and ctx.mass_dtype is not torch.float64:
             grad_mass = grad_mass.to(ctx.mass_dtype)
         return (grad_pos if ctx.needs_input_grad[0] else None), grad_mass, None, None, None
 
@@ -77,7 +87,7 @@ class RolloutFn(torch.autograd.Function):
         v = v0.detach().clone()
         acc = torch.empty((3, n), dtype=torch.float64, device=x0.device)
         traj = torch.empty((nsteps + 1, 3, n), dtype=torch.float64, device=x0.device)
-        opts = make_opts(precision=precision, centre=centre)
+        opts = _call_opts(precision, {}, centre)
         _lib.nbody_leapfrog(n, x.data_ptr(), v.data_ptr(), m32.data_ptr(), float(eps), float(dt),
                             int(nsteps), acc.data_ptr(), None, traj.data_ptr(),
                             _lib.NBODY_LF_INIT_ACC, opts, stream_ptr())
@@ -96,7 +106,7 @@ class RolloutFn(torch.autograd.Function):
         vbar = (gv.to(torch.float64).clone() if gv is not None
                 else torch.zeros((3, n), dtype=torch.float64, device=dev)).contiguous()
         mbar = torch.zeros(n, dtype=torch.float64, device=dev) if ctx.needs_input_grad[2] else None
-        opts = make_opts(precision=ctx.precision, centre=ctx.centre)
+        opts = _call_opts(ctx.precision, {}, ctx.centre)
         _lib.nbody_leapfrog_adjoint(n, traj.data_ptr(), m32.data_ptr(), float(ctx.eps),
                                     float(ctx.dt), int(ctx.nsteps), xbar.data_ptr(),
                                     vbar.data_ptr(), mbar.data_ptr() if mbar is not None else None,
