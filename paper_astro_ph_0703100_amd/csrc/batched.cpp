@@ -136,7 +136,7 @@ nbody_status enqueue_batched_steps(const nbody_plan *p, double *x, double *v, co
                 return st;
             continue;
         }
-        if ((st = launch_kick_drift(p->total, x, v, acc, 0.5 * dt, dt, s))) return st;
+        if ((st = launch_kick_drift(p->total, x, x, v, acc, 0.5 * dt, dt, s))) return st;
         if ((st = batched_f64_core(p, x, m, eps, acc, t + 1 == nsteps ? pot : nullptr, v, 0.5 * dt, s)))
             return st;
     }

@@ -1,5 +1,6 @@
 // Force evaluation of one system: the gravity pipeline on the tile engine (grid
 // launch), the FP64 finalize, and the FP64-position pre-pass (centre, conversion).
+#include "centre_sum.h"
 #include "gravity.h"
 #include "outputs.h"
 #include "wave_engine.h"
@@ -107,32 +108,6 @@ __global__ __launch_bounds__(256) void centred_convert2_kernel(int64_t n, const 
     for (int c = 0; c < 3; ++c) out[c * n + i] = (float)(pos[c * n + i] - sh[c][0] / (double)n);
 }
 
-// v + (value of lane + W, for the lanes below W), the tree step of distance W inside a wave.
-template <int W>
-__device__ __forceinline__ double tree_step(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = (int)b, hi = (int)(b >> 32);
-    auto join = [](int l, int h) {
-        return __longlong_as_double((long long)(((unsigned long long)(unsigned)h << 32) | (unsigned)l));
-    };
-    if constexpr (W == 32) {
-        const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        return join(l[0], h[0]) + join(l[1], h[1]);
-    } else if constexpr (W == 16) {
-        const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        return join(l[0], h[0]) + join(l[1], h[1]);
-    } else {
-        constexpr int kCtrl = W == 8 ? 0x128 :  // row_ror 8
-                              W == 4 ? 0x12C :  // row_ror 12: lane l receives lane l + 4
-                              W == 2 ? 0x4E :   // quad_perm [2, 3, 0, 1]
-                                       0xB1;    // quad_perm [1, 0, 3, 2]
-        return v + join(__builtin_amdgcn_mov_dpp(lo, kCtrl, 0xF, 0xF, false),
-                        __builtin_amdgcn_mov_dpp(hi, kCtrl, 0xF, 0xF, false));
-    }
-}
-
 // Centre and conversion in one launch, for few particles (kSelfCentre): each block adds the
 // whole centre in the order of the two stages, a wave taking 256 particles (one first-stage
 // block) at a time with its lanes holding what would be four threads, two at a time in flight
@@ -167,29 +142,15 @@ __global__ __launch_bounds__(256) void self_centred_convert_kernel(int64_t n, co
         for (int d = 0; d < 2; ++d)
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                // Distances 128 and 64, then the wave's own.
-                double s = (v[d][c][0] + v[d][c][2]) + (v[d][c][1] + v[d][c][3]);
-                s = tree_step<32>(s);
-                s = tree_step<16>(s);
-                s = tree_step<8>(s);
-                s = tree_step<4>(s);
-                s = tree_step<2>(s);
-                s = tree_step<1>(s);
+                const double s = centre::wave_sum(v[d][c]);
                 if (lane == 0 && q0 + 4 * d < chunks) sh[c][q0 + 4 * d] = s;
             }
     }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        // The other first-stage blocks hold zeros: the tree's distances above 16 add nothing.
-        double s = lane < chunks ? sh[c][lane & 31] : 0.0;
-        s = tree_step<16>(s);
-        s = tree_step<8>(s);
-        s = tree_step<4>(s);
-        s = tree_step<2>(s);
-        s = tree_step<1>(s);
-        const double centre = __shfl(s, 0) / (double)n;
-        if (i < n) out[c * n + i] = (float)(mine[c] - centre);
+        const double mean = centre::second_stage(sh[c], chunks, lane) / (double)n;
+        if (i < n) out[c * n + i] = (float)(mine[c] - mean);
     }
 }
 

@@ -35,7 +35,7 @@ nbody_status check_leapfrog(int64_t n, const double *x, const double *v, const f
 nbody_status enqueue_steps(int64_t n, double *x, double *v, const float *m, float eps, double dt,
                            int32_t nsteps, double *acc, double *pot, double *traj, bool init,
                            const nbody_opts &o, const TileCfg &cfg, const F64Scratch &ws,
-                           hipStream_t s) {
+                           double *alt, hipStream_t s) {
     nbody_status st;
     const size_t n3 = 3 * (size_t)n;
     if (init || (nsteps == 0 && pot)) {
@@ -53,18 +53,22 @@ nbody_status enqueue_steps(int64_t n, double *x, double *v, const float *m, floa
     const bool chain = o.centre == NBODY_CENTRE_SYSTEM && !cfg.sym &&
                        n <= (stored ? kSelfCentre : kStepCentre);
     if (chain) {
+        // alt: positions in turn there and in x, the last ones in x, for evaluations that read
+        // the FP64 positions while they store the next ones (N = 2048: 2 -> 1 launch a step).
+        const auto at = [&](int32_t t) { return alt && (nsteps - 1 - t) % 2 ? alt : x; };
         for (int32_t t = 0; t < nsteps; ++t) {
             if (t == 0) {
                 double *checkpoint = traj ? traj + n3 : nullptr;
-                st = stored ? launch_kick_drift(n, x, v, acc, 0.5 * dt, dt, s, checkpoint)
+                st = stored ? launch_kick_drift(n, x, at(0), v, acc, 0.5 * dt, dt, s, checkpoint)
                             : launch_kick_drift_centre(n, x, v, acc, 0.5 * dt, dt, checkpoint,
                                                        ws.centre_scratch, s);
                 if (st) return st;
             }
             const bool last = t + 1 == nsteps;
-            const NextDrift next{x, dt, traj && !last ? traj + (size_t)(t + 2) * n3 : nullptr,
+            const NextDrift next{last ? nullptr : at(t + 1), at(t), dt,
+                                 traj && !last ? traj + (size_t)(t + 2) * n3 : nullptr,
                                  ws.centre_scratch};
-            if ((st = force_f64_core(n, x, m, eps, acc, last ? pot : nullptr, o, cfg, ws, v,
+            if ((st = force_f64_core(n, at(t), m, eps, acc, last ? pot : nullptr, o, cfg, ws, v,
                                      0.5 * dt, s, !stored, last ? nullptr : &next)))
                 return st;
         }
@@ -76,13 +80,23 @@ nbody_status enqueue_steps(int64_t n, double *x, double *v, const float *m, floa
         const bool fused = o.centre == NBODY_CENTRE_SYSTEM;
         st = fused ? launch_kick_drift_centre(n, x, v, acc, 0.5 * dt, dt, checkpoint,
                                               ws.centre_scratch, s)
-                   : launch_kick_drift(n, x, v, acc, 0.5 * dt, dt, s, checkpoint);
+                   : launch_kick_drift(n, x, x, v, acc, 0.5 * dt, dt, s, checkpoint);
         if (st) return st;
         if ((st = force_f64_core(n, x, m, eps, acc, t + 1 == nsteps ? pot : nullptr, o, cfg, ws, v,
                                  0.5 * dt, s, fused)))
             return st;
     }
     return NBODY_OK;
+}
+
+// Bytes after the evaluation's scratch for the alternate positions (0: not used).
+size_t alt_bytes(int64_t n, int32_t nsteps, const nbody_opts &o, const TileCfg &cfg) {
+    if (nsteps < 2 || o.centre != NBODY_CENTRE_SYSTEM || !set_shape_f64(cfg, n, o)) return 0;
+    return sizeof(double) * 3 * (size_t)n;
+}
+
+double *alt_at(void *ws, size_t offset, size_t bytes) {
+    return bytes ? reinterpret_cast<double *>(static_cast<char *>(ws) + offset) : nullptr;
 }
 
 }  // namespace
@@ -129,11 +143,15 @@ nbody_status nbody_leapfrog(int64_t n, double *pos64, double *vel64, const float
     hipStream_t s = static_cast<hipStream_t>(stream);
     TileCfg cfg;
     if ((st = choose_cfg(KERNEL_FORCE, n, o.precision, o, &cfg, force_engines(o)))) return st;
+    // The alternate positions only where the caller's workspace holds them as well.
+    const size_t need = f64_scratch_bytes(n, cfg, o.precision);
+    size_t extra = alt_bytes(n, nsteps, o, cfg);
+    if (o.workspace && o.workspace_bytes < need + extra) extra = 0;
     void *ws = nullptr;
-    if ((st = get_workspace(o, f64_scratch_bytes(n, cfg, o.precision), s, &ws))) return st;
+    if ((st = get_workspace(o, need + extra, s, &ws))) return st;
     return enqueue_steps(n, pos64, vel64, mass, eps, dt, nsteps, acc, pot, traj,
                          (flags & NBODY_LF_INIT_ACC) != 0, o, cfg,
-                         f64_scratch_layout(ws, n, cfg, o.precision), s);
+                         f64_scratch_layout(ws, n, cfg, o.precision), alt_at(ws, need, extra), s);
 }
 
 nbody_status nbody_graph_create_leapfrog(int64_t n, double *pos64, double *vel64,
@@ -164,7 +182,9 @@ nbody_status nbody_graph_create_leapfrog(int64_t n, double *pos64, double *vel64
     hipError_t e = hipGetDevice(&g->device);
     if (e != hipSuccess) return fail(hip_error(e, "hipGetDevice"));
     // The graph owns its scratch: a shared cache could be reallocated under it.
-    const size_t need = f64_scratch_bytes(n, cfg, o.precision);
+    const size_t base = f64_scratch_bytes(n, cfg, o.precision);
+    const size_t extra = alt_bytes(n, nsteps, o, cfg);
+    const size_t need = base + extra;
     if ((e = hipMalloc(&g->workspace, need)) != hipSuccess) {
         g->workspace = nullptr;
         return fail(hip_error(e, "hipMalloc(graph workspace)"));
@@ -175,7 +195,7 @@ nbody_status nbody_graph_create_leapfrog(int64_t n, double *pos64, double *vel64
     const F64Scratch lay = f64_scratch_layout(g->workspace, n, cfg, o.precision);
     st = capture_graph(g, [&](hipStream_t cs) {
         return enqueue_steps(n, pos64, vel64, mass, eps, dt, nsteps, acc, pot, nullptr, false, o,
-                             cfg, lay, cs);
+                             cfg, lay, alt_at(g->workspace, base, extra), cs);
     });
     if (st) return fail(st);
     *out = g;

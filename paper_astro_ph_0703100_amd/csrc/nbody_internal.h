@@ -124,6 +124,18 @@ struct PairArgs {
     int npad;
 };
 
+// Arguments of the whole-set force kernel: FP32 positions, or FP64 positions taken relative to
+// their FP64 mean (centred) or as they are.
+struct SetArgs {
+    const float *pos;     // [3][n] or null
+    const double *pos64;  // [3][n] or null
+    const float *m;
+    int n;
+    float eps2;
+    int jt;  // records per tile
+    int centred;
+};
+
 // Arguments of the symmetric pair kernel (each unordered pair once; FP32
 // structure-of-arrays input).  Block rows of bi = 64 W IPL particles; row b's
 // symmetric range is split into segments of segt j-tiles.
@@ -270,8 +282,9 @@ struct FinalizeArgs {
     double *kick_v;    // [3][n]: if not null, v += kick_h * a after a is written
     double kick_h;
     // Leapfrog between two steps: if not null, the next step's first kick (kick_h again) and
-    // drift follow: v += kick_h * a, x += drift_dt * v, and checkpoint = x.
+    // drift follow: v += kick_h * a, x = drift_from + drift_dt * v, and checkpoint = x.
     double *drift_x = nullptr;
+    const double *drift_from = nullptr;
     double drift_dt = 0.0;
     double *checkpoint = nullptr;
 };
@@ -374,10 +387,11 @@ nbody_opts resolve_opts(const nbody_opts *opts);
 nbody_status check_force_f32(int64_t n, const float *pos, const float *mass, float eps,
                              const double *acc, const double *pot, const nbody_opts &o);
 // What follows the second kick when another leapfrog step comes: its first kick and drift
-// (x += dt v, checkpoint = x), and where the centre's first stage over the new x goes if a
-// finalize launch can sum it.
+// (x = from + dt v, checkpoint = x), and where the centre's first stage over the new x goes if
+// a finalize launch can sum it.
 struct NextDrift {
     double *x;
+    const double *from;
     double dt;
     double *checkpoint;
     double *centre_part;
@@ -385,6 +399,18 @@ struct NextDrift {
 
 // The pair launch stores the outputs itself (no finalize launch).
 inline bool stores_outputs(const TileCfg &c) { return c.jl > 1 || (!c.sym && c.wseg == 1); }
+
+// Shapes of the whole-set force kernel (force_set.hip): every record in the LDS of one compute
+// unit, a tile's share of a lane one FP32 block.
+constexpr int64_t kSetMax = 8192;
+inline bool set_shape(const TileCfg &c, int64_t n) {
+    return n <= kSetMax && c.ipl == 1 && (c.jl == 32 || c.jl == 64) && c.jt % (4 * c.jl) == 0 &&
+           c.jt / c.jl <= 128;
+}
+// It takes FP64 positions there with system-wide centre or none.
+inline bool set_shape_f64(const TileCfg &c, int64_t n, const nbody_opts &o) {
+    return set_shape(c, n) && o.centre != NBODY_CENTRE_TILE;
+}
 
 // Pair kernel + FP64 finalize on FP32 positions [3][n] with the partial sums in `ws`
 // (partial_bytes(cfg, o.precision) bytes); with kick_v set, v += kick_h * a follows, and
@@ -440,6 +466,9 @@ nbody_status launch_finalize_step(int precision, const FinalizeArgs &a, double *
 // vjp_split.hip); the finalize arguments say what is stored.
 nbody_status launch_pair_split(const TileCfg &cfg, int precision, bool with_pot,
                                const PairArgs &a, const FinalizeArgs &f, hipStream_t s);
+// Whole-set force kernel (force_set.hip), where set_shape holds: the same in fewer passes.
+nbody_status launch_pair_set(const TileCfg &cfg, int precision, bool with_pot, const SetArgs &a,
+                             const FinalizeArgs &f, hipStream_t s);
 nbody_status launch_vjp_split(const TileCfg &cfg, int precision, const VjpArgs &a, bool with_mass,
                               const VjpFinalizeArgs &f, hipStream_t s);
 // Symmetric engine (cfg.sym): pair kernel and its finalize (force_sym.hip).
@@ -482,9 +511,11 @@ nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, 
                                  hipStream_t s);
 size_t morton_scratch_bytes(int64_t n);
 // Leapfrog pieces (leapfrog.hip).
-// v += h a; x += dt v (and checkpoint = x when checkpoint is not null).
-nbody_status launch_kick_drift(int64_t n, double *x, double *v, const double *acc, double h,
-                               double dt, hipStream_t s, double *checkpoint = nullptr);
+// v += h a; x_out = x + dt v (and checkpoint = x_out when checkpoint is not null); x_out may be
+// x.
+nbody_status launch_kick_drift(int64_t n, const double *x, double *x_out, double *v,
+                               const double *acc, double h, double dt, hipStream_t s,
+                               double *checkpoint = nullptr);
 // The same kick and drift, fused with the first stage of the FP64 centre of the new
 // positions: writes the kCentreBlocks x 3 partials launch_centred_convert computes, in
 // the same order, to `centre_part`.

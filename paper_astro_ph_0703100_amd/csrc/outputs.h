@@ -34,7 +34,7 @@ struct ForceOut {
         double x = 0.0;
         if (a.drift_x) {
             v = v + a.kick_h * r;
-            x = a.drift_x[q] + a.drift_dt * v;
+            x = a.drift_from[q] + a.drift_dt * v;
             a.drift_x[q] = x;
             if (a.checkpoint) a.checkpoint[q] = x;
         }
