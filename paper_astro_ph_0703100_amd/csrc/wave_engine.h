@@ -31,6 +31,14 @@ constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
 // interleaved pairs take too many registers), so it has no such variant.
 constexpr int64_t kLoneWaves = 1024;
 
+// Waves up to which those of a PLAIN launch should end together (6 per SIMD, all there at
+// once, with chains of 256 to 512 pairs): N = 6000 / 8000 / 9000, force-jerk 37.3 / 48.8 /
+// 57.7 -> 34.8 / 44.6 / 54.3 us; force, N = 8192 / 9000, 31.4 / 33.9 -> 28.4 / 31.2 us.
+// Nothing is gained with 6300 (N = 10007: 40.5 -> 42.5 us without the potential), and where
+// waves follow each other priorities only disturb their order (N = 20011: 124 -> 132 us), as
+// with the short chains of the other modes (16384 of 131072 particles: 591 -> 599 us).
+constexpr int kRound = 6144;
+
 // Bytes of LDS of a block of `waves` waves: staging, then the cross-wave sums.
 template <class Op>
 constexpr size_t lds_bytes(int waves) {
@@ -138,10 +146,24 @@ __device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
     }
 }
 
+// The less of a wave's work is done, the higher its priority.  Left to themselves the oldest
+// waves of a SIMD finish first and the last one runs alone, at half the rate; that counts
+// where no others take their places.
+__device__ __forceinline__ void priority_by_rest(int t, int all) {
+    if (4 * t < all)
+        __builtin_amdgcn_s_setprio(3);
+    else if (2 * t < all)
+        __builtin_amdgcn_s_setprio(2);
+    else if (4 * t < 3 * all)
+        __builtin_amdgcn_s_setprio(1);
+    else
+        __builtin_amdgcn_s_setprio(0);
+}
+
 // One wave's work: its 64 * IPL i-particles from i0 (ni of them exist) against the
 // j-range [j0, j0 + nj), in FP32 blocks of BJ from j0 on.  All arguments are uniform.
-// Sums: FP64RED ds, COMP hs and ls, PLAIN hs.
-template <class Op, int IPL, int BJ, int MODE, bool FULL, bool LONE = false>
+// Sums: FP64RED ds, COMP hs and ls, PLAIN hs.  EVEN: waves of a SIMD should end together.
+template <class Op, int IPL, int BJ, int MODE, bool FULL, bool LONE = false, bool EVEN = false>
 __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl, int i0, int ni,
                                           int j0, int nj, float eps2,
                                           float (&hs)[IPL][Op::kOut], float (&ls)[IPL][Op::kOut],
@@ -182,6 +204,7 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
     const int stages = (nj + kStage - 1) / kStage;
     if (stages > 0) fetch(0);
     for (int t0 = 0; t0 < stages; t0 += PER) {
+        if constexpr (EVEN) priority_by_rest(t0, stages);
         float bs[IPL][NO];
         if constexpr (MODE != NBODY_PLAIN)
 #pragma unroll
@@ -343,7 +366,10 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
     float hs[IPL][NO], ls[IPL][NO];
     double ds[IPL][NO];
     if constexpr (MODE == NBODY_PLAIN) {
-        wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
+        if ((int)(gridDim.x * gridDim.y) * waves <= kRound)
+            wave_work<Op, IPL, BJ, MODE, FULL, LONE, true>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
+        else
+            wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
         store_plain<Sink, IPL, FULL>(f, i0, n, hs, nseg == 1, part, plane, (size_t)i0);
     } else {
         const Run r = block_run<BJ>(nj, wave, waves);
