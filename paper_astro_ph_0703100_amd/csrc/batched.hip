@@ -37,7 +37,7 @@ __global__ __launch_bounds__(1024) void batched_pair_kernel(PairArgs a, Finalize
         wave::store_plain<ForceOut, IPL, FULL>(f, it.i0, it.i0 + it.ni, hs, it.whole, part,
                                                (size_t)it.npad, (size_t)it.col0);
     } else {
-        const wave::Run r = wave::block_run<BJ>(it.nj, wave, waves);
+        const wave::Range r = wave::block_run<BJ>(it.nj, wave, waves);
         wave::wave_work<Gravity, IPL, BJ, MODE, FULL>(a, tl, it.i0, it.ni, it.j0 + r.j0, r.nj, eps2,
                                                       hs, ls, ds);
         wave::store_sums<ForceOut, IPL, MODE, FULL>(f, reinterpret_cast<double *>(lds), wave,

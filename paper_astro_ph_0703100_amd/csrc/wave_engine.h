@@ -24,20 +24,24 @@ namespace nbody {
 namespace wave {
 
 constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
-// Waves up to which a launch counts as few (LONE, pipelines with Op::kLone): one per SIMD.
+// Waves up to which a launch counts as few (kLone, pipelines with Op::kLone): one per SIMD.
 // One launch of the force on N = 1000 / 2000 / 3000 particles (0.1 / 0.5 / 1.1 waves per
 // SIMD): 6.9 / 7.1 / 8.8 us against 7.4 / 7.6 / 8.6 us; PLAIN, 431 particles against 3452:
 // 10.5 against 11.6 us.  The force-jerk gains under 3 % there and loses 20 % at 1.1 (its
 // interleaved pairs take too many registers), so it has no such variant.
 constexpr int64_t kLoneWaves = 1024;
 
-// Waves up to which those of a PLAIN launch should end together (6 per SIMD, all there at
-// once, with chains of 256 to 512 pairs): N = 6000 / 8000 / 9000, force-jerk 37.3 / 48.8 /
-// 57.7 -> 34.8 / 44.6 / 54.3 us; force, N = 8192 / 9000, 31.4 / 33.9 -> 28.4 / 31.2 us.
-// Nothing is gained with 6300 (N = 10007: 40.5 -> 42.5 us without the potential), and where
-// waves follow each other priorities only disturb their order (N = 20011: 124 -> 132 us), as
-// with the short chains of the other modes (16384 of 131072 particles: 591 -> 599 us).
-constexpr int kRound = 6144;
+// Above that and up to this many (5 per SIMD, all there at once, with chains of 128 to 512
+// pairs), the waves of a launch should end together (kEven, one record per lane).  N = 4099 /
+// 5000 / 8192 / 9000 / 10007, with the finalize: force-jerk 22.7 / 27.5 / 47.4 / 54.0 / 69.3
+// -> 21.7 / 26.0 / 42.8 / 51.3 / 67.9 us, adjoint 26.3 / 31.2 / 52.2 / 63.0 / 81.3 -> 25.0 /
+// 29.4 / 48.8 / 58.9 / 78.8 us; force, N = 8192 / 9000, 26.9 / 32.0 -> 24.4 / 29.6 us; PLAIN,
+// N = 6000 / 8000 / 9000, force-jerk 37.3 / 48.8 / 57.7 -> 34.8 / 44.6 / 54.3 us.  With 6 per
+// SIMD nothing is gained (N = 7000: 41.2 -> 41.0) or lost (N = 12000: 92 -> 96 us), under one
+// it costs 2 % (N = 2100), and where waves follow each other priorities only disturb their
+// order (PLAIN force, N = 20011: 124 -> 132 us).
+constexpr int64_t kEvenWaves = 5120;
+enum Run { kMany, kLone, kEven };
 
 // Bytes of LDS of a block of `waves` waves: staging, then the cross-wave sums.
 template <class Op>
@@ -162,8 +166,8 @@ __device__ __forceinline__ void priority_by_rest(int t, int all) {
 
 // One wave's work: its 64 * IPL i-particles from i0 (ni of them exist) against the
 // j-range [j0, j0 + nj), in FP32 blocks of BJ from j0 on.  All arguments are uniform.
-// Sums: FP64RED ds, COMP hs and ls, PLAIN hs.  EVEN: waves of a SIMD should end together.
-template <class Op, int IPL, int BJ, int MODE, bool FULL, bool LONE = false, bool EVEN = false>
+// Sums: FP64RED ds, COMP hs and ls, PLAIN hs.
+template <class Op, int IPL, int BJ, int MODE, bool FULL, Run RUN = kMany>
 __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl, int i0, int ni,
                                           int j0, int nj, float eps2,
                                           float (&hs)[IPL][Op::kOut], float (&ls)[IPL][Op::kOut],
@@ -204,7 +208,6 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
     const int stages = (nj + kStage - 1) / kStage;
     if (stages > 0) fetch(0);
     for (int t0 = 0; t0 < stages; t0 += PER) {
-        if constexpr (EVEN) priority_by_rest(t0, stages);
         float bs[IPL][NO];
         if constexpr (MODE != NBODY_PLAIN)
 #pragma unroll
@@ -214,6 +217,7 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
         const int t1 = min(t0 + PER, stages);
 #pragma unroll 1
         for (int t = t0; t < t1; ++t) {
+            if constexpr (RUN == kEven) priority_by_rest(t, stages);
             // LDS serves a wave's accesses in order, so the slice can be rewritten as soon
             // as its last reads are issued; the fences keep the compiler to that order.
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -229,7 +233,7 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
             auto pass = [&](auto self) {
                 constexpr bool SELF = decltype(self)::value;
                 auto run = [&](float(&acc)[IPL][NO]) {
-                    if constexpr (LONE)
+                    if constexpr (RUN == kLone)
                         lone_pass<Op, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
                     else
                         stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
@@ -263,11 +267,11 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
 }
 
 // Wave `wave`'s contiguous run of the FP32 blocks of a segment of snj j's.
-struct Run {
+struct Range {
     int j0, nj;
 };
 template <int BJ>
-__device__ __forceinline__ Run block_run(int snj, int wave, int waves) {
+__device__ __forceinline__ Range block_run(int snj, int wave, int waves) {
     const int nb = (snj + BJ - 1) / BJ;
     const int b0 = nb * wave / waves * BJ;
     return {b0, max(0, min(nb * (wave + 1) / waves * BJ, snj) - b0)};
@@ -341,9 +345,9 @@ __device__ __forceinline__ void store_sums(const typename Sink::Args &f, double 
 
 // Grid launch: blockIdx.x = group of 64 * IPL i's, blockIdx.y = j-segment of a.seg_len
 // j's (PLAIN: one segment per wave, blockDim.x / 64 of them per block).  Partial planes
-// [segment][word][npad], or, with nseg = 1, the outputs through the Sink.  LONE: for launches
-// of few waves.
-template <class Op, class Sink, int IPL, int BJ, int MODE, bool FULL, bool LONE>
+// [segment][word][npad], or, with nseg = 1, the outputs through the Sink.  RUN: for launches
+// of so many waves.
+template <class Op, class Sink, int IPL, int BJ, int MODE, bool FULL, Run RUN>
 __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typename Sink::Args f,
                                                     int nseg) {
     constexpr int NO = Op::kOut;
@@ -366,14 +370,11 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
     float hs[IPL][NO], ls[IPL][NO];
     double ds[IPL][NO];
     if constexpr (MODE == NBODY_PLAIN) {
-        if ((int)(gridDim.x * gridDim.y) * waves <= kRound)
-            wave_work<Op, IPL, BJ, MODE, FULL, LONE, true>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
-        else
-            wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
+        wave_work<Op, IPL, BJ, MODE, FULL, RUN>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
         store_plain<Sink, IPL, FULL>(f, i0, n, hs, nseg == 1, part, plane, (size_t)i0);
     } else {
-        const Run r = block_run<BJ>(nj, wave, waves);
-        wave_work<Op, IPL, BJ, MODE, FULL, LONE>(a, tl, i0, ni, j0 + r.j0, r.nj, a.eps2, hs, ls, ds);
+        const Range r = block_run<BJ>(nj, wave, waves);
+        wave_work<Op, IPL, BJ, MODE, FULL, RUN>(a, tl, i0, ni, j0 + r.j0, r.nj, a.eps2, hs, ls, ds);
         store_sums<Sink, IPL, MODE, FULL>(f, reinterpret_cast<double *>(lds), wave, waves, i0, n,
                                           hs, ls, ds, nseg == 1, part, plane, (size_t)i0);
     }
@@ -384,39 +385,40 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
 template <class Op, class Sink>
 using WaveFn = void (*)(typename Op::Args, typename Sink::Args, int);
 
-template <class Op, class Sink, int IPL, bool LONE = false>
+template <class Op, class Sink, int IPL, Run RUN>
 WaveFn<Op, Sink> pick_mode(int bj, int mode, bool full) {
     switch (mode) {
         case NBODY_PLAIN:
-            return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, true, LONE>
-                        : wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, false, LONE>;
+            return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, true, RUN>
+                        : wave_kernel<Op, Sink, IPL, 64, NBODY_PLAIN, false, RUN>;
         case NBODY_FP64RED:
             if (bj == 64)
-                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, true, LONE>
-                            : wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, false, LONE>;
-            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, true, LONE>
-                        : wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, false, LONE>;
+                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, true, RUN>
+                            : wave_kernel<Op, Sink, IPL, 64, NBODY_FP64RED, false, RUN>;
+            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, true, RUN>
+                        : wave_kernel<Op, Sink, IPL, 128, NBODY_FP64RED, false, RUN>;
         case NBODY_COMP:
             if (bj == 64)
-                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, true, LONE>
-                            : wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, false, LONE>;
-            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, true, LONE>
-                        : wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, false, LONE>;
+                return full ? wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, true, RUN>
+                            : wave_kernel<Op, Sink, IPL, 64, NBODY_COMP, false, RUN>;
+            return full ? wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, true, RUN>
+                        : wave_kernel<Op, Sink, IPL, 128, NBODY_COMP, false, RUN>;
     }
     return nullptr;
 }
 
 template <class Op, class Sink>
-WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full, bool lone) {
+WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full, Run run) {
     static_assert(Op::kBlockJ == 128, "FP32 blocks of 64 or 128 j's");
     switch (ipl) {
         case 1:
             if constexpr (Op::kLone)
-                if (lone) return pick_mode<Op, Sink, 1, true>(bj, mode, full);
-            return pick_mode<Op, Sink, 1>(bj, mode, full);
-        case 2: return pick_mode<Op, Sink, 2>(bj, mode, full);
+                if (run == kLone) return pick_mode<Op, Sink, 1, kLone>(bj, mode, full);
+            return run == kEven ? pick_mode<Op, Sink, 1, kEven>(bj, mode, full)
+                                : pick_mode<Op, Sink, 1, kMany>(bj, mode, full);
+        case 2: return pick_mode<Op, Sink, 2, kMany>(bj, mode, full);
         case 4:
-            if constexpr (Op::kMaxIpl >= 4) return pick_mode<Op, Sink, 4>(bj, mode, full);
+            if constexpr (Op::kMaxIpl >= 4) return pick_mode<Op, Sink, 4, kMany>(bj, mode, full);
     }
     return nullptr;
 }
@@ -428,7 +430,10 @@ nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
                     const typename Op::Args &a, const typename Sink::Args &f, hipStream_t s) {
     const int64_t groups = (ni + 64 * cfg.wi - 1) / (64 * cfg.wi);
     const int64_t waves = groups * cfg.wseg * (precision == NBODY_PLAIN ? 1 : cfg.wpb);
-    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full, waves <= kLoneWaves);
+    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full,
+                                  waves <= kLoneWaves   ? kLone
+                                  : waves <= kEvenWaves ? kEven
+                                                        : kMany);
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no pair kernel for this ipl/jtile/precision");
     if (ni <= 0 || cfg.wseg <= 0) return NBODY_OK;
     const int per_block = precision == NBODY_PLAIN ? cfg.wpb : 1;  // segments per block

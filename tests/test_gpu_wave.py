@@ -132,3 +132,20 @@ def test_jerk_and_adjoint_splits_agree(n):
                         api.force_jerk(p, v, mm, EPS, **kw)
                         + api.force_jerk_ij(pi, vi, p, v, mm, EPS, **kw) + vjp(**kw)):
             assert float((a - b).abs().max()) <= 1e-11 * max(float(a.abs().max()), 1e-300)
+
+
+@pytest.mark.parametrize("precision", ["comp", "plain"])
+@pytest.mark.parametrize("n", [3000, 4099, 9000])
+def test_waves_that_end_together(precision, n):
+    # One to five waves per SIMD: only priorities differ from a launch of more waves (segments
+    # asked for), so the sums differ by the rounding of FP64 (PLAIN: of 2 against ceil(n / 256)
+    # FP32 segments, at most n 2^-24 of the sum of magnitudes).
+    x, m = sphere(n, 6)
+    v = np.ascontiguousarray(x[::-1])
+    p, w, mm = (torch.from_numpy(t).to(DEV) for t in (x, v, m))
+    one = api.force_jerk(p, w, mm, EPS, precision=precision)
+    two = api.force_jerk(p, w, mm, EPS, precision=precision, ipl=2, jtile=128,
+                         nseg=2 if precision == "plain" else 64)
+    tol = 1e-11 if precision == "comp" else n * 2.0 ** -24
+    for a, b in zip(one, two):
+        assert float((a - b).abs().max() / a.abs().max()) < tol
