@@ -8,6 +8,7 @@
 //     segment partials (no j == i term: the pair kernel left it out) and the kick;
 //   * per-system FP64 centres (one block per system, fixed-order reduction) and the
 //     conversion of FP64 positions to FP32 relative to them.
+#include "centre_sum.h"
 #include "gravity.h"
 #include "outputs.h"
 #include "wave_engine.h"
@@ -79,16 +80,9 @@ __global__ __launch_bounds__(256) void system_centre_kernel(const int64_t *offse
     for (int64_t p = b + threadIdx.x; p < e; p += 256)
 #pragma unroll
         for (int c = 0; c < 3; ++c) s[c] += pos[c * total + p];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) centre[3 * k + threadIdx.x] = e > b ? sh[threadIdx.x][0] / (double)(e - b) : 0.0;
+    const double sum = centre::block_sum(s, sh);
+    const int c = threadIdx.x >> 6;
+    if (c < 3 && threadIdx.x % 64 == 0) centre[3 * k + c] = e > b ? sum / (double)(e - b) : 0.0;
 }
 
 // One block per system: the leapfrog's first kick and drift (v not null), the FP64 centre in
@@ -112,15 +106,10 @@ __global__ __launch_bounds__(256) void system_step_kernel(const int64_t *offsets
             }
             s[c] += xx;
         }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
+    const double sum = centre::block_sum(s, sh);
+    const int wave = threadIdx.x >> 6;
+    if (wave < 3 && threadIdx.x % 64 == 0) sh[wave][0] = sum;  // wave c alone reads sh[c] before
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
     for (int64_t p = b + threadIdx.x; p < e; p += 256)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {

@@ -47,6 +47,37 @@ __device__ __forceinline__ double wave_sum(const double (&v)[4]) {
     return tree_step<1>(s);
 }
 
+// The tree sums of a block's 256 threads, NC values each (all threads must call it): wave c
+// adds value c and returns the sum in its lane 0.  One barrier instead of one per distance,
+// and the second stage without any: 8 Hermite steps of 4099 particles (a finalize with two
+// first stages and a conversion with the second, each) 211 -> 202 us, a force from 10007 FP64
+// positions 43.1 -> 42.4 us.
+template <int NC>
+__device__ __forceinline__ double block_sum(const double (&s)[NC], double (&sh)[NC][256]) {
+    static_assert(NC <= 4, "a wave per value");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sh[c][threadIdx.x] = s[c];
+    __syncthreads();
+    if (wave >= NC) return 0.0;
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = sh[wave][k * 64 + lane];
+    return wave_sum(v);
+}
+
+// Second stage over the kCentreBlocks partials [block][3] of the first, component c; every
+// lane of the wave returns it.
+__device__ __forceinline__ double partials_sum(const double *part, int c) {
+    static_assert(kCentreBlocks == 256, "four partials per lane");
+    const int lane = threadIdx.x & 63;
+    double v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = part[(k * 64 + lane) * 3 + c];
+    return __shfl(wave_sum(v), 0);
+}
+
 // Second stage over sh[0 .. chunks), chunks <= 32 (the other blocks hold zeros: the tree's
 // distances above 16 add nothing); every lane returns it.
 __device__ __forceinline__ double second_stage(const double *sh, int chunks, int lane) {

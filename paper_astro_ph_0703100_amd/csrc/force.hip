@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void finalize_kernel(FinalizeArgs a) {
 // Grid: (kCentreBlocks, 3).
 template <int MODE, int BATCH>
 __global__ __launch_bounds__(256) void finalize_step_kernel(FinalizeArgs a, double *centre_part) {
-    __shared__ double sh[256];
+    __shared__ double sh[1][256];
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int c = blockIdx.y;
     double x = 0.0;
@@ -38,7 +38,8 @@ __global__ __launch_bounds__(256) void finalize_step_kernel(FinalizeArgs a, doub
         x = ForceOut::store(a, (size_t)c * a.n + i,
                             engine::sum_partial_output<kForceOutputs, MODE, BATCH>(
                                 a.part, a.nseg, (size_t)a.npad, i, c));
-    engine::tree_sum_256(x, sh, centre_part + 3 * blockIdx.x + c);
+    const double sum = centre::block_sum<1>({x}, sh);
+    if (threadIdx.x == 0) centre_part[3 * blockIdx.x + c] = sum;
 }
 
 // Two-stage fixed-order FP64 mean of the positions [3][n]: kCentreBlocks partial
@@ -51,37 +52,30 @@ __global__ __launch_bounds__(256) void centre_partial_kernel(int64_t n, const do
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
 #pragma unroll
         for (int c = 0; c < 3; ++c) s[c] += pos[c * n + i];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = sh[threadIdx.x][0];
+    const double sum = centre::block_sum(s, sh);
+    const int c = threadIdx.x >> 6;
+    if (c < 3 && threadIdx.x % 64 == 0) part[blockIdx.x * 3 + c] = sum;
 }
 
-// The second stage fused with the conversion to FP32: every block adds the
-// kCentreBlocks partials in the same fixed tree order, so all blocks use the identical
-// centre c = sum / n, then converts its 256 particles to fp32(x - c).
+// The second stage fused with the conversion to FP32: every wave adds the kCentreBlocks
+// partials in the same fixed tree order, so all use the identical centre c = sum / n, then
+// converts its 64 particles to fp32(x - c).
+__device__ __forceinline__ void convert_centred(int64_t n, const double *pos, const double *part,
+                                                float *out) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    double x[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) x[c] = i < n ? pos[c * n + i] : 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const double mean = centre::partials_sum(part, c) / (double)n;
+        if (i < n) out[c * n + i] = (float)(x[c] - mean);
+    }
+}
+
 __global__ __launch_bounds__(256) void centred_convert_kernel(int64_t n, const double *pos,
                                                              const double *part, float *out) {
-    __shared__ double sh[3][kCentreBlocks];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = part[threadIdx.x * 3 + c];
-    __syncthreads();
-    for (int w = kCentreBlocks / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c * n + i] = (float)(pos[c * n + i] - sh[c][0] / (double)n);
+    convert_centred(n, pos, part, out);
 }
 
 // The second stage and conversion of two arrays (blockIdx.y).
@@ -89,23 +83,10 @@ __global__ __launch_bounds__(256) void centred_convert2_kernel(int64_t n, const 
                                                               const double *a_part, float *a_out,
                                                               const double *b,
                                                               const double *b_part, float *b_out) {
-    __shared__ double sh[3][kCentreBlocks];
     const double *pos = blockIdx.y ? b : a;
     const double *part = blockIdx.y ? b_part : a_part;
     float *out = blockIdx.y ? b_out : a_out;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = part[threadIdx.x * 3 + c];
-    __syncthreads();
-    for (int w = kCentreBlocks / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) out[c * n + i] = (float)(pos[c * n + i] - sh[c][0] / (double)n);
+    convert_centred(n, pos, part, out);
 }
 
 // Centre and conversion in one launch, for few particles (kSelfCentre): each block adds the
@@ -173,16 +154,9 @@ __global__ __launch_bounds__(256) void tile_centre_kernel(int64_t n, int itile, 
     for (int64_t p = b + threadIdx.x; p < e; p += 256)
 #pragma unroll
         for (int c = 0; c < 3; ++c) s[c] += pos[c * n + p];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) centres[3 * blockIdx.x + threadIdx.x] = sh[threadIdx.x][0] / (double)(e - b);
+    const double sum = centre::block_sum(s, sh);
+    const int c = threadIdx.x >> 6;
+    if (c < 3 && threadIdx.x % 64 == 0) centres[3 * blockIdx.x + c] = sum / (double)(e - b);
 }
 
 }  // namespace

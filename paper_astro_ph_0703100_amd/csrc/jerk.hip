@@ -1,5 +1,6 @@
 // Launch of the force-jerk-potential pipeline on FP32 inputs and the FP64 finalize of
 // its partial sums (shared by every force-jerk path).
+#include "centre_sum.h"
 #include "jerk_pipeline.h"
 #include "outputs.h"
 #include "wave_engine.h"
@@ -26,7 +27,7 @@ __global__ __launch_bounds__(256) void jerk_finalize_kernel(JerkFinalizeArgs a) 
 template <int MODE, int BATCH>
 __global__ __launch_bounds__(256) void jerk_finalize_step_kernel(JerkFinalizeArgs a, double *x_part,
                                                                 double *v_part) {
-    __shared__ double sh[256];
+    __shared__ double sh[2][256];
     const int i = blockIdx.x * 256 + threadIdx.x;
     const int c = blockIdx.y;
     double2 p = make_double2(0.0, 0.0);
@@ -38,9 +39,9 @@ __global__ __launch_bounds__(256) void jerk_finalize_step_kernel(JerkFinalizeArg
         p = JerkOut::step(a, (size_t)c * a.n + i, sum(c), sum(c + 3));
     }
     if (!x_part) return;
-    engine::tree_sum_256(p.x, sh, x_part + 3 * blockIdx.x + c);
-    __syncthreads();
-    engine::tree_sum_256(p.y, sh, v_part + 3 * blockIdx.x + c);
+    const double sum = centre::block_sum<2>({p.x, p.y}, sh);
+    if (threadIdx.x == 0) x_part[3 * blockIdx.x + c] = sum;
+    if (threadIdx.x == 64) v_part[3 * blockIdx.x + c] = sum;
 }
 
 }  // namespace

@@ -1,6 +1,6 @@
 // FP64 element-wise kernels of the kick-drift-kick leapfrog.  The state is
 // structure-of-arrays [3][n] doubles; one lane per element of the 3n-vector.
-#include "nbody_internal.h"
+#include "centre_sum.h"
 
 namespace nbody {
 namespace {
@@ -40,16 +40,9 @@ __global__ __launch_bounds__(256) void kick_drift_centre_kernel(
             if (checkpoint) checkpoint[q] = xx;
             s[c] += xx;
         }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = sh[threadIdx.x][0];
+    const double sum = centre::block_sum(s, sh);
+    const int c = threadIdx.x >> 6;
+    if (c < 3 && threadIdx.x % 64 == 0) part[blockIdx.x * 3 + c] = sum;
 }
 
 __global__ __launch_bounds__(256) void kick_kernel(int64_t count, double *__restrict__ v,
@@ -109,16 +102,9 @@ __global__ __launch_bounds__(256) void adj_drift_kick_centre_kernel(
             abar[q] = h * vb;
             s[c] += next[q];
         }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] = s[c];
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sh[c][threadIdx.x] += sh[c][threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) part[blockIdx.x * 3 + threadIdx.x] = sh[threadIdx.x][0];
+    const double sum = centre::block_sum(s, sh);
+    const int c = threadIdx.x >> 6;
+    if (c < 3 && threadIdx.x % 64 == 0) part[blockIdx.x * 3 + c] = sum;
 }
 
 dim3 grid_for(int64_t count) { return dim3((unsigned)((count + 255) / 256)); }

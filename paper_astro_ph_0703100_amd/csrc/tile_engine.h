@@ -259,18 +259,5 @@ __device__ __forceinline__ void sum_partials(const void *part, int nseg, size_t 
     for (int c = 0; c < NO; ++c) r[c] = (double)acc[c];
 }
 
-// The block's 256 values added by the tree of the centre's first stage (every kernel that
-// sums a centre uses this order); thread 0 writes the sum.
-__device__ __forceinline__ void tree_sum_256(double v, double *sh, double *out) {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) sh[t] += sh[t + w];
-        __syncthreads();
-    }
-    if (t == 0) *out = sh[0];
-}
-
 }  // namespace engine
 }  // namespace nbody

@@ -1,6 +1,7 @@
 // Launch of the adjoint pipeline on FP32 positions and the FP64 finalize of its
 // partial sums.
 #include "adjoint_pipeline.h"
+#include "centre_sum.h"
 #include "outputs.h"
 #include "wave_engine.h"
 
@@ -28,7 +29,7 @@ template <int MODE, int BATCH>
 __global__ __launch_bounds__(256) void vjp_finalize_step_kernel(VjpFinalizeArgs a,
                                                                const double *next,
                                                                double *centre_part) {
-    __shared__ double sh[256];
+    __shared__ double sh[1][256];
     const int k = blockIdx.x * 256 + threadIdx.x;
     const int c = blockIdx.y;
     if (k < a.n)
@@ -36,9 +37,10 @@ __global__ __launch_bounds__(256) void vjp_finalize_step_kernel(VjpFinalizeArgs 
             return engine::sum_partial_output<kVjpOutputs, MODE, BATCH>(a.part, a.nseg,
                                                                         (size_t)a.npad, k, o);
         });
-    if (c < 3)
-        engine::tree_sum_256(k < a.n ? next[(size_t)c * a.n + k] : 0.0, sh,
-                             centre_part + 3 * blockIdx.x + c);
+    if (c < 3) {
+        const double sum = centre::block_sum<1>({k < a.n ? next[(size_t)c * a.n + k] : 0.0}, sh);
+        if (threadIdx.x == 0) centre_part[3 * blockIdx.x + c] = sum;
+    }
 }
 
 }  // namespace
