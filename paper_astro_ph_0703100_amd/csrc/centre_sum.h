@@ -9,9 +9,13 @@
 namespace nbody {
 namespace centre {
 
-// v + (value of lane + W, for the lanes below W), the tree step of distance W inside a wave.
-template <int W>
-__device__ __forceinline__ double tree_step(double v) {
+struct Plus {
+    __device__ double operator()(double a, double b) const { return a + b; }
+};
+
+// op(v, value of lane + W), for the lanes below W: the tree step of distance W inside a wave.
+template <int W, class Op = Plus>
+__device__ __forceinline__ double tree_step(double v, Op op = Op()) {
     const long long b = __double_as_longlong(v);
     const int lo = (int)b, hi = (int)(b >> 32);
     auto join = [](int l, int h) {
@@ -20,32 +24,36 @@ __device__ __forceinline__ double tree_step(double v) {
     if constexpr (W == 32) {
         const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
         const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-        return join(l[0], h[0]) + join(l[1], h[1]);
+        return op(join(l[0], h[0]), join(l[1], h[1]));
     } else if constexpr (W == 16) {
         const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
         const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        return join(l[0], h[0]) + join(l[1], h[1]);
+        return op(join(l[0], h[0]), join(l[1], h[1]));
     } else {
         constexpr int kCtrl = W == 8 ? 0x128 :  // row_ror 8
                               W == 4 ? 0x12C :  // row_ror 12: lane l receives lane l + 4
                               W == 2 ? 0x4E :   // quad_perm [2, 3, 0, 1]
                                        0xB1;    // quad_perm [1, 0, 3, 2]
-        return v + join(__builtin_amdgcn_mov_dpp(lo, kCtrl, 0xF, 0xF, false),
-                        __builtin_amdgcn_mov_dpp(hi, kCtrl, 0xF, 0xF, false));
+        return op(v, join(__builtin_amdgcn_mov_dpp(lo, kCtrl, 0xF, 0xF, false),
+                          __builtin_amdgcn_mov_dpp(hi, kCtrl, 0xF, 0xF, false)));
     }
 }
 
-// First stage: the tree sum of a block whose threads l, l + 64, l + 128 and l + 192 hold
-// lane l's four values; lane 0 returns it.
-__device__ __forceinline__ double wave_sum(const double (&v)[4]) {
-    double s = (v[0] + v[2]) + (v[1] + v[3]);  // distances 128 and 64
-    s = tree_step<32>(s);
-    s = tree_step<16>(s);
-    s = tree_step<8>(s);
-    s = tree_step<4>(s);
-    s = tree_step<2>(s);
-    return tree_step<1>(s);
+// The tree over 256 values, lane l holding those of threads l, l + 64, l + 128 and l + 192;
+// lane 0 returns the result.
+template <class Op>
+__device__ __forceinline__ double wave_tree(const double (&v)[4], Op op) {
+    double s = op(op(v[0], v[2]), op(v[1], v[3]));  // distances 128 and 64
+    s = tree_step<32>(s, op);
+    s = tree_step<16>(s, op);
+    s = tree_step<8>(s, op);
+    s = tree_step<4>(s, op);
+    s = tree_step<2>(s, op);
+    return tree_step<1>(s, op);
 }
+
+// First stage: the tree sum of a block; lane 0 returns it.
+__device__ __forceinline__ double wave_sum(const double (&v)[4]) { return wave_tree(v, Plus()); }
 
 // The tree sums of a block's 256 threads, NC values each (all threads must call it): wave c
 // adds value c and returns the sum in its lane 0.  One barrier instead of one per distance,

@@ -15,17 +15,20 @@
 //     puts them in that order in LDS and writes each digit's run contiguously.
 //
 // Bound: 16 bytes read and written per word and pass, 6 passes of 7 bits at 2^20
-// particles, but at that size the launches cost more than the traffic.  2^20 particles:
-// see the design notes for the times; the bitonic network in global memory this replaced
-// took 210 launches.
+// particles, but at that size each launch takes longer to start and to fill than its traffic.
+// 2^20 particles: 112 us in 19 launches, 779 us in the 210 launches of a bitonic network in
+// global memory.  Prefix sums and the final box run inside waves and the counts are plain
+// additions: with 8 and 9 block-wide steps for the former and ballots for the latter 139 us.
 #include <utility>
 
+#include "centre_sum.h"
 #include "nbody_internal.h"
 
 namespace nbody {
 namespace {
 
-constexpr int kBoxBlocks = 256;
+constexpr int kBoxBlocks = 256;  // one slot of the final reduction each
+constexpr int kBoxThreads = 512;
 constexpr int kSmall = 8192;       // words one block sorts in LDS (64 KB)
 constexpr int kSmallThreads = 1024;
 constexpr int kTile = 4096;        // words per block of the radix passes
@@ -55,6 +58,7 @@ __device__ __forceinline__ void thread_box(int64_t n, const double *pos, int64_t
                                            int64_t stride, double (*lo)[THREADS],
                                            double (*hi)[THREADS]) {
     double l[3] = {INFINITY, INFINITY, INFINITY}, h[3] = {-INFINITY, -INFINITY, -INFINITY};
+#pragma unroll 4
     for (int64_t i = first; i < n; i += stride)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -69,10 +73,35 @@ __device__ __forceinline__ void thread_box(int64_t n, const double *pos, int64_t
     }
 }
 
-__global__ __launch_bounds__(256) void box_partial_kernel(int64_t n, const double *pos, double *part) {
-    __shared__ double lo[3][256], hi[3][256];
-    thread_box<256>(n, pos, (int64_t)blockIdx.x * 256 + threadIdx.x, (int64_t)gridDim.x * 256, lo, hi);
-    reduce_box<256>(lo, hi);
+struct Lowest {
+    __device__ double operator()(double a, double b) const { return fmin(a, b); }
+};
+struct Highest {
+    __device__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+
+// Six values of each of 256 slots, v[6 slot + c], reduced by one wave: lowest for c < 3,
+// highest above; lane 0 returns them.
+__device__ __forceinline__ void wave_box(const double *v, double (&l)[3], double (&h)[3]) {
+    const int lane = threadIdx.x & 63;
+    double x[6][4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) x[c][k] = v[6 * (k * 64 + lane) + c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        l[c] = centre::wave_tree(x[c], Lowest());
+        h[c] = centre::wave_tree(x[c + 3], Highest());
+    }
+}
+
+__global__ __launch_bounds__(kBoxThreads) void box_partial_kernel(int64_t n, const double *pos,
+                                                                 double *part) {
+    __shared__ double lo[3][kBoxThreads], hi[3][kBoxThreads];
+    thread_box<kBoxThreads>(n, pos, (int64_t)blockIdx.x * kBoxThreads + threadIdx.x,
+                            (int64_t)gridDim.x * kBoxThreads, lo, hi);
+    reduce_box<kBoxThreads>(lo, hi);
     if (threadIdx.x < 3) {
         part[6 * blockIdx.x + threadIdx.x] = lo[threadIdx.x][0];
         part[6 * blockIdx.x + 3 + threadIdx.x] = hi[threadIdx.x][0];
@@ -93,7 +122,7 @@ __device__ __forceinline__ uint64_t spread3(uint64_t v) {
 
 // Word of particle i: coordinates quantised to qbits in the box, interleaved, then the
 // index in ibits.
-__device__ __forceinline__ uint64_t particle_word(int64_t n, int64_t i, const double *pos,
+__device__ __forceinline__ uint64_t particle_word(int64_t i, const double (&x)[3],
                                                   const double (&lo)[3], const double (&hi)[3],
                                                   int qbits, int ibits) {
     const uint64_t low = (1ull << qbits) - 1;
@@ -102,7 +131,7 @@ __device__ __forceinline__ uint64_t particle_word(int64_t n, int64_t i, const do
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const double span = hi[c] - lo[c];
-        double q = span > 0.0 ? (pos[c * n + i] - lo[c]) / span * top : 0.0;
+        double q = span > 0.0 ? (x[c] - lo[c]) / span * top : 0.0;
         q = q < 0.0 ? 0.0 : (q > top ? top : q);
         key |= spread3((uint64_t)q & low) << (2 - c);
     }
@@ -126,8 +155,14 @@ __global__ __launch_bounds__(kSmallThreads) void small_kernel(int n, int npow, c
         h[c] = hi[c][0];
     }
     __syncthreads();
-    for (int i = t; i < npow; i += kSmallThreads)
-        words[i] = i < n ? particle_word(n, i, pos, l, h, qbits, ibits) : ~0ull;
+    for (int i = t; i < npow; i += kSmallThreads) {
+        uint64_t w = ~0ull;
+        if (i < n) {
+            const double x[3] = {pos[i], pos[n + i], pos[2 * n + i]};
+            w = particle_word(i, x, l, h, qbits, ibits);
+        }
+        words[i] = w;
+    }
     __syncthreads();
     for (int k = 2; k <= npow; k <<= 1)
         for (int j = k >> 1; j > 0; j >>= 1) {
@@ -156,23 +191,30 @@ __device__ __forceinline__ unsigned long long peers(unsigned d, int bits, bool v
     return m;
 }
 
-// The tile's digit counts into counts[digit][tile].
+// The tile's digit counts into counts[digit][tile].  Lanes add one by one to one of kCopies sets
+// of counts each, so that few of a wave's additions meet where many words share a digit, as
+// the high digits of clustered particles do (2^20 particles of a Plummer sphere: with one set
+// 127 us, with eight 112 us; uniform ones 112 us with either).
+constexpr int kCopies = 8;
+constexpr int kCopyStride = kMaxDigits + 8;  // the copies of a digit in different banks
 __device__ __forceinline__ void tile_counts(const uint64_t (&w)[kRows], const bool (&valid)[kRows],
-                                            int shift, int bits, unsigned *sh, unsigned *counts,
-                                            int tiles) {
+                                            int shift, int bits,
+                                            unsigned (&sh)[kCopies * kCopyStride],
+                                            unsigned *counts, int tiles) {
     const unsigned digits = 1u << bits;
-    for (unsigned d = threadIdx.x; d < digits; d += kTileThreads) sh[d] = 0;
+    for (int q = threadIdx.x; q < kCopies * kCopyStride; q += kTileThreads) sh[q] = 0;
     __syncthreads();
-    const int lane = threadIdx.x & 63;
+    unsigned *mine = sh + (threadIdx.x % kCopies) * kCopyStride;
 #pragma unroll
-    for (int r = 0; r < kRows; ++r) {
-        const unsigned d = (unsigned)(w[r] >> shift) & (digits - 1);
-        const unsigned long long m = peers(d, bits, valid[r]);
-        if (valid[r] && lane == __ffsll((long long)m) - 1) atomicAdd(&sh[d], (unsigned)__popcll(m));
-    }
+    for (int r = 0; r < kRows; ++r)
+        if (valid[r]) atomicAdd(&mine[(unsigned)(w[r] >> shift) & (digits - 1)], 1u);
     __syncthreads();
-    for (unsigned d = threadIdx.x; d < digits; d += kTileThreads)
-        counts[(size_t)d * tiles + blockIdx.x] = sh[d];
+    for (unsigned d = threadIdx.x; d < digits; d += kTileThreads) {
+        unsigned sum = 0;
+#pragma unroll
+        for (int k = 0; k < kCopies; ++k) sum += sh[k * kCopyStride + d];
+        counts[(size_t)d * tiles + blockIdx.x] = sum;
+    }
 }
 
 // Index of row r's word of this lane: a wave holds kRows consecutive rows of 64.
@@ -180,36 +222,36 @@ __device__ __forceinline__ int64_t word_index(int r) {
     return (int64_t)blockIdx.x * kTile + (threadIdx.x >> 6) * (kRows * 64) + r * 64 + (threadIdx.x & 63);
 }
 
-// Final reduction of the box (by every block, in the same order), the words of the block's
+// Final reduction of the box (by every wave), the words of the block's
 // tile, and the first digit's counts.
 __global__ __launch_bounds__(kTileThreads) void word_kernel(int64_t n, const double *pos,
                                                            const double *part, int qbits, int ibits,
                                                            int bits, uint64_t *words,
                                                            unsigned *counts, int tiles) {
-    __shared__ double lo[3][kTileThreads], hi[3][kTileThreads];
-    __shared__ unsigned sh[kMaxDigits];
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        lo[c][t] = t < kBoxBlocks ? part[6 * t + c] : INFINITY;
-        hi[c][t] = t < kBoxBlocks ? part[6 * t + 3 + c] : -INFINITY;
-    }
-    reduce_box<kTileThreads>(lo, hi);
-    double l[3], h[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        l[c] = lo[c][0];
-        h[c] = hi[c][0];
-    }
-    uint64_t w[kRows];
+    __shared__ unsigned sh[kCopies * kCopyStride];
+    double x[kRows][3];
     bool valid[kRows];
 #pragma unroll
     for (int r = 0; r < kRows; ++r) {
         const int64_t i = word_index(r);
         valid[r] = i < n;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[r][c] = valid[r] ? pos[c * n + i] : 0.0;
+    }
+    double l[3], h[3];
+    wave_box(part, l, h);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        l[c] = __shfl(l[c], 0);
+        h[c] = __shfl(h[c], 0);
+    }
+    uint64_t w[kRows];
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+        const int64_t i = word_index(r);
         w[r] = 0;
         if (valid[r]) {
-            w[r] = particle_word(n, i, pos, l, h, qbits, ibits);
+            w[r] = particle_word(i, x[r], l, h, qbits, ibits);
             words[i] = w[r];
         }
     }
@@ -219,7 +261,7 @@ __global__ __launch_bounds__(kTileThreads) void word_kernel(int64_t n, const dou
 __global__ __launch_bounds__(kTileThreads) void count_kernel(int64_t n, const uint64_t *words,
                                                             int shift, int bits, unsigned *counts,
                                                             int tiles) {
-    __shared__ unsigned sh[kMaxDigits];
+    __shared__ unsigned sh[kCopies * kCopyStride];
     uint64_t w[kRows];
     bool valid[kRows];
 #pragma unroll
@@ -231,26 +273,37 @@ __global__ __launch_bounds__(kTileThreads) void count_kernel(int64_t n, const ui
     tile_counts(w, valid, shift, bits, sh, counts, tiles);
 }
 
-// Exclusive prefix sum of v over the block's threads (256); total in `sum`.
-__device__ __forceinline__ unsigned block_prefix(unsigned v, unsigned *sh, unsigned *sum) {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-        const unsigned o = t >= d ? sh[t - d] : 0;
-        __syncthreads();
-        sh[t] += o;
-        __syncthreads();
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ unsigned wave_prefix(unsigned v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned o = __shfl_up(v, d);
+        v += lane >= d ? o : 0;
     }
-    const unsigned incl = sh[t];
-    *sum = sh[255];
+    return v;
+}
+
+// Exclusive prefix sum of v over the block's threads (256); total in `sum`.
+__device__ __forceinline__ unsigned block_prefix(unsigned v, unsigned (&sh)[4], unsigned *sum) {
+    const int wave = threadIdx.x >> 6;
+    const unsigned incl = wave_prefix(v);
     __syncthreads();
-    return incl - v;
+    if (threadIdx.x % 64 == 63) sh[wave] = incl;
+    __syncthreads();
+    unsigned before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        before += w < wave ? sh[w] : 0;
+        all += sh[w];
+    }
+    *sum = all;
+    return before + incl - v;
 }
 
 // Block d: counts[d][0 .. tiles) to exclusive prefix sums, and the digit's total.
 __global__ __launch_bounds__(256) void scan_kernel(unsigned *counts, unsigned *totals, int tiles) {
-    __shared__ unsigned sh[256];
+    __shared__ unsigned sh[4];
     unsigned *row = counts + (size_t)blockIdx.x * tiles;
     unsigned run = 0;
     for (int b = 0; b < tiles; b += 256) {
@@ -274,7 +327,7 @@ __global__ __launch_bounds__(kTileThreads) void scatter_kernel(int64_t n, const 
                                                               uint64_t mask) {
     __shared__ uint64_t sorted[kTile];
     __shared__ unsigned hist[kWaves][kMaxDigits];  // per wave, then the wave's first local slot
-    __shared__ unsigned scan[2][kMaxDigits];
+    __shared__ unsigned scan[2][kMaxDigits / 64];  // per wave
     __shared__ unsigned dest[kMaxDigits];          // output slot - local slot of each digit's
                                                    // words (modulo 2^32)
     const unsigned digits = 1u << bits;
@@ -291,6 +344,11 @@ __global__ __launch_bounds__(kTileThreads) void scatter_kernel(int64_t n, const 
         const int64_t i = word_index(r);
         valid[r] = i < n;
         w[r] = valid[r] ? in[i] : 0;
+    }
+    unsigned total = 0, before_tile = 0;  // digit t's, needed after the ranks
+    if (t < (int)digits) {
+        total = totals[t];
+        before_tile = counts[(size_t)t * tiles + blockIdx.x];
     }
     __syncthreads();
     // Rank of each word among the wave's words of the same digit, row by row.
@@ -309,32 +367,24 @@ __global__ __launch_bounds__(kTileThreads) void scatter_kernel(int64_t n, const 
     __syncthreads();
     // Digit t: its count in the tile, and exclusive prefix sums over the digits of the
     // tile's counts (local slots) and of the totals (output slots).
-    unsigned own = 0, total = 0;
-    if (t < (int)digits) {
+    unsigned own = 0;
+    if (t < (int)digits)
         for (int v = 0; v < kWaves; ++v) own += hist[v][t];
-        total = totals[t];
-    }
-    if (t < kMaxDigits) {
-        scan[0][t] = own;
-        scan[1][t] = total;
+    unsigned own_to = wave_prefix(own), total_to = wave_prefix(total);
+    if (wave < kMaxDigits / 64 && lane == 63) {
+        scan[0][wave] = own_to;
+        scan[1][wave] = total_to;
     }
     __syncthreads();
-    for (int d = 1; d < kMaxDigits; d <<= 1) {
-        unsigned a = 0, b = 0;
-        if (t < kMaxDigits && t >= d) {
-            a = scan[0][t - d];
-            b = scan[1][t - d];
+#pragma unroll
+    for (int v = 0; v < kMaxDigits / 64; ++v)
+        if (v < wave) {
+            own_to += scan[0][v];
+            total_to += scan[1][v];
         }
-        __syncthreads();
-        if (t < kMaxDigits) {
-            scan[0][t] += a;
-            scan[1][t] += b;
-        }
-        __syncthreads();
-    }
     if (t < (int)digits) {
-        unsigned slot = scan[0][t] - own;
-        dest[t] = scan[1][t] - total + counts[(size_t)t * tiles + blockIdx.x] - slot;
+        unsigned slot = own_to - own;
+        dest[t] = total_to - total + before_tile - slot;
         for (int v = 0; v < kWaves; ++v) {
             const unsigned c = hist[v][t];
             hist[v][t] = slot;
@@ -396,7 +446,7 @@ nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, 
     const int bits = (key_bits + passes - 1) / passes;  // digits of 6 to 8 bits
     const uint64_t mask = (1ull << ibits) - 1;
     const dim3 grid((unsigned)tiles), block(kTileThreads);
-    hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(256), 0, s, n, pos64, part);
+    hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(kBoxThreads), 0, s, n, pos64, part);
     hipLaunchKernelGGL(word_kernel, grid, block, 0, s, n, pos64, (const double *)part, qbits, ibits,
                        bits, words, counts, tiles);
     for (int p = 0; p < passes; ++p) {
