@@ -7,7 +7,7 @@
 // permutation.  Ties in the key are broken by index, so the order is unique.
 //
 //   * up to kSmall particles: one block does it all in LDS (bounding box, words, bitonic
-//     network), one launch;
+//     network or radix passes), one launch;
 //   * above: a stable radix sort of the key bits alone, from the least significant digit
 //     (the words start in index order, so ties stay in it).  Each pass is three launches:
 //     digit counts of every tile, prefix sums of the counts over the tiles (one block per
@@ -19,6 +19,7 @@
 // 2^20 particles: 112 us in 19 launches, 779 us in the 210 launches of a bitonic network in
 // global memory.  Prefix sums and the final box run inside waves and the counts are plain
 // additions: with 8 and 9 block-wide steps for the former and ballots for the latter 139 us.
+#include <algorithm>
 #include <utility>
 
 #include "centre_sum.h"
@@ -29,7 +30,11 @@ namespace {
 
 constexpr int kBoxBlocks = 256;  // one slot of the final reduction each
 constexpr int kBoxThreads = 512;
-constexpr int kSmall = 8192;       // words one block sorts in LDS (64 KB)
+// One block sorts up to kSmall words in LDS (64 KB), up to kBitonic by a bitonic network
+// (N = 1000: 17.1 us, by radix passes 20.4; 2048: 24.6 and 23.8; 4096: 43.9 and 37.0; 8192:
+// 85.4 and 64.5 us; 8193, in 23 launches: 84.5 us).
+constexpr int kBitonic = 1024;
+constexpr int kSmall = 8192;
 constexpr int kSmallThreads = 1024;
 constexpr int kTile = 4096;        // words per block of the radix passes
 constexpr int kTileThreads = 512;  // 8 waves, 8 rows of 64 words each
@@ -53,12 +58,12 @@ __device__ __forceinline__ void reduce_box(double (*lo)[THREADS], double (*hi)[T
 }
 
 // This thread's box of the particles first, first + stride, ...
-template <int THREADS>
+template <int THREADS, int AHEAD = 1>
 __device__ __forceinline__ void thread_box(int64_t n, const double *pos, int64_t first,
                                            int64_t stride, double (*lo)[THREADS],
                                            double (*hi)[THREADS]) {
     double l[3] = {INFINITY, INFINITY, INFINITY}, h[3] = {-INFINITY, -INFINITY, -INFINITY};
-#pragma unroll 4
+#pragma unroll AHEAD
     for (int64_t i = first; i < n; i += stride)
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -99,7 +104,7 @@ __device__ __forceinline__ void wave_box(const double *v, double (&l)[3], double
 __global__ __launch_bounds__(kBoxThreads) void box_partial_kernel(int64_t n, const double *pos,
                                                                  double *part) {
     __shared__ double lo[3][kBoxThreads], hi[3][kBoxThreads];
-    thread_box<kBoxThreads>(n, pos, (int64_t)blockIdx.x * kBoxThreads + threadIdx.x,
+    thread_box<kBoxThreads, 4>(n, pos, (int64_t)blockIdx.x * kBoxThreads + threadIdx.x,
                             (int64_t)gridDim.x * kBoxThreads, lo, hi);
     reduce_box<kBoxThreads>(lo, hi);
     if (threadIdx.x < 3) {
@@ -138,7 +143,7 @@ __device__ __forceinline__ uint64_t particle_word(int64_t i, const double (&x)[3
     return (key << ibits) | (uint64_t)i;
 }
 
-// Up to kSmall particles in one block: npow (a power of two >= n) words in LDS.
+// Up to kBitonic particles in one block: npow (a power of two >= n) words in LDS.
 __global__ __launch_bounds__(kSmallThreads) void small_kernel(int n, int npow, const double *pos,
                                                              int qbits, int ibits, int32_t *perm) {
     extern __shared__ uint64_t words[];
@@ -189,6 +194,104 @@ __device__ __forceinline__ unsigned long long peers(unsigned d, int bits, bool v
         m &= one ? v : ~v;
     }
     return m;
+}
+
+// Inclusive prefix sum over the wave's lanes.
+__device__ __forceinline__ unsigned wave_prefix(unsigned v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned o = __shfl_up(v, d);
+        v += lane >= d ? o : 0;
+    }
+    return v;
+}
+
+// Up to ROWS * kSmallThreads particles in one block: the radix passes below with every word in
+// registers between them and in LDS during them.  A wave holds ROWS consecutive rows of 64.
+template <int ROWS>
+__global__ __launch_bounds__(kSmallThreads) void small_radix_kernel(int n, const double *pos,
+                                                                   int qbits, int ibits, int bits,
+                                                                   int passes, int32_t *perm) {
+    constexpr int W = kSmallThreads / 64;
+    __shared__ unsigned hist[W][kMaxDigits];  // per wave, then the wave's first slot
+    __shared__ unsigned scan[kMaxDigits / 64];
+    extern __shared__ uint64_t words[];
+    const int t = threadIdx.x;
+    const int lane = t & 63;
+    const int wave = t >> 6;
+    // The box first, in the words' memory.
+    double(*lo)[kSmallThreads] = reinterpret_cast<double(*)[kSmallThreads]>(words);
+    double(*hi)[kSmallThreads] = lo + 3;
+    thread_box<kSmallThreads>(n, pos, t, kSmallThreads, lo, hi);
+    reduce_box<kSmallThreads>(lo, hi);
+    double l[3], h[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        l[c] = lo[c][0];
+        h[c] = hi[c][0];
+    }
+    uint64_t w[ROWS];
+    bool valid[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int i = (wave * ROWS + r) * 64 + lane;
+        valid[r] = i < n;
+        w[r] = 0;
+        if (valid[r]) {
+            const double x[3] = {pos[i], pos[n + i], pos[2 * n + i]};
+            w[r] = particle_word(i, x, l, h, qbits, ibits);
+        }
+    }
+    const unsigned digits = 1u << bits;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = ibits + p * bits;
+        __syncthreads();
+        for (int q = t; q < W * kMaxDigits; q += kSmallThreads) (&hist[0][0])[q] = 0;
+        __syncthreads();
+        unsigned slot[ROWS];
+        volatile unsigned *mine = hist[wave];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            const unsigned d = (unsigned)(w[r] >> shift) & (digits - 1);
+            const unsigned long long m = peers(d, bits, valid[r]);
+            const unsigned before = mine[d];
+            slot[r] = before + (unsigned)__popcll(m & ((1ull << lane) - 1));
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid[r] && lane == __ffsll((long long)m) - 1) mine[d] = before + (unsigned)__popcll(m);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        __syncthreads();
+        // Digit t: exclusive prefix sums of its counts over the digits, then over the waves.
+        unsigned own = 0;
+        if (t < kMaxDigits)
+            for (int v = 0; v < W; ++v) own += hist[v][t];
+        unsigned to = wave_prefix(own);
+        if (wave < kMaxDigits / 64 && lane == 63) scan[wave] = to;
+        __syncthreads();
+        if (t < kMaxDigits) {
+#pragma unroll
+            for (int v = 0; v < kMaxDigits / 64; ++v) to += v < wave ? scan[v] : 0;
+            unsigned first = to - own;
+            for (int v = 0; v < W; ++v) {
+                const unsigned c = hist[v][t];
+                hist[v][t] = first;
+                first += c;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (valid[r]) words[hist[wave][(unsigned)(w[r] >> shift) & (digits - 1)] + slot[r]] = w[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            if (valid[r]) w[r] = words[(wave * ROWS + r) * 64 + lane];
+    }
+    const uint64_t mask = (1ull << ibits) - 1;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+        if (valid[r]) perm[(wave * ROWS + r) * 64 + lane] = (int32_t)(w[r] & mask);
 }
 
 // The tile's digit counts into counts[digit][tile].  Lanes add one by one to one of kCopies sets
@@ -271,17 +374,6 @@ __global__ __launch_bounds__(kTileThreads) void count_kernel(int64_t n, const ui
         w[r] = valid[r] ? words[i] : 0;
     }
     tile_counts(w, valid, shift, bits, sh, counts, tiles);
-}
-
-// Inclusive prefix sum over the wave's lanes.
-__device__ __forceinline__ unsigned wave_prefix(unsigned v) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned o = __shfl_up(v, d);
-        v += lane >= d ? o : 0;
-    }
-    return v;
 }
 
 // Exclusive prefix sum of v over the block's threads (256); total in `sum`.
@@ -424,7 +516,10 @@ nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, 
     int ibits = 0;
     while ((int64_t(1) << ibits) < n) ++ibits;
     const int qbits = (64 - ibits) / 3;
-    if (n <= kSmall) {
+    const int key_bits = 3 * qbits;
+    const int passes = (key_bits + 7) / 8;
+    const int bits = (key_bits + passes - 1) / passes;  // digits of 6 to 8 bits
+    if (n <= kBitonic) {
         int npow = 1;
         while (npow < n) npow <<= 1;
         // At least the box reduction's six doubles per thread.
@@ -435,15 +530,22 @@ nbody_status launch_morton_order(int64_t n, const double *pos64, int32_t *perm, 
         NBODY_HIP_CHECK(hipGetLastError());
         return NBODY_OK;
     }
+    if (n <= kSmall) {
+        auto fn = n <= 2 * kSmallThreads   ? small_radix_kernel<2>
+                  : n <= 4 * kSmallThreads ? small_radix_kernel<4>
+                                           : small_radix_kernel<8>;
+        const size_t lds = std::max(sizeof(uint64_t) * (size_t)n, sizeof(double) * 6 * kSmallThreads);
+        hipLaunchKernelGGL(fn, dim3(1), dim3(kSmallThreads), lds, s, (int)n, pos64, qbits, ibits, bits,
+                           passes, perm);
+        NBODY_HIP_CHECK(hipGetLastError());
+        return NBODY_OK;
+    }
     uint64_t *words = static_cast<uint64_t *>(scratch);
     uint64_t *other = words + n;
     double *part = reinterpret_cast<double *>(other + n);
     unsigned *totals = reinterpret_cast<unsigned *>(part + 6 * kBoxBlocks);
     unsigned *counts = totals + kMaxDigits;
     const int tiles = tiles_of(n);
-    const int key_bits = 3 * qbits;
-    const int passes = (key_bits + 7) / 8;
-    const int bits = (key_bits + passes - 1) / passes;  // digits of 6 to 8 bits
     const uint64_t mask = (1ull << ibits) - 1;
     const dim3 grid((unsigned)tiles), block(kTileThreads);
     hipLaunchKernelGGL(box_partial_kernel, dim3(kBoxBlocks), dim3(kBoxThreads), 0, s, n, pos64, part);

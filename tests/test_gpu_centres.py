@@ -127,11 +127,12 @@ def test_leapfrog_with_tile_centres_matches_oracle():
     assert rel_errors(acc.cpu().numpy().T, ao)["rel_rms"] < 1e-6
 
 
-@pytest.mark.parametrize("n", [2, 3, 64, 1025, 4097, 8191, 8192, 8193, 12288, 16385, 70000])
+@pytest.mark.parametrize("n", [2, 3, 64, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192,
+                               8193, 12288, 16385, 70000])
 @pytest.mark.parametrize("kind", ["sphere", "ties", "line"])
 def test_morton_order_of_every_sort_path(n, kind):
-    # One block in LDS up to 8192 particles, the radix passes above; many equal keys, and a
-    # degenerate box (two coordinates constant).
+    # One block in LDS up to 8192 particles (bitonic, then radix passes), many blocks above;
+    # many equal keys, and a degenerate box (two coordinates constant).
     pos, _, _ = ics.plummer(n, seed=91, velocities=False)
     if kind == "ties":
         pos = np.round(pos)
