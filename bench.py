@@ -22,7 +22,7 @@ accuracy against the FP64 oracle on the configuration's stated sample):
                  oracle on the FP32-rounded inputs the kernel saw (representation
                  error apart from arithmetic error).
   clusters_2048  2048 ragged Plummer clusters: one graph-replayed batched KDK step
-                 (persistent work-queue kernel); pairs = sum N_k^2; 16 systems checked
+                 (one pair launch over a work list); pairs = sum N_k^2; 16 systems checked
                  (acceleration and potential) at step 0 and after the timed steps.
   adjoint_16384  N = 16384, 32 KDK steps dt = 1/256 and the reverse pass: one loss +
                  gradient (33 force and 33 adjoint evaluations of N^2 pairs).
@@ -83,12 +83,13 @@ SLOTS = {"gravity": 13 + RSQ_SLOTS, "jerk": 27 + RSQ_SLOTS, "adjoint": 31 + RSQ_
 # potential, the count customary for fourth-order Hermite codes; 45 for the adjoint.
 FLOPS = {"gravity": 20, "jerk": 60, "adjoint": 45}
 
-# The files that define the pair kernel tile_kernel<Gravity> (force.hip only instantiates
+# The files that define the pair kernel wave_kernel<Gravity> (force.hip only instantiates
 # it; its own kernels are the finalize and centre passes), and the tuning file whose
 # force-kernel entries for N = 131072 (size bucket 17) pick the launch shape; the
 # committed counter record is dropped when either changes.
 KERNEL_SOURCES = ["paper_astro_ph_0703100_amd/csrc/nbody_internal.h",
                   "paper_astro_ph_0703100_amd/csrc/tile_engine.h",
+                  "paper_astro_ph_0703100_amd/csrc/wave_engine.h",
                   "paper_astro_ph_0703100_amd/csrc/gravity.h"]
 TUNING_FILE = "paper_astro_ph_0703100_amd/tuning_gfx950.json"
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "pair_kernel_plummer_131072.md")
@@ -357,7 +358,7 @@ def bench_plummer(args, torch, w):
     # The committed counter record is the grid engine's pair kernel.
     rec = None if args.symmetric else committed_record()
     kname = ("sym_kernel (+ sym_finalize_kernel), each unordered pair once" if args.symmetric
-             else "tile_kernel<Gravity> (+ finalize_kernel)")
+             else "wave_kernel<Gravity> (+ finalize_kernel)")
     roof = roofline("gravity", pairs, r0["kernel_ms"], kname,
                     rec["bytes_per_launch"] if rec else None)
     if rec and rec.get("sustained_clock_ghz"):
@@ -476,7 +477,7 @@ def bench_small(args, torch, w):
     head = next(iter(res))
     r0 = res[head]
     kname = ("split_kernel<Gravity, ForceOut> (one launch per evaluation)" if r0["shape"][3] > 1
-             else "tile_kernel<Gravity> + finalize_kernel")
+             else "wave_kernel<Gravity> + finalize_kernel")
     return {
         "value": pairs / (r0["kernel_ms"] * 1e-3), "ms_per_step": r0["kernel_ms"],
         "config": {"workload": w.name, "n": n, "eps": eps, "seed": w.seed, "precision": head,
@@ -591,7 +592,7 @@ def bench_stress(args, torch, w):
                            "arithmetic relative to per-i-tile FP64 centres",
                    "description": w.description},
         "roofline": roofline("gravity", pairs, r0["kernel_ms"],
-                             "tile_kernel<GravityTile> (+ centres, finalize)"),
+                             "wave_kernel<GravityTile> (+ centres, finalize)"),
         "cpu_baseline": cpu,
         "modes": {"%s/%s" % (p, c): {"ms_per_step": r["kernel_ms"],
                                      **fractions("gravity", pairs, r["kernel_ms"]),
@@ -602,7 +603,7 @@ def bench_stress(args, torch, w):
 
 
 def bench_clusters(args, torch, w):
-    """2048 ragged clusters: graph-replayed batched KDK steps (persistent kernel)."""
+    """2048 ragged clusters: graph-replayed batched KDK steps (work list)."""
     from paper_astro_ph_0703100_amd import api, ics, metrics
     b = ics.cluster_batch(w.n, seed=w.seed, eps=w.eps)
     dev = torch.device("cuda:0")
@@ -674,11 +675,11 @@ def bench_clusters(args, torch, w):
         "value": pairs * args.steps / r0["wall"], "ms_per_step": r0["wall"] / args.steps * 1e3,
         "config": {"workload": w.name, "systems": w.n, "particles": int(b.offsets[-1]),
                    "pairs_per_step": pairs, "eps": w.eps, "dt": w.dt, "precision": head,
-                   "step": "one graph-replayed batched KDK step (one persistent launch over "
+                   "step": "one graph-replayed batched KDK step (one pair launch over "
                            "cost-sorted work items)", "plan": r0["info"],
                    "description": w.description},
         "roofline": roofline("gravity", pairs, r0["kernel_ms"],
-                             "persistent_kernel<Gravity> (+ batched finalize)"),
+                             "batched_pair_kernel (+ finalize of divided systems)"),
         "cpu_baseline": cpu,
         "modes": {p: {"value": pairs * args.steps / r["wall"],
                       "ms_per_step": r["wall"] / args.steps * 1e3,
@@ -775,7 +776,7 @@ def bench_adjoint(args, torch, w, big=True):
                            "pass with the adjoint kernel; pairs counted: forward + adjoint"
                            % w.steps, "description": w.description},
         "roofline": roofline("adjoint", float(n) * n, float(np.mean(kms)),
-                             "tile_kernel<Adjoint> (+ finalize)"),
+                             "wave_kernel<Adjoint> (+ finalize)"),
         "cpu_baseline": cpu,
         "modes": {"comp": {"value": pairs_step * args.steps / wall,
                            "ms_per_step": wall / args.steps * 1e3,
@@ -840,7 +841,7 @@ def bench_shard(args, torch, w):
                            "potential as for any separate i-set",
                    "description": w.description},
         "roofline": roofline("gravity", pairs, r0["kernel_ms"],
-                             "tile_kernel<GravityIJ> (+ finalize_kernel)"),
+                             "wave_kernel<GravityIJ> (+ finalize_kernel)"),
         "cpu_baseline": cpu,
         "modes": {p: {"value": pairs * args.steps / r["wall"],
                       "ms_per_step": r["wall"] / args.steps * 1e3,
@@ -923,7 +924,7 @@ def bench_jerk(args, torch, w):
                            "mean position and velocity), FP64 corrector",
                    "description": w.description},
         "roofline": roofline("jerk", pairs, r0["kernel_ms"],
-                             "tile_kernel<GravityJerk> (+ jerk_finalize_kernel)"),
+                             "wave_kernel<GravityJerk> (+ jerk_finalize_kernel)"),
         "cpu_baseline": cpu,
         "modes": {p: {"value": pairs * args.steps / r["wall"],
                       "ms_per_step": r["wall"] / args.steps * 1e3,
@@ -1003,7 +1004,7 @@ def bench_active(args, torch, w):
                            "the active particles' own pairs count as for any separate i-set",
                    "description": w.description},
         "roofline": roofline("jerk", pairs, r0["kernel_ms"],
-                             "tile_kernel<GravityJerkIJ> (+ jerk_finalize_kernel)"),
+                             "wave_kernel<GravityJerkIJ> (+ jerk_finalize_kernel)"),
         "cpu_baseline": cpu,
         "modes": {p: {"value": pairs * args.steps / r["wall"],
                       "ms_per_step": r["wall"] / args.steps * 1e3,

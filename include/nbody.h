@@ -90,17 +90,20 @@ typedef struct nbody_opts {
 } nbody_opts;
 
 /* Launch shapes.  Three pair engines evaluate the same sums:
- *   - the grid engine (jlanes = 1): a block of 256 lanes holds 256 * ipl i-particles
- *     and walks one of nseg j-segments in LDS tiles of jtile records (64 to 512);
- *     the segment partial sums go to scratch memory and a second kernel adds them
- *     per particle in FP64 (the paper's i-parallel FORCE-LOOP, Sec. 2.2);
+ *   - the grid engine (jlanes = 1): each wavefront holds 64 * ipl i-particles (ipl at
+ *     most 4, jerk and adjoint 2) against runs of j's in FP32 blocks of min(jtile, 128)
+ *     records; the partial sums of up to nseg j-segments go to scratch memory and a
+ *     second kernel adds them per particle in FP64 (the paper's i-parallel FORCE-LOOP,
+ *     Sec. 2.2).  With one segment the launch stores the outputs itself;
  *   - the split engine (jlanes = 8, 16, 32 or 64; ipl = 1 or 2; jtile = 256, 512,
  *     1024, or 2048 with jlanes >= 32; the adjoint: 256 or 512; nseg must be 0): for
  *     systems too small to
  *     fill the chip with whole i-tiles, the j-range of each i-particle is split over
  *     jlanes lanes of one wavefront, whose partial sums are added across the lanes
  *     in FP64 (PLAIN: FP32) by DPP / permlane moves in a fixed order.  One launch, no
- *     scratch for partial sums.  Available for nbody_force, nbody_force_ex,
+ *     scratch for partial sums.  The force with ipl = 1, jlanes >= 32 and at most 8192
+ *     particles runs with every record in LDS, FP64 positions with their centre in the
+ *     same launch.  Available for nbody_force, nbody_force_ex,
  *     nbody_force_f64, the leapfrog, nbody_force_vjp(_f64) and the leapfrog adjoint,
  *     not with NBODY_CENTRE_TILE (which uses the grid engine's i-tiles);
  *   - the symmetric engine (symmetric = 2; ipl = 1, 2 or 4; jtile = 64 or 128;
@@ -134,7 +137,9 @@ NBODY_API const char *nbody_version(void);
 
 /* Bytes of scratch that nbody_force, nbody_force_ex, nbody_force_f64 and
  * nbody_leapfrog need for n particles with these options (0 for n <= 0 or invalid
- * options; the batched plan owns its own). */
+ * options; the batched plan owns its own).  With 3n doubles more, a leapfrog step of at
+ * most 8192 particles is one launch instead of two (same results; the library's own
+ * scratch and a graph's have them). */
 NBODY_API size_t nbody_workspace_size(int64_t n, const nbody_opts *opts);
 
 /* ------------------------------------------------------------------------------
@@ -379,9 +384,8 @@ NBODY_API nbody_status nbody_leapfrog_adjoint(int64_t n, const double *traj, con
  * A plan is built once from the HOST array offsets (int64, nsys + 1 entries,
  * offsets[0] = 0, non-decreasing, total < 2^30; empty systems allowed).  It cuts every
  * system into work items (an i-tile against a j-range), sorts them by decreasing
- * cost, and owns the device tables, the partial-sum scratch and the ticket counter of
- * the persistent kernel that runs them - so every call with a plan allocates nothing
- * and can be captured in a graph.  Calls with the same plan must not overlap in time
+ * cost, and owns the device tables and the partial-sum scratch of the launch that runs
+ * them - so every call with a plan allocates nothing and can be captured in a graph.  Calls with the same plan must not overlap in time
  * (they share its scratch).  opts: precision, centre (NONE or SYSTEM), ipl, jtile;
  * self_pot must be 0 and workspace NULL.  The plan belongs to the current device.
  * ---------------------------------------------------------------------------- */
@@ -389,7 +393,7 @@ typedef struct nbody_plan nbody_plan;
 NBODY_API nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
                                                  const nbody_opts *opts, nbody_plan **out);
 NBODY_API void nbody_plan_destroy(nbody_plan *plan);
-/* info[0..8): nsys, total particles, work items, persistent blocks, pairs (sum N_k^2),
+/* info[0..8): nsys, total particles, work items, blocks of the pair launch, pairs (sum N_k^2),
  * pairs including tile padding, ipl, jtile. */
 NBODY_API nbody_status nbody_plan_info(const nbody_plan *plan, int64_t *info);
 

@@ -1,5 +1,5 @@
-// Output stages shared by the FP64 finalize kernels of the tile engine and by the
-// single-launch split engine (device code): what is stored for store slot c of
+// Output stages shared by the FP64 finalize kernels of the grid engine and by the launches
+// that store their outputs themselves (device code): what is stored for store slot c of
 // particle i, given `sum(o)`, the FP64 sum over all j of the pipeline's output o.
 #pragma once
 

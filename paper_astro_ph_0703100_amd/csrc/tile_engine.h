@@ -1,22 +1,21 @@
-// Generic i-tile x j-tile pair engine for gfx950 (device code, header-only).
+// What the pair engines for gfx950 share (device code, header-only): the pipeline interface,
+// the two-sum, the pass over an LDS tile and the sums of segment partials.  The grid engine
+// itself is in wave_engine.h; the split, whole-set and symmetric engines have headers of
+// their own.
 //
 // The paper's library evaluates arbitrary pair interactions from a user-written pipeline
 // description that reads an i-record and a j-record and accumulates outputs
 // (Sec. 4.5, Appendix A).  This engine is that idea on CDNA4: a pipeline type `Op`
 // supplies the records and the pair body; the engine supplies the blocking.
 //
-//   * a block of 256 lanes owns an i-tile of 256 * IPL particles; each lane keeps IPL
-//     i-records in VGPRs (lane-strided so global loads and stores coalesce);
-//   * blockIdx.y selects a j-segment; the block walks it in LDS tiles of JT
-//     j-records, staged with coalesced loads and double-buffered (one barrier per
-//     tile), the J-BAG / J-PACKING of Sec. 2.2;
-//   * every lane reads each j-record from LDS with broadcast 16-byte reads and runs
-//     the pair body for its IPL i-records;
+//   * each lane keeps IPL i-records in VGPRs (lane-strided so global loads and stores
+//     coalesce); j-records pass through LDS, the J-BAG / J-PACKING of Sec. 2.2, and are
+//     read back with broadcast 16-byte reads;
 //   * the j == i pair is left out of every sum (eq. (1) sums over the other
-//     particles): in the few j-tiles that hold some of the block's own i's (i- and
+//     particles): in the few stretches of j's that hold some of a wave's own i's (i- and
 //     j-sets the same, Op::kSelf), each lane swaps the record of its own particle
 //     for Op::null_j of it (same position, nothing that adds), by a compare and a
-//     select per pair; all other tiles run the plain pass;
+//     select per pair; all others run the plain pass;
 //   * accumulation (Sec. 2.2.2, eq. (2); Sec. 3.4):
 //       PLAIN   - one FP32 accumulator per output and (i, segment);
 //       FP64RED - FP32 partial over each block of min(Op::kBlockJ, JT) j's, added into FP64;

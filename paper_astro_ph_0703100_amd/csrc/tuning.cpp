@@ -29,11 +29,10 @@ TuneEntry g_tab[KERNEL_COUNT][3][kBuckets];
 
 TuneEntry builtin(int kernel, int64_t n, int engines) {
     const bool split_ok = (engines & kEngineSplit) != 0;
-    // Measured on MI355X (tune.py): one i-particle per lane (37 VGPRs, 8 waves per
-    // SIMD) and many j-segments beat wider i-tiles for every kernel and size tried;
-    // the j-split itself is chosen from n (nseg = 0).  Below 2^13 particles the force's
-    // single-launch split engine is faster (graph-replayed evaluations, N = 2048: 5.4
-    // against 9.5 us; N = 4096: 10.7 against 13.0 us); from 2^13 on the grid engine is.
+    // ipl 1 leaves the i-records per lane of a grid-engine launch to the size of the launch,
+    // nseg 0 the j-split.  Below 2^13 particles the force's single launches (split and
+    // whole-set engines) are faster (N = 2000: 5.1 against 7.1 us, one launch each);
+    // from 2^13 on the grid engine is (N = 8192: 24.4 us, 25.8 us in one launch).
     // The 2048-record tile (64 KB of LDS, two blocks per CU) only while every block fits
     // in one round.
     // Up to 2048 particles the tile is the smallest that holds every j (padding records
