@@ -120,11 +120,13 @@ int wave_ipl(int kernel, int precision, int64_t blocks, int ipl) {
     // systems), fewer leave more waves to spread over the chip.  Force, pair kernel +
     // finalize, ipl 1 / 2 / 4: N = 20011 (49000 blocks) 122.2 / 123.6 / - us, 32768
     // (131072 blocks) 298.8 / 293.1 / 300 us, 131072 (2^21 blocks) - / 4491 / 4380 us.
+    // Between them, N = 28648 (100352 blocks) without / with jerk 233.9 / 447.9 us with one and
+    // 245.3 / 458.3 with two, 30000 (110215) 254.4 / 487.4 and 253.6 / 478.6.
     // PLAIN, whose segments are given: N = 65536 1175 / 1149 / 1175 us, 131072 4660 /
     // 4470 / 4730 us.  Batches of small systems pay for padded i's too: 2048 clusters of 256
     // to 16384 particles 18.25 / 17.61 / 17.86 ms.
     if (precision == NBODY_PLAIN) return blocks >= 200000 ? 2 : 1;
-    return std::min(blocks >= 1000000 ? 4 : blocks >= 100000 ? 2 : 1, most);
+    return std::min(blocks >= 1000000 ? 4 : blocks >= 105000 ? 2 : 1, most);
 }
 
 // Launch of the grid engine for a shape whose ipl, jt and nseg are chosen: what the result
