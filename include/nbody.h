@@ -18,7 +18,12 @@
  *   - stream is a hipStream_t passed as void* (NULL = the null stream).  Every call
  *     only enqueues work on it and returns without synchronising, except where a
  *     function says otherwise.
- *   - Outputs must not alias inputs.  n = 0 is a valid no-op.
+ *   - Outputs must not alias inputs, except that calls which the grid engine serves and
+ *     calls of nbody_force_f64 without per-tile centres may store an output in the memory
+ *     of inputs (an array in its own place, or over inputs that only the pairs read): the
+ *     outputs are then stored by a launch of their own after the pairs.  The split engine
+ *     on FP32 positions, the split adjoint and batched plans on FP32 positions store
+ *     outputs while they read inputs.  n = 0 is a valid no-op.
  *   - eps must be finite and > 0 (the self pair would otherwise be 0/0).
  *   - NaN or Inf in the inputs propagate to the outputs; they are not checked.
  *   - Scratch memory: if opts->workspace is NULL the library uses a per-device
@@ -203,7 +208,7 @@ NBODY_API nbody_status nbody_force_noalloc(int64_t n, const float *pos, const fl
  *   acc     double [3][ni] (written); pot double [ni] or NULL (written)
  *   opts    precision, ipl, jtile, nseg and workspace apply; centre and self_pot are
  *           ignored (the inputs are FP32 already); NULL = defaults
- * nj = 0 writes zeros.  Outputs must not alias inputs.  Scratch:
+ * nj = 0 writes zeros.  Scratch:
  * nbody_workspace_size_ij bytes (the per-device cache when opts->workspace is NULL).
  * ---------------------------------------------------------------------------- */
 NBODY_API nbody_status nbody_force_ij(int64_t ni, const float *pos_i, const float *eps_i,
@@ -226,7 +231,7 @@ NBODY_API size_t nbody_workspace_size_ij(int64_t ni, int64_t nj, const nbody_opt
  *   acc    double [3][n], jerk double [3][n] (written); pot double [n] or NULL
  *   opts   precision, self_pot, ipl, jtile, nseg, workspace; NULL = defaults
  * Scratch: nbody_workspace_size_jerk bytes (covers both entry points), from
- * opts->workspace or the per-device cache.  Outputs must not alias inputs.
+ * opts->workspace or the per-device cache.
  * ---------------------------------------------------------------------------- */
 NBODY_API nbody_status nbody_force_jerk(int64_t n, const float *pos, const float *vel,
                                         const float *mass, float eps, double *acc, double *jerk,
@@ -258,7 +263,7 @@ NBODY_API nbody_status nbody_force_jerk_f64(int64_t n, const double *pos64, cons
  *   acc     double [3][ni], jerk double [3][ni] (written); pot double [ni] or NULL
  *   opts    precision, ipl, jtile, nseg and workspace apply; centre and self_pot are
  *           ignored; NULL = defaults
- * nj = 0 writes zeros.  Outputs must not alias inputs.  Scratch:
+ * nj = 0 writes zeros.  Scratch:
  * nbody_workspace_size_jerk_ij bytes (the per-device cache when opts->workspace is NULL).
  * ---------------------------------------------------------------------------- */
 NBODY_API nbody_status nbody_force_jerk_ij(int64_t ni, const float *pos_i, const float *vel_i,

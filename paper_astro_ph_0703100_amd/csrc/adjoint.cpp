@@ -45,8 +45,11 @@ nbody_status vjp_f32_core(int64_t n, const float *pos, const float *mass, float 
     VjpFinalizeArgs fa{part,      cfg.wseg, cfg.npad,           (int)n, g_pot,
                        grad_pos,  grad_mass, accumulate ? 1 : 0, g_acc};
     if (cfg.jl > 1) return launch_vjp_split(cfg, o.precision, va, grad_mass != nullptr, fa, s);
-    nbody_status st = launch_vjp(cfg, o.precision, va, grad_mass != nullptr, fa, s);
-    if (st || cfg.wseg == 1) return st;
+    const TileCfg run = without_races(
+        cfg, {span(grad_pos, 3 * n), span(grad_mass, n)},
+        {span(pos, 3 * n), span(mass, n), span(g_acc, 3 * n), span(g_pot, n)});
+    nbody_status st = launch_vjp(run, o.precision, va, grad_mass != nullptr, fa, s);
+    if (st || run.direct) return st;
     if (!step) return launch_vjp_finalize(o.precision, fa, s);
     fa.vbar = step->vbar;
     fa.abar = step->abar;
@@ -74,8 +77,11 @@ nbody_status vjp_f64_core(int64_t n, const double *pos64, const float *mass, flo
                        g_pot, (int)n, cfg.wseg_len, e2, ws.part, cfg.npad, centres, itile};
         VjpFinalizeArgs fa{ws.part,  cfg.wseg, cfg.npad,           (int)n, g_pot,
                            grad_pos, grad_mass, accumulate ? 1 : 0, g_acc};
-        st = launch_vjp_tile(cfg, o.precision, va, grad_mass != nullptr, fa, s);
-        if (st || cfg.wseg == 1) return st;
+        const TileCfg run = without_races(
+            cfg, {span(grad_pos, 3 * n), span(grad_mass, n)},
+            {span(pos64, 3 * n), span(mass, n), span(g_acc, 3 * n), span(g_pot, n)});
+        st = launch_vjp_tile(run, o.precision, va, grad_mass != nullptr, fa, s);
+        if (st || run.direct) return st;
         return launch_vjp_finalize(o.precision, fa, s);
     }
     if (o.centre == NBODY_CENTRE_SYSTEM) {

@@ -1,10 +1,10 @@
 // Host side of the C ABI: argument validation, launch-shape choice, scratch memory
 // and dispatch to the kernels.  Nothing here touches particle data on the host.
 #include <algorithm>
-#include <functional>
 #include <cfloat>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <string>
 
@@ -290,8 +290,25 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
     c.nseg = jtiles > 0 ? (int)((jtiles + per - 1) / per) : 1;
     choose_wave_shape(kernel, ni, nj, precision, o.ipl ? o.ipl : (t.ipl > 1 ? t.ipl : 0),
                       o.nseg > 0, &c);
+    c.direct = c.wseg == 1;
     *cfg = c;
     return NBODY_OK;
+}
+
+bool overlap(std::initializer_list<Span> a, std::initializer_list<Span> b) {
+    const std::less<const char *> before;
+    for (const Span &x : a)
+        for (const Span &y : b) {
+            if (!x.p || !y.p) continue;
+            const char *xp = static_cast<const char *>(x.p), *yp = static_cast<const char *>(y.p);
+            if (before(xp, yp + y.bytes) && before(yp, xp + x.bytes)) return true;
+        }
+    return false;
+}
+
+TileCfg without_races(TileCfg cfg, std::initializer_list<Span> out, std::initializer_list<Span> in) {
+    if (cfg.direct && overlap(out, in)) cfg.direct = false;
+    return cfg;
 }
 
 nbody_status choose_cfg(int kernel, int64_t n, int precision, const nbody_opts &o, TileCfg *cfg,
@@ -378,8 +395,10 @@ nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, floa
         return launch_pair_set(cfg, o.precision, pot != nullptr, sa, fa, s);
     }
     if (cfg.sym) return launch_pair_sym(cfg, o.precision, pot != nullptr, pa, fa, s);
-    nbody_status st = launch_pair(cfg, o.precision, pot != nullptr, pa, fa, s);
-    if (st || cfg.wseg == 1) return st;
+    const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(pot, n)},
+                                      {span(pos, 3 * n), span(mass, n)});
+    nbody_status st = launch_pair(run, o.precision, pot != nullptr, pa, fa, s);
+    if (st || run.direct) return st;
     return next && next->centre_part ? launch_finalize_step(o.precision, fa, next->centre_part, s)
                                      : launch_finalize(o.precision, fa, s);
 }
@@ -400,17 +419,18 @@ nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, f
                         ws.part, cfg.npad, centres, itile};
         FinalizeArgs fa{ws.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,     pot,      kick_v,   kick_h};
-        st = launch_pair_tile(cfg, o.precision, pot != nullptr, ta, fa, s);
-        if (st || cfg.wseg == 1) return st;
+        const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(pot, n)},
+                                          {span(pos64, 3 * n), span(mass, n)});
+        st = launch_pair_tile(run, o.precision, pot != nullptr, ta, fa, s);
+        if (st || run.direct) return st;
         return launch_finalize(o.precision, fa, s);
     }
     // One launch, unless it would write positions that another block has yet to read.
-    const double *end = pos64 + 3 * n;
-    auto apart = [&](const double *p, int64_t len) {
-        return !p || std::greater_equal<>()(p, end) || std::less_equal<>()(p + len, pos64);
-    };
-    if (set_shape_f64(cfg, n, o) && apart(acc, 3 * n) && apart(pot, n) && apart(kick_v, 3 * n) &&
-        (!next || (apart(next->x, 3 * n) && apart(next->checkpoint, 3 * n)))) {
+    if (set_shape_f64(cfg, n, o) &&
+        !overlap({span(acc, 3 * n), span(pot, n), span(kick_v, 3 * n),
+                  span(next ? next->x : nullptr, 3 * n),
+                  span(next ? next->checkpoint : nullptr, 3 * n)},
+                 {span(pos64, 3 * n)})) {
         const SetArgs sa{nullptr, pos64, mass, (int)n, eps * eps, cfg.jt,
                          o.centre == NBODY_CENTRE_SYSTEM};
         FinalizeArgs fa{nullptr, 1, 0, (int)n, mass, eps, o.self_pot, acc, pot, kick_v, kick_h};
@@ -531,8 +551,10 @@ nbody_status nbody_force_ij(int64_t ni, const float *pos_i, const float *eps_i, 
     IJPairArgs a{pos_i, pos_i + ni, pos_i + 2 * ni, eps_i, pos_j, pos_j + nj, pos_j + 2 * nj,
                  mass_j, (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
     FinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, pot, nullptr, 0.0};
+    cfg = without_races(cfg, {span(acc, 3 * ni), span(pot, ni)},
+                        {span(pos_i, 3 * ni), span(eps_i, ni), span(pos_j, 3 * nj), span(mass_j, nj)});
     st = launch_pair_ij(cfg, o.precision, pot != nullptr, a, fa, s);
-    if (st || cfg.wseg == 1) return st;
+    if (st || cfg.direct) return st;
     return launch_finalize(o.precision, fa, s);
 }
 

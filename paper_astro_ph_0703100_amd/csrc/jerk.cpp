@@ -74,8 +74,10 @@ nbody_status jerk_core(int64_t n, const float *pos, const float *vel, const floa
         fa.vp = tail->vp;
         fa.dt = tail->dt;
     }
-    nbody_status st = launch_jerk(cfg, o.precision, pot != nullptr, a, fa, s);
-    if (st || cfg.wseg == 1) return st;
+    const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(jerk, 3 * n), span(pot, n)},
+                                      {span(pos, 3 * n), span(vel, 3 * n), span(mass, n)});
+    nbody_status st = launch_jerk(run, o.precision, pot != nullptr, a, fa, s);
+    if (st || run.direct) return st;
     return tail ? launch_jerk_finalize_step(o.precision, fa, tail->xp ? tail->x_part : nullptr,
                                             tail->v_part, s)
                 : launch_jerk_finalize(o.precision, fa, s);
@@ -109,8 +111,10 @@ nbody_status jerk_f64_core(int64_t n, const double *pos64, const double *vel64, 
                        (int)n, cfg.wseg_len, e2, w.part, cfg.npad, cx, cv, itile};
         JerkFinalizeArgs fa{w.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                             acc,    jerk,     pot};
-        st = launch_jerk_tile(cfg, o.precision, pot != nullptr, a, fa, s);
-        if (st || cfg.wseg == 1) return st;
+        const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(jerk, 3 * n), span(pot, n)},
+                                          {span(pos64, 3 * n), span(vel64, 3 * n), span(mass, n)});
+        st = launch_jerk_tile(run, o.precision, pot != nullptr, a, fa, s);
+        if (st || run.direct) return st;
         return launch_jerk_finalize(o.precision, fa, s);
     }
     if (o.centre == NBODY_CENTRE_SYSTEM) {
@@ -290,8 +294,11 @@ nbody_status nbody_force_jerk_ij(int64_t ni, const float *pos_i, const float *ve
                  pos_j, pos_j + nj, pos_j + 2 * nj, mass_j, vel_j, vel_j + nj, vel_j + 2 * nj,
                  (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
     JerkFinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, jerk, pot};
+    cfg = without_races(cfg, {span(acc, 3 * ni), span(jerk, 3 * ni), span(pot, ni)},
+                        {span(pos_i, 3 * ni), span(vel_i, 3 * ni), span(pos_j, 3 * nj),
+                         span(vel_j, 3 * nj), span(mass_j, nj)});
     st = launch_jerk_ij(cfg, o.precision, pot != nullptr, a, fa, s);
-    if (st || cfg.wseg == 1) return st;
+    if (st || cfg.direct) return st;
     return launch_jerk_finalize(o.precision, fa, s);
 }
 

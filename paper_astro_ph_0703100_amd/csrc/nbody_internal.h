@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <functional>
+#include <initializer_list>
 #include <string>
 
 #include "nbody.h"
@@ -63,6 +64,7 @@ struct TileCfg {
     int wseg = 1;    // at most nseg
     int wseg_len = 0;
     int bj = 128;
+    bool direct = false;  // one segment, and the pair launch stores the outputs itself
     int jl = 1;      // lanes per i-particle's j-range: 1 = grid engine, 8..64 = split engine
                      // (then itiles = blocks of 4 * (64 / jl) * ipl i's, nseg = 1)
     // Symmetric engine (sym = 1; jl = 1): block rows of 512 * ipl particles, nb rows,
@@ -398,7 +400,23 @@ struct NextDrift {
 };
 
 // The pair launch stores the outputs itself (no finalize launch).
-inline bool stores_outputs(const TileCfg &c) { return c.jl > 1 || (!c.sym && c.wseg == 1); }
+inline bool stores_outputs(const TileCfg &c) { return c.jl > 1 || c.direct; }
+
+// An array of a call.
+struct Span {
+    const void *p;
+    size_t bytes;
+};
+template <typename T>
+inline Span span(const T *p, int64_t count) {
+    return {p, sizeof(T) * (size_t)count};
+}
+// Does any of `a` share memory with any of `b` (null arrays do not)?
+bool overlap(std::initializer_list<Span> a, std::initializer_list<Span> b);
+// cfg for a call of these outputs and inputs: where they share memory, a grid-engine launch of
+// one segment leaves the outputs to the finalize launch, since its blocks would otherwise store
+// what others have yet to read.
+TileCfg without_races(TileCfg cfg, std::initializer_list<Span> out, std::initializer_list<Span> in);
 
 // Shapes of the whole-set force kernel (force_set.hip): every record in the LDS of one compute
 // unit, a tile's share of a lane one FP32 block.
@@ -453,7 +471,7 @@ struct DeviceInfo {
 };
 const DeviceInfo &device_info();
 
-// Launchers (force.hip).  A grid-engine launch with cfg.wseg == 1 stores the outputs (f)
+// Launchers (force.hip).  A grid-engine launch with cfg.direct stores the outputs (f)
 // itself; otherwise the finalize follows.
 nbody_status launch_pair(const TileCfg &cfg, int precision, bool with_pot, const PairArgs &a,
                          const FinalizeArgs &f, hipStream_t s);
@@ -552,7 +570,7 @@ nbody_status launch_system_step(int nsys, const int64_t *offsets, int64_t total,
 nbody_status launch_batched_convert(int64_t total, const double *pos64, const int32_t *sys_of,
                                     const double *centre, float *pos32, hipStream_t s);
 // Force-jerk-potential kernels and their FP64 finalize (jerk.hip, jerk_tile.hip, jerk_ij.hip);
-// with cfg.wseg == 1 the pair launch stores the outputs itself, as for the force.
+// with cfg.direct the pair launch stores the outputs itself, as for the force.
 nbody_status launch_jerk(const TileCfg &cfg, int precision, bool with_pot, const JerkArgs &a,
                          const JerkFinalizeArgs &f, hipStream_t s);
 nbody_status launch_jerk_finalize(int precision, const JerkFinalizeArgs &a, hipStream_t s);

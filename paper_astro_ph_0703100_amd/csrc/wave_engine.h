@@ -345,11 +345,11 @@ __device__ __forceinline__ void store_sums(const typename Sink::Args &f, double 
 
 // Grid launch: blockIdx.x = group of 64 * IPL i's, blockIdx.y = j-segment of a.seg_len
 // j's (PLAIN: one segment per wave, blockDim.x / 64 of them per block).  Partial planes
-// [segment][word][npad], or, with nseg = 1, the outputs through the Sink.  RUN: for launches
-// of so many waves.
+// [segment][word][npad], or, with `whole` (nseg = 1), the outputs through the Sink.  RUN: for
+// launches of so many waves.
 template <class Op, class Sink, int IPL, int BJ, int MODE, bool FULL, Run RUN>
 __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typename Sink::Args f,
-                                                    int nseg) {
+                                                    int nseg, bool whole) {
     constexpr int NO = Op::kOut;
     constexpr int V = Op::kJWords / 4;
     constexpr int WO = NO * engine::words_per_out<MODE>();
@@ -371,19 +371,19 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
     double ds[IPL][NO];
     if constexpr (MODE == NBODY_PLAIN) {
         wave_work<Op, IPL, BJ, MODE, FULL, RUN>(a, tl, i0, ni, j0, nj, a.eps2, hs, ls, ds);
-        store_plain<Sink, IPL, FULL>(f, i0, n, hs, nseg == 1, part, plane, (size_t)i0);
+        store_plain<Sink, IPL, FULL>(f, i0, n, hs, whole, part, plane, (size_t)i0);
     } else {
         const Range r = block_run<BJ>(nj, wave, waves);
         wave_work<Op, IPL, BJ, MODE, FULL, RUN>(a, tl, i0, ni, j0 + r.j0, r.nj, a.eps2, hs, ls, ds);
         store_sums<Sink, IPL, MODE, FULL>(f, reinterpret_cast<double *>(lds), wave, waves, i0, n,
-                                          hs, ls, ds, nseg == 1, part, plane, (size_t)i0);
+                                          hs, ls, ds, whole, part, plane, (size_t)i0);
     }
 }
 
 // Launch-shape dispatch: IPL up to Op::kMaxIpl, FP32 blocks of 64 or 128 j's (PLAIN sums
 // have no blocks).
 template <class Op, class Sink>
-using WaveFn = void (*)(typename Op::Args, typename Sink::Args, int);
+using WaveFn = void (*)(typename Op::Args, typename Sink::Args, int, bool);
 
 template <class Op, class Sink, int IPL, Run RUN>
 WaveFn<Op, Sink> pick_mode(int bj, int mode, bool full) {
@@ -423,7 +423,7 @@ WaveFn<Op, Sink> pick_wave(int ipl, int bj, int mode, bool full, Run run) {
     return nullptr;
 }
 
-// One launch of cfg's wave shape; ni i-particles.  With cfg.wseg == 1 the outputs are
+// One launch of cfg's wave shape; ni i-particles.  With cfg.direct the outputs are
 // stored by the launch itself (f), otherwise its partial sums await the finalize.
 template <class Op, class Sink>
 nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
@@ -439,7 +439,8 @@ nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
     const int per_block = precision == NBODY_PLAIN ? cfg.wpb : 1;  // segments per block
     const dim3 grid((unsigned)groups,
                     (unsigned)((cfg.wseg + per_block - 1) / per_block));
-    hipLaunchKernelGGL(fn, grid, dim3(64 * cfg.wpb), lds_bytes<Op>(cfg.wpb), s, a, f, cfg.wseg);
+    hipLaunchKernelGGL(fn, grid, dim3(64 * cfg.wpb), lds_bytes<Op>(cfg.wpb), s, a, f, cfg.wseg,
+                       cfg.direct);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }
