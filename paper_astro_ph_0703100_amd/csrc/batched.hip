@@ -8,6 +8,8 @@
 //     segment partials (no j == i term: the pair kernel left it out) and the kick;
 //   * per-system FP64 centres (one block per system, fixed-order reduction) and the
 //     conversion of FP64 positions to FP32 relative to them.
+#include <algorithm>
+
 #include "centre_sum.h"
 #include "gravity.h"
 #include "outputs.h"
@@ -167,9 +169,14 @@ nbody_status launch_batched_pair(int ipl, int jt, int waves, int precision, bool
                        : ipl == 4 ? pick_batched<4>(jt, precision, with_pot)
                                   : nullptr;
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no batched kernel for this shape");
-    if (sc.nitems <= 0) return NBODY_OK;
-    hipLaunchKernelGGL(fn, dim3((unsigned)sc.nitems), dim3(64 * waves),
-                       wave::lds_bytes<Gravity>(waves), s, a, f, sc);
+    // One launch unless the items are more than its threads allow (2^24 items of 4 waves).
+    const int64_t most = kMaxThreads / (64 * waves);
+    for (int64_t first = 0; first < sc.nitems; first += most) {
+        const int64_t count = std::min<int64_t>(most, sc.nitems - first);
+        const BatchSched part{sc.items + first, (int)count, sc.eps, sc.part};
+        hipLaunchKernelGGL(fn, dim3((unsigned)count), dim3(64 * waves),
+                           wave::lds_bytes<Gravity>(waves), s, a, f, part);
+    }
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }

@@ -25,6 +25,8 @@ namespace nbody {
 // Threads per block of every pair kernel: four 64-wide wavefronts, one per SIMD of
 // a compute unit.
 constexpr int kTPB = 256;
+// Most threads a launch can have along one dimension (the dispatch packet's grid size).
+constexpr int64_t kMaxThreads = UINT32_MAX;
 // Largest number of j-segments a launch may split the j range into.
 constexpr int kMaxSeg = 1024;
 // Blocks of the first stage of the FP64 system centre (fixed, so the sum order is too).
