@@ -113,8 +113,14 @@ nbody_status get_workspace(const nbody_opts &o, size_t need, hipStream_t s, void
     return NBODY_OK;
 }
 
-int wave_ipl(int kernel, int precision, int64_t blocks, int ipl) {
-    if (ipl) return std::min(ipl, kernel == KERNEL_FORCE || kernel == KERNEL_BATCHED ? 4 : 2);
+int wave_ipl(int kernel, int precision, int64_t blocks, int64_t waves1, int ipl) {
+    if (ipl) {
+        // At most that many, and as many as leave the chip its waves: N = 2048 in 128-j blocks,
+        // asked for 4, 134.6 us with 4 and 10.4 with 1; 16384 x 8 PLAIN segments 335 and 103 us.
+        int w = std::min(ipl, kernel == KERNEL_FORCE || kernel == KERNEL_BATCHED ? 4 : 2);
+        while (w > 1 && waves1 / w < kFullWaves) w /= 2;
+        return w;
+    }
     const int most = kernel == KERNEL_FORCE ? 4 : 2;
     // More i's per lane save LDS reads (and with them power, which bounds the large
     // systems), fewer leave more waves to spread over the chip.  Force, pair kernel +
@@ -135,9 +141,11 @@ int wave_ipl(int kernel, int precision, int64_t blocks, int ipl) {
 void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ipl, bool nseg_asked,
                        TileCfg *c) {
     c->bj = std::min(c->jt, kBlockJ);
-    const int64_t nb = std::max<int64_t>(1, (nj + c->bj - 1) / c->bj);
-    const int64_t nb128 = std::max<int64_t>(1, (nj + 127) / 128);
-    c->wi = wave_ipl(kernel, precision, (ni + 63) / 64 * nb128, ipl);
+    const int64_t nb = std::max<int64_t>(1, (nj + c->bj - 1) / c->bj);  // FP32 blocks
+    const int64_t pieces = (ni + 63) / 64 * std::max<int64_t>(1, (nj + 127) / 128);
+    c->wi = wave_ipl(kernel, precision, pieces,
+                     (ni + 63) / 64 * (precision == NBODY_PLAIN ? c->nseg : nb), ipl);
+    const int64_t groups = (ni + 64 * c->wi - 1) / (64 * c->wi);
     c->wseg = c->nseg;
     c->wseg_len = c->seg_len;
     c->wpb = 4;
@@ -147,23 +155,38 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
         c->wpb = 1;
         return;
     }
-    if (nseg_asked) return;
-    // j's per wave, in blocks of 128: up to 3, 8 and 6 for ipl 1, 2 and 4 (short waves keep
-    // the last ones busy together, longer ones cost less to start: N = 16384, ipl 1, force
-    // with 2 / 3 / 4 blocks 83.9 / 82.3 / 84.2 us, jerk 154.7 / 151.4 / 157.1 us; ipl 2, jerk
-    // at N = 32768 with 4 / 6 / 8 blocks 573 / 586 / 589 us, at 131072 9471 / 9432 / 9295
-    // us), fewer where there would be under 4 waves per SIMD.
-    const int64_t waves1 = (ni + 64 * c->wi - 1) / (64 * c->wi) * nb128;  // with one block each
-    const int64_t per = c->wi == 1   ? std::max<int64_t>(1, std::min<int64_t>(3, waves1 / 4000))
-                        : c->wi == 2 ? std::max<int64_t>(4, std::min<int64_t>(8, waves1 / 32000))
-                                     : 6;
-    int64_t seg = (nb128 + 4 * per - 1) / (4 * per);
-    // The waves of one block cover every j: one launch, no partial sums.  One block of j's
+    if (nseg_asked) {
+        // At most that many: short segments in multiples of the block's 4 waves (N = 8192, 128
+        // segments of one 64-j block, which leave 3 waves idle: 58.0 us, in blocks of one wave
+        // 40.6, as 32 segments 30 us; 40000, 125 segments of 5 blocks: 547 us, of 8 526 us).
+        const int64_t len = c->seg_len / c->bj;
+        if (len < 16) {
+            const int64_t even = (len + 3) / 4 * 4;
+            c->wseg = (int)((nb + even - 1) / even);
+            c->wseg_len = (int)(even * c->bj);
+        }
+        c->wpb = (int)std::min<int64_t>(4, nb);
+        return;
+    }
+    // j's per wave, in pieces of 128 (of 64 for few j's in FP32 blocks of 64): up to 3, 8 and 6
+    // for ipl 1, 2 and 4 (short waves keep the last ones busy together, longer ones cost less
+    // to start: N = 16384, ipl 1, force with 2 / 3 / 4 pieces 83.9 / 82.3 / 84.2 us, jerk 154.7
+    // / 151.4 / 157.1 us; ipl 2, jerk at N = 32768 with 4 / 6 / 8 pieces 573 / 586 / 589 us, at
+    // 131072 9471 / 9432 / 9295 us), fewer where the waves would not fill the chip.
+    const int64_t piece = c->bj == 64 && nj <= 2048 ? 64 : 128;
+    const int64_t np = std::max<int64_t>(1, (nj + piece - 1) / piece);
+    const int64_t waves1 = groups * np;  // with one piece each
+    const int64_t most = c->wi == 1   ? 3
+                         : c->wi == 2 ? std::max<int64_t>(4, std::min<int64_t>(8, waves1 / 32000))
+                                      : 6;
+    const int64_t per = std::max<int64_t>(1, std::min(most, waves1 / kFullWaves));
+    int64_t seg = (np + 4 * per - 1) / (4 * per);
+    // The waves of one block cover every j: one launch, no partial sums.  One piece of j's
     // more per wave costs the force about as much as the finalize's launch (5 us); a chain of
     // 128 force-jerk or adjoint pairs takes 7.5 us (N = 3000: 18 us with the finalize, 33 us
-    // in one launch of 2 blocks per wave).
-    if (nb128 <= 16 * (per + (kernel == KERNEL_FORCE ? 1 : 0))) {
-        c->wpb = (int)std::min<int64_t>(16, (nb128 + per - 1) / per);
+    // in one launch of 2 pieces per wave).
+    if (np <= 16 * (per + (kernel == KERNEL_FORCE && piece == 128 ? 1 : 0))) {
+        c->wpb = (int)std::min<int64_t>(16, (np + per - 1) / per);
         seg = 1;
     }
     seg = std::min<int64_t>(seg, c->nseg);

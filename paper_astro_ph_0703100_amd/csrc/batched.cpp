@@ -200,14 +200,17 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
 
     // i-records per lane: asked for, else by the work (pieces of 64 i's x 128 j's), as for
     // one system.
-    int64_t blocks1 = 0;
+    int64_t blocks1 = 0, runs1 = 0;
     int64_t &largest = p->largest;
     for (int32_t k = 0; k < nsys; ++k) {
         const int64_t n = h_offsets[k + 1] - h_offsets[k];
         blocks1 += (n + 63) / 64 * ((n + 127) / 128);
+        runs1 += (n + 63) / 64 * ((n + kItemJ - 1) / kItemJ);
         largest = std::max(largest, n);
     }
-    p->wi = wave_ipl(KERNEL_BATCHED, o.precision, blocks1, o.ipl ? o.ipl : (te.ipl > 1 ? te.ipl : 0));
+    p->wi = wave_ipl(KERNEL_BATCHED, o.precision, blocks1,
+                     o.precision == NBODY_PLAIN ? runs1 : blocks1,
+                     o.ipl ? o.ipl : (te.ipl > 1 ? te.ipl : 0));
     // Waves per item: 4, and as many as the largest segment has FP32 blocks, up to 16, where
     // there is too little work to keep 4 waves per SIMD busy with longer runs.
     p->waves = 4;

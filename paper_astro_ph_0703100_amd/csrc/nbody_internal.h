@@ -380,8 +380,10 @@ inline int force_engines(const nbody_opts &o) {
     return o.centre != NBODY_CENTRE_TILE ? kEngineSplit | kEngineSym : 0;
 }
 // i-records per lane of a grid-engine launch (ipl: asked for, or 0) of `blocks` pieces of 64
-// i's x 128 j's.
-int wave_ipl(int kernel, int precision, int64_t blocks, int ipl);
+// i's x 128 j's, that can have `waves1` waves with one record per lane.
+int wave_ipl(int kernel, int precision, int64_t blocks, int64_t waves1, int ipl);
+// Waves that fill the chip (about 4 per SIMD).
+constexpr int64_t kFullWaves = 4000;
 size_t partial_bytes(const TileCfg &c, int precision, int outputs = kForceOutputs);
 size_t align_up(size_t v, size_t a);
 nbody_status check_common(int64_t n, const void *pos, const void *mass, float eps,
