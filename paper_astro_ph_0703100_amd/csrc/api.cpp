@@ -181,12 +181,16 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
                                       : 6;
     const int64_t per = std::max<int64_t>(1, std::min(most, waves1 / kFullWaves));
     int64_t seg = (np + 4 * per - 1) / (4 * per);
-    // The waves of one block cover every j: one launch, no partial sums.  One piece of j's
-    // more per wave costs the force about as much as the finalize's launch (5 us); a chain of
-    // 128 force-jerk or adjoint pairs takes 7.5 us (N = 3000: 18 us with the finalize, 33 us
-    // in one launch of 2 pieces per wave).
-    if (np <= 16 * (per + (kernel == KERNEL_FORCE && piece == 128 ? 1 : 0))) {
-        c->wpb = (int)std::min<int64_t>(16, (np + per - 1) / per);
+    // The waves of one block cover every j: one launch, no partial sums.  Up to 8 waves (N = 600,
+    // 5 waves, jerk 11.8 us, in blocks of 4 with the finalize 14.1; 1000, 8 waves, 13.9 both
+    // ways; 1500, 12 waves, 18.0 and 14.5; 2000, 16 waves, 22.1 and 14.9), up to 16 where there
+    // is a block for every compute unit; there one piece of j's more per wave costs the force
+    // about as much as the finalize's launch (5 us), while on a few of them it cost 15 us (N =
+    // 4000, force with tile centres, 28.1 us instead of 13.8).
+    const bool every_cu = groups >= 256;
+    const int64_t most_waves = every_cu ? 16 : 8;
+    if (np <= most_waves * (per + (every_cu && kernel == KERNEL_FORCE ? 1 : 0))) {
+        c->wpb = (int)std::min(most_waves, (np + per - 1) / per);
         seg = 1;
     }
     seg = std::min<int64_t>(seg, c->nseg);
