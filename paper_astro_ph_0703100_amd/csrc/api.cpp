@@ -151,8 +151,10 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
     c->wpb = 4;
     if (precision == NBODY_PLAIN) {
         // Waves share nothing there: blocks of one wave leave their SIMD as soon as they end
-        // (N = 10007, 40 segments: 33.0 us, with 4 waves per block 36.9 us).
-        c->wpb = 1;
+        // (N = 10007, 40 segments: 33.0 us, with 4 waves per block 36.9 us).  Up to one wave per
+        // SIMD, the waves of a block of 4 have a SIMD each, while single ones can meet on one
+        // (separate sets, 1024 i's x 8192 j's, 512 waves: 13.9 us in ones, 13.3 us in fours).
+        c->wpb = groups * c->nseg <= kLoneWaves && c->nseg >= 4 ? 4 : 1;
         return;
     }
     if (nseg_asked) {

@@ -24,14 +24,7 @@ namespace nbody {
 namespace wave {
 
 constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
-// Waves up to which a launch counts as few (kLone, pipelines with Op::kLone): one per SIMD.
-// One launch of the force on N = 1000 / 2000 / 3000 particles (0.1 / 0.5 / 1.1 waves per
-// SIMD): 6.9 / 7.1 / 8.8 us against 7.4 / 7.6 / 8.6 us; PLAIN, 431 particles against 3452:
-// 10.5 against 11.6 us.  The force-jerk gains under 3 % there and loses 20 % at 1.1 (its
-// interleaved pairs take too many registers), so it has no such variant.
-constexpr int64_t kLoneWaves = 1024;
-
-// Above that and up to this many (5 per SIMD, all there at once, with chains of 128 to 512
+// Above kLoneWaves and up to this many (5 per SIMD, all there at once, with chains of 128 to 512
 // pairs), the waves of a launch should end together (kEven, one record per lane).  N = 4099 /
 // 5000 / 8192 / 9000 / 10007, with the finalize: force-jerk 22.7 / 27.5 / 47.4 / 54.0 / 69.3
 // -> 21.7 / 26.0 / 42.8 / 51.3 / 67.9 us, adjoint 26.3 / 31.2 / 52.2 / 63.0 / 81.3 -> 25.0 /
@@ -107,17 +100,19 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
 }
 
 // The same with one record per lane and few waves on the chip: a lone wave issues an
-// instruction every 4.7 clocks whatever it depends on, so what counts is their number.  Four
-// records are read ahead of their pairs and the compiler interleaves the four pair bodies,
-// which leaves no s_nop (a lone wave: 73 clocks per gravity pair instead of 86).
-template <class Op, bool FULL, bool SELF>
+// instruction every 4.7 clocks whatever it depends on, so what counts is their number.  A
+// records are read ahead of their pairs and the compiler interleaves the A pair bodies, which
+// leaves no s_nop (a lone wave: 73 clocks per gravity pair instead of 86).  A = 8 for PLAIN
+// sums (N = 16384 in one segment: 565 us, with A = 4 612), whose waves are alone on their SIMD;
+// A = 4 where the waves of a block can meet on one (2048 i's and j's, separate sets: 13.5 us,
+// with A = 8 14.3).
+template <class Op, int A, bool FULL, bool SELF>
 __device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
                                           const typename Op::IState (&is)[1], float eps2,
                                           float (&acc)[1][Op::kOut], int lane, int d0) {
     constexpr int W = Op::kJWords;
     constexpr int V = W / 4;
-    constexpr int A = 4;
-    static_assert(kStage % A == 0, "whole groups per stage");
+    static_assert(kStage % (2 * A) == 0, "whole groups per stage");
     float jr[2][A][W];
     auto read = [&](int h, int j0) {
 #pragma unroll
@@ -234,7 +229,8 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
                 constexpr bool SELF = decltype(self)::value;
                 auto run = [&](float(&acc)[IPL][NO]) {
                     if constexpr (RUN == kLone)
-                        lone_pass<Op, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
+                        lone_pass<Op, MODE == NBODY_PLAIN ? 8 : 4, FULL, SELF>(
+                            tl, cnt, is, eps2, acc, lane, d0);
                     else
                         stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
                 };
