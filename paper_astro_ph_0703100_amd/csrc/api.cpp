@@ -403,7 +403,8 @@ F64Scratch f64_scratch_layout(void *ws, int64_t n, const TileCfg &cfg, int preci
 // Pair kernel + FP64 reduction on FP32 structure-of-arrays positions.
 nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, float eps, double *acc,
                             double *pot, const nbody_opts &o, const TileCfg &cfg, void *ws,
-                            double *kick_v, double kick_h, hipStream_t s, const NextDrift *next) {
+                            double *kick_v, double kick_h, hipStream_t s, const NextDrift *next,
+                            bool converted) {
     const float e2 = eps * eps;
     PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.wseg_len, e2, ws, cfg.npad};
     FinalizeArgs fa{ws, cfg.sym ? cfg.nseg : cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
@@ -415,10 +416,7 @@ nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, floa
         fa.checkpoint = next->checkpoint;
     }
     if (cfg.jl > 1) {
-        // With 64 lanes per i-particle both engines add the same in the same order; up to 2048
-        // particles the split engine starts faster (N = 200 / 1000 / 2048: 2.6 / 3.4 / 5.1 us
-        // against 2.7 / 3.9 / 5.1).
-        if (!set_shape(cfg, n) || (cfg.jl == 64 && n <= 2048))
+        if (!(converted && cfg.jl == 32 ? set_shape(cfg, n) : set_shape_f32(cfg, n)))
             return launch_pair_split(cfg, o.precision, pot != nullptr, pa, fa, s);
         const SetArgs sa{pos, nullptr, mass, (int)n, e2, cfg.jt, 0};
         return launch_pair_set(cfg, o.precision, pot != nullptr, sa, fa, s);
@@ -478,7 +476,8 @@ nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, f
     } else {
         if ((st = launch_convert(n, pos64, nullptr, ws.x32, s))) return st;
     }
-    return force_f32_core(n, ws.x32, mass, eps, acc, pot, o, cfg, ws.part, kick_v, kick_h, s, next);
+    return force_f32_core(n, ws.x32, mass, eps, acc, pot, o, cfg, ws.part, kick_v, kick_h, s, next,
+                          true);
 }
 
 }  // namespace nbody

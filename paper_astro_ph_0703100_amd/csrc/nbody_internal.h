@@ -435,6 +435,13 @@ inline bool set_shape(const TileCfg &c, int64_t n) {
     return n <= kSetMax && c.ipl == 1 && (c.jl == 32 || c.jl == 64) && c.jt % (4 * c.jl) == 0 &&
            c.jt / c.jl <= 128;
 }
+// Where it takes FP32 positions.  With 64 lanes per i-particle the split engine adds the same in
+// the same order and starts faster up to 2048 particles (N = 200 / 1000 / 2048: 2.6 / 3.4 / 5.1
+// us against 2.7 / 3.9 / 5.1); with 32 it is the faster one there and below two tiles (N =
+// 2048 and 3000 in tiles of 2048: 5.2 and 10.4 us against 6.8 and 11.2; 4096: 10.5 and 9.9).
+inline bool set_shape_f32(const TileCfg &c, int64_t n) {
+    return set_shape(c, n) && n > 2048 && (c.jl == 64 || n >= 2 * c.jt);
+}
 // It takes FP64 positions there with system-wide centre or none.
 inline bool set_shape_f64(const TileCfg &c, int64_t n, const nbody_opts &o) {
     return set_shape(c, n) && o.centre != NBODY_CENTRE_TILE;
@@ -442,11 +449,12 @@ inline bool set_shape_f64(const TileCfg &c, int64_t n, const nbody_opts &o) {
 
 // Pair kernel + FP64 finalize on FP32 positions [3][n] with the partial sums in `ws`
 // (partial_bytes(cfg, o.precision) bytes); with kick_v set, v += kick_h * a follows, and
-// with `next` the next step's start (not with potentials).
+// with `next` the next step's start (not with potentials).  converted: pos are converted FP64
+// positions, whose sums are those of the launch that takes the FP64 positions themselves.
 nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, float eps, double *acc,
                             double *pot, const nbody_opts &o, const TileCfg &cfg, void *ws,
                             double *kick_v, double kick_h, hipStream_t s,
-                            const NextDrift *next = nullptr);
+                            const NextDrift *next = nullptr, bool converted = false);
 
 // Scratch layout of one FP64-position force evaluation: partial sums, FP32 relative
 // positions [3][n] (or, with per-i-tile centres, the tile centres), and the partials of
