@@ -233,7 +233,7 @@ size_t centre_scratch_bytes() { return sizeof(double) * 3 * kCentreBlocks; }
 nbody_status launch_centred_convert(int64_t n, const double *pos64, double *scratch,
                                     float *pos32, hipStream_t s) {
     if (n <= 0) return NBODY_OK;
-    if (n <= kSelfCentre) return launch_self_centred_convert(n, pos64, pos32, nullptr, nullptr, s);
+    if (n <= kSelfCentreOne) return launch_self_centred_convert(n, pos64, pos32, nullptr, nullptr, s);
     hipLaunchKernelGGL(centre_partial_kernel, dim3(kCentreBlocks), dim3(256), 0, s, n, pos64, scratch);
     NBODY_HIP_CHECK(hipGetLastError());
     hipLaunchKernelGGL(centred_convert_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,

@@ -525,6 +525,10 @@ nbody_status launch_convert(int64_t n, const double *pos64, const double *centre
 // launch_centred_convert in one launch, for n <= kSelfCentre: every block sums the centre for
 // itself, in the same order.  With a second pair of arrays, both.
 constexpr int64_t kSelfCentre = 8192;
+// Up to where it is the faster way for one array alone (adjoint from FP64 positions, N = 2048 /
+// 3000 / 4096 / 5000 / 8192: 29.2 / 26.2 / 25.0 / 35.5 / 56.6 us, with two launches 30.3 / 26.6 /
+// 24.7 / 34.6 / 54.1).
+constexpr int64_t kSelfCentreOne = 4096;
 nbody_status launch_self_centred_convert(int64_t n, const double *a64, float *a32, const double *b64,
                                          float *b32, hipStream_t s);
 // launch_centred_convert_ready of two arrays in one launch.
