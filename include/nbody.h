@@ -399,7 +399,8 @@ NBODY_API nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_
                                                  const nbody_opts *opts, nbody_plan **out);
 NBODY_API void nbody_plan_destroy(nbody_plan *plan);
 /* info[0..8): nsys, total particles, work items, blocks of the pair launch, pairs (sum N_k^2),
- * pairs including tile padding, ipl, jtile. */
+ * pairs including the padding of i-groups and of the last j's, i-particles per lane of that
+ * launch, jtile. */
 NBODY_API nbody_status nbody_plan_info(const nbody_plan *plan, int64_t *info);
 
 /* Forces and potentials of every system.  pos float [3][total], mass float [total],

@@ -19,7 +19,7 @@ struct nbody_plan {
     int nsys = 0;
     int64_t total = 0;
     nbody_opts opts{};
-    int ipl = 4, jt = 256;
+    int jt = 256;
     int wi = 1;          // i-records per lane of the launch
     int waves = 4;       // waves per work item
     int nitems = 0;
@@ -190,7 +190,6 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
     p->nsys = nsys;
     p->total = total;
     p->opts = o;
-    p->ipl = ipl;
     p->jt = jt;
     hipError_t e = hipGetDevice(&p->device);
     if (e != hipSuccess) {
@@ -233,6 +232,7 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
         int64_t part;
     };
     const int64_t itile = (int64_t)64 * p->wi;
+    const int64_t unroll = wave_unroll(p->wi);
     const int wo = 4 * (o.precision == NBODY_PLAIN ? 1 : 2);  // words per (i, segment)
     const int64_t tiles_per_seg = std::max<int64_t>(1, item_j / jt);
     std::vector<Segment> segments;
@@ -282,7 +282,7 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
             w.npad = npad[k];
             w.whole = nseg[k] == 1;
             sorted.push_back(w);
-            p->padded_pairs += itile * ((sg.nj + 7) / 8 * 8);
+            p->padded_pairs += itile * ((sg.nj + unroll - 1) / unroll * unroll);
         }
     }
     p->nitems = (int)sorted.size();
@@ -330,7 +330,7 @@ nbody_status nbody_plan_info(const nbody_plan *plan, int64_t *info) {
     info[3] = plan->nitems;
     info[4] = plan->pairs;
     info[5] = plan->padded_pairs;
-    info[6] = plan->ipl;
+    info[6] = plan->wi;
     info[7] = plan->jt;
     return NBODY_OK;
 }

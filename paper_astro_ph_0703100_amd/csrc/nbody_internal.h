@@ -382,6 +382,8 @@ inline int force_engines(const nbody_opts &o) {
 // i-records per lane of a grid-engine launch (ipl: asked for, or 0) of `blocks` pieces of 64
 // i's x 128 j's, that can have `waves1` waves with one record per lane.
 int wave_ipl(int kernel, int precision, int64_t blocks, int64_t waves1, int ipl);
+// Records that a wave's pass takes per loop iteration (the last one is padded).
+constexpr int wave_unroll(int ipl) { return ipl == 1 ? 16 : 8; }
 // Waves up to which a launch counts as few (the wave engine's kLone, pipelines with Op::kLone):
 // one per SIMD.  One launch of the force on N = 1000 / 2000 / 3000 particles (0.1 / 0.5 / 1.1 waves per
 // SIMD): 6.9 / 7.1 / 8.8 us against 7.4 / 7.6 / 8.6 us; PLAIN, 431 particles against 3452:

@@ -52,7 +52,7 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
                                            float (&acc)[IPL][Op::kOut], int lane, int d0) {
     constexpr int W = Op::kJWords;
     constexpr int V = W / 4;
-    constexpr int U = IPL == 1 ? 16 : 8;  // records per loop iteration (padding adds zero)
+    constexpr int U = wave_unroll(IPL);  // (padding adds zero)
     static_assert(kStage % U == 0, "whole iterations per stage");
     float4 cur[V], nxt[V];
 #pragma unroll

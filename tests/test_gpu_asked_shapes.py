@@ -88,3 +88,25 @@ def test_lanes_of_small_systems(precision, jtile, n):
     buf, p = x64.clone(), torch.empty_like(pot)
     api.force_f64(buf, mm, EPS, out=(buf, p), **kw)
     assert torch.equal(buf, acc) and torch.equal(p, pot)
+
+
+@pytest.mark.parametrize("sizes,ipl,want,per_iteration", [
+    ([300, 1000], 0, 1, 16), ([300, 1000], 8, 1, 16), ([20000, 33, 7], 2, 2, 8),
+    ([40000, 64], 8, 4, 8)])
+def test_plan_info_describes_the_launch(sizes, ipl, want, per_iteration):
+    # Records per lane of the launch (an asked number is an upper limit), one block per item,
+    # and pairs with the i-groups filled and the j's in whole iterations.
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    plan = api.BatchPlan(off, ipl=ipl, jtile=128)
+    info = plan.info()
+    plan.close()
+    assert info["ipl"] == want and info["blocks"] == info["items"]
+    group = 64 * want
+    pairs = items = 0
+    for n in sizes:
+        segs = -(-n // 4096)
+        per = -(-(-(-n // 128)) // segs) * 128
+        lens = [min(per, n - s) for s in range(0, n, per)]
+        items += -(-n // group) * len(lens)
+        pairs += -(-n // group) * group * sum(-(-j // per_iteration) * per_iteration for j in lens)
+    assert info["items"] == items and info["padded_pairs"] == pairs
