@@ -95,11 +95,14 @@ typedef struct nbody_opts {
 } nbody_opts;
 
 /* Launch shapes.  Three pair engines evaluate the same sums:
- *   - the grid engine (jlanes = 1): each wavefront holds 64 * ipl i-particles (ipl at
- *     most 4, jerk and adjoint 2) against runs of j's in FP32 blocks of min(jtile, 128)
- *     records; the partial sums of up to nseg j-segments go to scratch memory and a
- *     second kernel adds them per particle in FP64 (the paper's i-parallel FORCE-LOOP,
- *     Sec. 2.2).  With one segment the launch stores the outputs itself;
+ *   - the grid engine (jlanes = 1): each wavefront holds 64 * ipl i-particles (at most 4,
+ *     jerk and adjoint 2, and as many as leave the chip its wavefronts; 0: by the size of
+ *     the launch) against runs of j's in FP32 blocks of min(jtile, 128) records; the
+ *     partial sums of nseg j-segments (0: by size; at most that many: segments of few
+ *     blocks are made longer, PLAIN excepted) go to scratch memory and a second kernel
+ *     adds them per particle in FP64 (the paper's i-parallel FORCE-LOOP, Sec. 2.2).  With
+ *     one segment the launch stores the outputs itself.  Per-tile centres are those of
+ *     256 * max(ipl, 1) consecutive particles;
  *   - the split engine (jlanes = 8, 16, 32 or 64; ipl = 1 or 2; jtile = 256, 512,
  *     1024, or 2048 with jlanes >= 32; the adjoint: 256 or 512; nseg must be 0): for
  *     systems too small to
@@ -431,9 +434,11 @@ NBODY_API nbody_status nbody_graph_create_leapfrog_batched(const nbody_plan *pla
  * Launch-shape table.  Shapes (i-particles per lane, j-tile, j-segments) are looked
  * up per kernel, precision mode and size bucket floor(log2 n) (batched: mean system
  * size); entries not set use built-in defaults; explicit opts fields override both.
- * The autotuner (tune.py) measures shapes and writes the JSON file these functions
- * read and write.  nseg = 0 lets the library choose the j-split from n.  The built-in
- * defaults use the split engine for the force below 2^13 particles.
+ * An entry runs the launch that the same values in opts run; in a grid-engine entry
+ * ipl = 0 and nseg = 0 leave those to the size of the launch.  The autotuner (tune.py)
+ * measures shapes and writes the JSON file these functions read and write.  The built-in
+ * defaults use the split engine for the force below 2^13 particles, and leave ipl and nseg
+ * of the grid engine to the size (nbody_tune_get then gives 1 and 0).
  * ---------------------------------------------------------------------------- */
 #define NBODY_KERNEL_FORCE 0
 #define NBODY_KERNEL_VJP 1

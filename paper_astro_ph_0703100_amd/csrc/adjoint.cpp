@@ -41,8 +41,8 @@ nbody_status vjp_f32_core(int64_t n, const float *pos, const float *mass, float 
                           const ReverseStep *step = nullptr) {
     const float e2 = eps * eps;
     VjpArgs va{pos,   pos + n, pos + 2 * n, mass, g_acc, g_acc + n, g_acc + 2 * n,
-               g_pot, (int)n,  cfg.wseg_len, e2,  part,  cfg.npad};
-    VjpFinalizeArgs fa{part,      cfg.wseg, cfg.npad,           (int)n, g_pot,
+               g_pot, (int)n,  cfg.seg_len, e2,  part,  cfg.npad};
+    VjpFinalizeArgs fa{part,      cfg.nseg, cfg.npad,           (int)n, g_pot,
                        grad_pos,  grad_mass, accumulate ? 1 : 0, g_acc};
     if (cfg.jl > 1) return launch_vjp_split(cfg, o.precision, va, grad_mass != nullptr, fa, s);
     const TileCfg run = without_races(
@@ -74,8 +74,8 @@ nbody_status vjp_f64_core(int64_t n, const double *pos64, const float *mass, flo
         if ((st = launch_tile_centres(n, itile, pos64, centres, s))) return st;
         const float e2 = eps * eps;
         VjpTileArgs va{pos64, pos64 + n, pos64 + 2 * n, mass, g_acc, g_acc + n, g_acc + 2 * n,
-                       g_pot, (int)n, cfg.wseg_len, e2, ws.part, cfg.npad, centres, itile};
-        VjpFinalizeArgs fa{ws.part,  cfg.wseg, cfg.npad,           (int)n, g_pot,
+                       g_pot, (int)n, cfg.seg_len, e2, ws.part, cfg.npad, centres, itile};
+        VjpFinalizeArgs fa{ws.part,  cfg.nseg, cfg.npad,           (int)n, g_pot,
                            grad_pos, grad_mass, accumulate ? 1 : 0, g_acc};
         const TileCfg run = without_races(
             cfg, {span(grad_pos, 3 * n), span(grad_mass, n)},

@@ -137,7 +137,8 @@ int wave_ipl(int kernel, int precision, int64_t blocks, int64_t waves1, int ipl)
 
 // Launch of the grid engine for a shape whose ipl, jt and nseg are chosen: what the result
 // depends on (the FP32 blocks of min(jt, 128) j's; PLAIN: the segments) stays, the rest is
-// split for the chip.  ipl: asked for, or 0; nseg_asked: c->nseg is the caller's.
+// split for the chip.  ipl: asked for (by the caller or the table), or 0; nseg_asked: so is
+// c->nseg, otherwise it is an upper limit.
 void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ipl, bool nseg_asked,
                        TileCfg *c) {
     c->bj = std::min(c->jt, kBlockJ);
@@ -146,8 +147,6 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
     c->wi = wave_ipl(kernel, precision, pieces,
                      (ni + 63) / 64 * (precision == NBODY_PLAIN ? c->nseg : nb), ipl);
     const int64_t groups = (ni + 64 * c->wi - 1) / (64 * c->wi);
-    c->wseg = c->nseg;
-    c->wseg_len = c->seg_len;
     c->wpb = 4;
     if (precision == NBODY_PLAIN) {
         // Waves share nothing there: blocks of one wave leave their SIMD as soon as they end
@@ -164,8 +163,8 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
         const int64_t len = c->seg_len / c->bj;
         if (len < 16) {
             const int64_t even = (len + 3) / 4 * 4;
-            c->wseg = (int)((nb + even - 1) / even);
-            c->wseg_len = (int)(even * c->bj);
+            c->nseg = (int)((nb + even - 1) / even);
+            c->seg_len = (int)(even * c->bj);
         }
         c->wpb = (int)std::min<int64_t>(4, nb);
         return;
@@ -197,8 +196,8 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
     }
     seg = std::min<int64_t>(seg, c->nseg);
     const int64_t len = (nb + seg - 1) / seg;
-    c->wseg_len = (int)(len * c->bj);
-    c->wseg = (int)((nb + len - 1) / len);
+    c->seg_len = (int)(len * c->bj);
+    c->nseg = (int)((nb + len - 1) / len);
 }
 
 // Launch shape for ni i-particles against nj j-particles: explicit options first, then
@@ -263,7 +262,6 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
         *cfg = c;
         return NBODY_OK;
     }
-    const bool split_ok = (engines & kEngineSplit) != 0;
     const int jl = o.jlanes ? o.jlanes : (explicit_shape || o.symmetric == 2 ? 1 : t.jl);
     if (jl > 1) {
         // Split engine: one launch of ceil(ni / i-per-block) blocks, no j-segments.
@@ -285,10 +283,8 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
         *cfg = c;
         return NBODY_OK;
     }
-    (void)split_ok;
     if (t.jl > 1 || t.sym) t = TuneEntry{1, 256, 0, 1};  // the table's shape is another engine's
-    if (t.jl > 1) t = TuneEntry{1, 256, 0, 1};  // the table's split shape does not apply
-    c.ipl = o.ipl ? o.ipl : t.ipl;
+    c.ipl = o.ipl ? o.ipl : std::max(t.ipl, 1);
     c.jt = o.jtile ? o.jtile : t.jt;
     if (!(c.ipl == 1 || c.ipl == 2 || c.ipl == 4 || c.ipl == 8))
         return set_error(NBODY_EINVAL, "ipl must be 1, 2, 4 or 8");
@@ -317,9 +313,9 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
     const int64_t per = jtiles > 0 ? (jtiles + nseg - 1) / nseg : 1;  // tiles per segment
     c.seg_len = (int)(per * c.jt);
     c.nseg = jtiles > 0 ? (int)((jtiles + per - 1) / per) : 1;
-    choose_wave_shape(kernel, ni, nj, precision, o.ipl ? o.ipl : (t.ipl > 1 ? t.ipl : 0),
-                      o.nseg > 0, &c);
-    c.direct = c.wseg == 1;
+    choose_wave_shape(kernel, ni, nj, precision, o.ipl ? o.ipl : t.set ? t.ipl : 0,
+                      o.nseg > 0 || (ni == nj && t.nseg > 0), &c);
+    c.direct = c.nseg == 1;
     *cfg = c;
     return NBODY_OK;
 }
@@ -406,8 +402,8 @@ nbody_status force_f32_core(int64_t n, const float *pos, const float *mass, floa
                             double *kick_v, double kick_h, hipStream_t s, const NextDrift *next,
                             bool converted) {
     const float e2 = eps * eps;
-    PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.wseg_len, e2, ws, cfg.npad};
-    FinalizeArgs fa{ws, cfg.sym ? cfg.nseg : cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+    PairArgs pa{pos, pos + n, pos + 2 * n, mass, (int)n, cfg.seg_len, e2, ws, cfg.npad};
+    FinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                     acc, pot, kick_v, kick_h};
     if (next) {
         fa.drift_x = next->x;
@@ -442,9 +438,9 @@ nbody_status force_f64_core(int64_t n, const double *pos64, const float *mass, f
         double *centres = reinterpret_cast<double *>(ws.x32);
         if ((st = launch_tile_centres(n, itile, pos64, centres, s))) return st;
         const float e2 = eps * eps;
-        TilePairArgs ta{pos64, pos64 + n, pos64 + 2 * n, mass, (int)n, cfg.wseg_len, e2,
+        TilePairArgs ta{pos64, pos64 + n, pos64 + 2 * n, mass, (int)n, cfg.seg_len, e2,
                         ws.part, cfg.npad, centres, itile};
-        FinalizeArgs fa{ws.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+        FinalizeArgs fa{ws.part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,     pot,      kick_v,   kick_h};
         const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(pot, n)},
                                           {span(pos64, 3 * n), span(mass, n)});
@@ -577,8 +573,8 @@ nbody_status nbody_force_ij(int64_t ni, const float *pos_i, const float *eps_i, 
     void *ws = nullptr;
     if ((st = get_workspace(o, partial_bytes(cfg, o.precision), s, &ws))) return st;
     IJPairArgs a{pos_i, pos_i + ni, pos_i + 2 * ni, eps_i, pos_j, pos_j + nj, pos_j + 2 * nj,
-                 mass_j, (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
-    FinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, pot, nullptr, 0.0};
+                 mass_j, (int)ni, (int)nj, cfg.seg_len, e2, ws, cfg.npad};
+    FinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, pot, nullptr, 0.0};
     cfg = without_races(cfg, {span(acc, 3 * ni), span(pot, ni)},
                         {span(pos_i, 3 * ni), span(eps_i, ni), span(pos_j, 3 * nj), span(mass_j, nj)});
     st = launch_pair_ij(cfg, o.precision, pot != nullptr, a, fa, s);

@@ -178,9 +178,10 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
     if (total > INT32_MAX / 2) return set_error(NBODY_EINVAL, "total particles must be < 2^30");
 
     TuneEntry te = tuned_shape(KERNEL_BATCHED, o.precision, total / std::max<int64_t>(1, nsys), 0);
-    const int ipl = o.ipl ? o.ipl : te.ipl;
+    // i-records per lane asked for, by the caller or the table; 0: by size, as the items are.
+    const int ipl = o.ipl ? o.ipl : te.set ? te.ipl : 0;
     const int jt = o.jtile ? o.jtile : te.jt;
-    if (!(ipl == 1 || ipl == 2 || ipl == 4 || ipl == 8))
+    if (!(ipl == 0 || ipl == 1 || ipl == 2 || ipl == 4 || ipl == 8))
         return set_error(NBODY_EINVAL, "ipl must be 1, 2, 4 or 8");
     if (!(jt == 64 || jt == 128 || jt == 256 || jt == 512))
         return set_error(NBODY_EINVAL, "jtile must be 64, 128, 256 or 512");
@@ -208,21 +209,20 @@ nbody_status nbody_plan_create_batched(int32_t nsys, const int64_t *h_offsets,
         largest = std::max(largest, n);
     }
     p->wi = wave_ipl(KERNEL_BATCHED, o.precision, blocks1,
-                     o.precision == NBODY_PLAIN ? runs1 : blocks1,
-                     o.ipl ? o.ipl : (te.ipl > 1 ? te.ipl : 0));
+                     o.precision == NBODY_PLAIN ? runs1 : blocks1, ipl);
     // Waves per item: 4, and as many as the largest segment has FP32 blocks, up to 16, where
     // there is too little work to keep 4 waves per SIMD busy with longer runs.
     p->waves = 4;
     if (o.precision == NBODY_PLAIN) {
         p->waves = 1;
-    } else if (!o.ipl && !o.jtile && blocks1 < 50000) {
+    } else if (!ipl && blocks1 < 50000) {
         const int64_t nb = (std::min(largest, kItemJ) + 127) / 128;
         p->waves = (int)std::max<int64_t>(4, std::min<int64_t>(16, nb));
     }
 
-    // j's per item.  With an open shape, and enough work to fill the chip with long items, the
+    // j's per item.  With the shape by size, and enough work to fill the chip with long items, the
     // largest systems of 2^14 particles stay whole as well: no partial sums, no finalize.
-    const bool open_shape = !o.ipl && !o.jtile && o.precision != NBODY_PLAIN;
+    const bool open_shape = !ipl && o.precision != NBODY_PLAIN;
     const int64_t item_j = open_shape && blocks1 >= 1000000 ? 4 * kItemJ : kItemJ;
 
     // The partial-sum layout, then the items: (system, j-segment) pairs in decreasing order

@@ -64,8 +64,8 @@ nbody_status jerk_core(int64_t n, const float *pos, const float *vel, const floa
                        const HermiteTail *tail = nullptr) {
     const float e2 = eps * eps;
     JerkArgs a{pos, pos + n, pos + 2 * n, mass, vel, vel + n, vel + 2 * n,
-               (int)n, cfg.wseg_len, e2, part, cfg.npad};
-    JerkFinalizeArgs fa{part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+               (int)n, cfg.seg_len, e2, part, cfg.npad};
+    JerkFinalizeArgs fa{part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                         acc,  jerk,     pot};
     if (tail) {
         fa.x = tail->x;
@@ -108,8 +108,8 @@ nbody_status jerk_f64_core(int64_t n, const double *pos64, const double *vel64, 
         if ((st = launch_tile_centres(n, itile, vel64, cv, s))) return st;
         const float e2 = eps * eps;
         JerkTileArgs a{pos64, pos64 + n, pos64 + 2 * n, mass, vel64, vel64 + n, vel64 + 2 * n,
-                       (int)n, cfg.wseg_len, e2, w.part, cfg.npad, cx, cv, itile};
-        JerkFinalizeArgs fa{w.part, cfg.wseg, cfg.npad, (int)n, mass, eps, o.self_pot,
+                       (int)n, cfg.seg_len, e2, w.part, cfg.npad, cx, cv, itile};
+        JerkFinalizeArgs fa{w.part, cfg.nseg, cfg.npad, (int)n, mass, eps, o.self_pot,
                             acc,    jerk,     pot};
         const TileCfg run = without_races(cfg, {span(acc, 3 * n), span(jerk, 3 * n), span(pot, n)},
                                           {span(pos64, 3 * n), span(vel64, 3 * n), span(mass, n)});
@@ -292,8 +292,8 @@ nbody_status nbody_force_jerk_ij(int64_t ni, const float *pos_i, const float *ve
     if ((st = get_workspace(o, jerk_partial_bytes(cfg, o.precision), s, &ws))) return st;
     JerkIJArgs a{pos_i, pos_i + ni, pos_i + 2 * ni, vel_i, vel_i + ni, vel_i + 2 * ni,
                  pos_j, pos_j + nj, pos_j + 2 * nj, mass_j, vel_j, vel_j + nj, vel_j + 2 * nj,
-                 (int)ni, (int)nj, cfg.wseg_len, e2, ws, cfg.npad};
-    JerkFinalizeArgs fa{ws, cfg.wseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, jerk, pot};
+                 (int)ni, (int)nj, cfg.seg_len, e2, ws, cfg.npad};
+    JerkFinalizeArgs fa{ws, cfg.nseg, cfg.npad, (int)ni, nullptr, eps, 0, acc, jerk, pot};
     cfg = without_races(cfg, {span(acc, 3 * ni), span(jerk, 3 * ni), span(pot, ni)},
                         {span(pos_i, 3 * ni), span(vel_i, 3 * ni), span(pos_j, 3 * nj),
                          span(vel_j, 3 * nj), span(mass_j, nj)});

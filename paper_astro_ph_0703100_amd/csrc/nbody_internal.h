@@ -55,16 +55,14 @@ inline int partial_words(int precision, int outputs = kForceOutputs) {
 struct TileCfg {
     int ipl = 4;     // i-particles per lane of an i-tile (kTPB * ipl particles)
     int jt = 256;    // j-particles per LDS tile
-    int nseg = 1;    // j-segments the scratch holds (PLAIN: the segments summed)
-    int seg_len = 0; // j's per segment, a multiple of jt
+    int nseg = 1;    // j-segments
+    int seg_len = 0; // j's per segment
     int itiles = 0;  // i-tiles
     int npad = 0;    // itiles * kTPB * ipl
-    // Launch of the grid engine (wave_engine.h): wseg segments of wseg_len j's, wpb waves
-    // per block, each holding 64 * wi i-particles, FP32 blocks of bj j's.
+    // Launch of the grid engine (wave_engine.h): wpb waves per block, each holding 64 * wi
+    // i-particles, FP32 blocks of bj j's.
     int wi = 1;
     int wpb = 4;
-    int wseg = 1;    // at most nseg
-    int wseg_len = 0;
     int bj = 128;
     bool direct = false;  // one segment, and the pair launch stores the outputs itself
     int jl = 1;      // lanes per i-particle's j-range: 1 = grid engine, 8..64 = split engine

@@ -6,7 +6,7 @@
 //      "jlanes": 1, "symmetric": 0}, ...]}
 // kernel: 0 force, 1 adjoint, 2 batched, 3 force-jerk; precision: 0 plain, 1 FP64-reduced,
 // 2 compensated; bucket: floor(log2 n) of the particle count (batched: mean system
-// size); jlanes (1 if absent) selects the grid (1) or split (8..64) engine, symmetric
+// size); ipl 0 and nseg 0: chosen from n (grid engine); jlanes (1 if absent) selects the grid (1) or split (8..64) engine, symmetric
 // (0 if absent) the symmetric engine.  Unknown keys are ignored.
 #include "tuning.h"
 
@@ -29,8 +29,8 @@ TuneEntry g_tab[KERNEL_COUNT][3][kBuckets];
 
 TuneEntry builtin(int kernel, int64_t n, int engines) {
     const bool split_ok = (engines & kEngineSplit) != 0;
-    // ipl 1 leaves the i-records per lane of a grid-engine launch to the size of the launch,
-    // nseg 0 the j-split.  Below 2^13 particles the force's single launches (split and
+    // Grid shapes: i-tiles of 256, the records per lane and the j-split by the size of the
+    // launch.  Below 2^13 particles the force's single launches (split and
     // whole-set engines) are faster (N = 2000: 5.1 against 7.1 us, one launch each);
     // from 2^13 on the grid engine is (N = 8192: 24.4 us, 25.8 us in one launch).
     // The 2048-record tile (64 KB of LDS, two blocks per CU) only while every block fits
@@ -63,7 +63,7 @@ bool valid_shape(int kernel, const TuneEntry &e) {
                (e.ipl == 1 || e.ipl == 2 || e.ipl == 4) && (e.jt == 64 || e.jt == 128) &&
                e.nseg >= 0 && e.nseg <= kMaxSeg;
     if (e.jl == 1)
-        return (e.ipl == 1 || e.ipl == 2 || e.ipl == 4 || e.ipl == 8) &&
+        return (e.ipl == 0 || e.ipl == 1 || e.ipl == 2 || e.ipl == 4 || e.ipl == 8) &&
                (e.jt == 64 || e.jt == 128 || e.jt == 256 || e.jt == 512) && e.nseg >= 0 &&
                e.nseg <= kMaxSeg;
     // Split engine: force and adjoint only; the adjoint's 32-byte j-records cap the
@@ -101,6 +101,7 @@ void set_tuned_shape(int kernel, int precision, int64_t n, const TuneEntry &e) {
     std::lock_guard<std::mutex> lk(g_mu);
     const int b = size_bucket(n);
     g_tab[kernel][precision][b] = e;
+    g_tab[kernel][precision][b].set = true;
     g_set[kernel][precision][b] = true;
 }
 
@@ -213,6 +214,7 @@ nbody_status nbody_tune_load(const char *path) {
     std::lock_guard<std::mutex> lk(g_mu);
     for (const Parsed &p : entries) {
         g_tab[p.kernel][p.precision][p.bucket] = p.e;
+        g_tab[p.kernel][p.precision][p.bucket].set = true;
         g_set[p.kernel][p.precision][p.bucket] = true;
     }
     return NBODY_OK;

@@ -9,12 +9,15 @@ namespace nbody {
 enum TuneKernel { KERNEL_FORCE = 0, KERNEL_VJP = 1, KERNEL_BATCHED = 2, KERNEL_JERK = 3, KERNEL_COUNT = 4 };
 
 struct TuneEntry {
-    int ipl;      // i-particles per lane
+    int ipl;      // i-particles per lane (grid engine: 0 = chosen from n, in i-tiles of 256)
     int jt;       // j-tile
     int nseg;     // j-segments, 0 = chosen from n (grid engine); symmetric engine: segments
                   // of the longest block row, 0 = chosen from n
     int jl = 1;   // lanes per i-particle's j-range: 1 = grid engine, 8..64 = split engine
     int sym = 0;  // 1: symmetric engine (jl = 1)
+    // The table's entry, which runs as the same shape in a call's options would; in a built-in
+    // grid shape ipl and nseg are chosen from n.
+    bool set = false;
 };
 
 // Engines a caller has kernels for besides the grid engine (bit mask).

@@ -427,17 +427,17 @@ nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
     const int64_t groups = (ni + 64 * cfg.wi - 1) / (64 * cfg.wi);
     int wpb = cfg.wpb;
     while (groups * 64 * wpb > kMaxThreads) wpb /= 2;  // from 2^28 i's on
-    const int64_t waves = groups * cfg.wseg * (precision == NBODY_PLAIN ? 1 : wpb);
+    const int64_t waves = groups * cfg.nseg * (precision == NBODY_PLAIN ? 1 : wpb);
     auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full,
                                   waves <= kLoneWaves   ? kLone
                                   : waves <= kEvenWaves ? kEven
                                                         : kMany);
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no pair kernel for this ipl/jtile/precision");
-    if (ni <= 0 || cfg.wseg <= 0) return NBODY_OK;
+    if (ni <= 0 || cfg.nseg <= 0) return NBODY_OK;
     const int per_block = precision == NBODY_PLAIN ? wpb : 1;  // segments per block
     const dim3 grid((unsigned)groups,
-                    (unsigned)((cfg.wseg + per_block - 1) / per_block));
-    hipLaunchKernelGGL(fn, grid, dim3(64 * wpb), lds_bytes<Op>(wpb), s, a, f, cfg.wseg,
+                    (unsigned)((cfg.nseg + per_block - 1) / per_block));
+    hipLaunchKernelGGL(fn, grid, dim3(64 * wpb), lds_bytes<Op>(wpb), s, a, f, cfg.nseg,
                        cfg.direct);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;

@@ -1,8 +1,8 @@
 """Autotuner: measure launch shapes on the GPU and write the library's tuning table.
 
-For each workload it sweeps i-particles per lane (1, 2, 4, 8), j-tile (64 .. 512)
+For each workload it sweeps i-particles per lane (by size, 1, 2, 4), j-tile (64 .. 512)
 and, for the single-system kernels (force, force-jerk, adjoint), the number of
-j-segments of the grid engine; for the force and the adjoint up to 2^15 particles
+j-segments of the grid engine (0: by size); for the force and the adjoint up to 2^15 particles
 also the split engine's shapes (lanes per i-particle 8 .. 64, i-particles per lane 1
 or 2, j-tile 256 .. 2048).  Every shape is timed with HIP events on the launch stream
 (median of ``reps`` runs, after a warm-up call): the force and the adjoint as HIP graphs
@@ -28,7 +28,7 @@ import torch
 from . import _lib, api, ics
 from .metrics import rel_errors
 
-IPLS = (1, 2, 4, 8)
+IPLS = (0, 1, 2, 4)  # 0: by the size of the launch (8 would run as 4)
 JTILES = (64, 128, 256, 512)
 SEGS = (0, 4, 8, 10, 12, 16, 20, 24, 32, 40, 48, 64, 96, 128)
 # Split engine: (ipl, jlanes, jtile); the adjoint's 32-byte j-records stop at 512.
@@ -274,11 +274,9 @@ def main(argv=None):
 
     _lib.load()
     only = [k for k in args.only.split(",") if k]
-    if only and os.path.exists(args.out):
-        _lib.nbody_tune_reset()
-        _lib.nbody_tune_load(args.out)  # keep the entries that are not re-tuned
-    else:
-        _lib.nbody_tune_reset()  # measure against the built-in shapes, not an old table
+    # Against the built-in shapes: a field that a swept shape leaves open would otherwise take
+    # the old table's value.
+    _lib.nbody_tune_reset()
     rep = open(args.report, "w") if args.report else None
 
     def log(row):
@@ -311,15 +309,18 @@ def main(argv=None):
         if best is None:
             print("tune: no shape passed the parity gate for %s/%s" % (kernel, prec), file=sys.stderr)
             continue
-        _lib.nbody_tune_set(_lib.KERNELS[kernel], _lib.PRECISIONS[prec], best["n"], best["ipl"],
-                            best["jtile"], best["nseg"], best.get("jlanes", 1))
         default = [r for r in rows if r["ok"]]
         print("tune: %-7s %-7s n=%-7d best ipl=%d jtile=%d nseg=%d jlanes=%d  %.4f ms  %.3g "
               "pairs/s (%d shapes, slowest admitted %.3f ms)"
               % (kernel, prec, best["n"], best["ipl"], best["jtile"], best["nseg"],
                  best.get("jlanes", 1), best["ms"], best["pairs_per_s"], len(rows),
                  max(r["ms"] for r in default)), flush=True)
-        summary.append(best)
+        summary.append(dict(best, kernel=kernel, precision=prec))
+    if only and os.path.exists(args.out):
+        _lib.nbody_tune_load(args.out)  # the entries that were not re-tuned stay
+    for b in summary:
+        _lib.nbody_tune_set(_lib.KERNELS[b["kernel"]], _lib.PRECISIONS[b["precision"]], b["n"],
+                            b["ipl"], b["jtile"], b["nseg"], b.get("jlanes", 1))
     _lib.nbody_tune_save(args.out)
     print("tune: wrote %s" % args.out, flush=True)
     if rep:
