@@ -84,13 +84,15 @@ SLOTS = {"gravity": 13 + RSQ_SLOTS, "jerk": 27 + RSQ_SLOTS, "adjoint": 31 + RSQ_
 FLOPS = {"gravity": 20, "jerk": 60, "adjoint": 45}
 
 # The files that define the pair kernel wave_kernel<Gravity> (force.hip only instantiates
-# it; its own kernels are the finalize and centre passes), and the tuning file whose
-# force-kernel entries for N = 131072 (size bucket 17) pick the launch shape; the
-# committed counter record is dropped when either changes.
+# it; its own kernels are the finalize and centre passes) and its launch shape (the rules in
+# api.cpp, the built-in shapes in tuning.cpp, and the tuning file's force-kernel entries for
+# N = 131072, size bucket 17); the committed counter record is dropped when any of them changes.
 KERNEL_SOURCES = ["paper_astro_ph_0703100_amd/csrc/nbody_internal.h",
                   "paper_astro_ph_0703100_amd/csrc/tile_engine.h",
                   "paper_astro_ph_0703100_amd/csrc/wave_engine.h",
-                  "paper_astro_ph_0703100_amd/csrc/gravity.h"]
+                  "paper_astro_ph_0703100_amd/csrc/gravity.h",
+                  "paper_astro_ph_0703100_amd/csrc/api.cpp",
+                  "paper_astro_ph_0703100_amd/csrc/tuning.cpp"]
 TUNING_FILE = "paper_astro_ph_0703100_amd/tuning_gfx950.json"
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "pair_kernel_plummer_131072.md")
 CONFIG_WORKLOADS = ("plummer_2048", "stress_1m", "clusters_2048", "adjoint_16384")
