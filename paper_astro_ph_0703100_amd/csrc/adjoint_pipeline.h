@@ -215,11 +215,6 @@ struct AdjointTile {
                                                       float (&acc)[kOut]) {
         Adjoint::pair_timed<MASS, MANY>(j, i, eps2, acc);
     }
-    template <bool MASS>
-    static __device__ __forceinline__ void pair(const float *j, const IState &k, float eps2,
-                                                float (&acc)[5]) {
-        Adjoint::pair<MASS>(j, k, eps2, acc);
-    }
 };
 
 }  // namespace

@@ -16,42 +16,11 @@
 namespace nbody {
 namespace {
 
-// One pair term.  The engine hands the j == i pair a massless record (null_j): with d
-// and w exactly zero and m = 0 it adds exactly zero to a, the jerk and phi.
-template <bool POT>
-__device__ __forceinline__ void jerk_pair(const float *j, float xi, float yi, float zi, float vxi,
-                                          float vyi, float vzi, float eps2, float (&acc)[7]) {
-    const float dx = j[0] - xi;
-    const float dy = j[1] - yi;
-    const float dz = j[2] - zi;
-    const float wx = j[4] - vxi;
-    const float wy = j[5] - vyi;
-    const float wz = j[6] - vzi;
-    float s2 = __builtin_fmaf(dx, dx, eps2);
-    s2 = __builtin_fmaf(dy, dy, s2);
-    s2 = __builtin_fmaf(dz, dz, s2);
-    const float ri = __builtin_amdgcn_rsqf(s2);
-    const float ri2 = ri * ri;
-    const float mri = j[3] * ri;
-    const float mri3 = mri * ri2;
-    float dw = dx * wx;
-    dw = __builtin_fmaf(dy, wy, dw);
-    dw = __builtin_fmaf(dz, wz, dw);
-    const float al = (dw * ri2) * 3.0f;
-    const float tx = __builtin_fmaf(-al, dx, wx);
-    const float ty = __builtin_fmaf(-al, dy, wy);
-    const float tz = __builtin_fmaf(-al, dz, wz);
-    acc[0] = __builtin_fmaf(mri3, dx, acc[0]);
-    acc[1] = __builtin_fmaf(mri3, dy, acc[1]);
-    acc[2] = __builtin_fmaf(mri3, dz, acc[2]);
-    acc[3] = __builtin_fmaf(mri3, tx, acc[3]);
-    acc[4] = __builtin_fmaf(mri3, ty, acc[4]);
-    acc[5] = __builtin_fmaf(mri3, tz, acc[5]);
-    if (POT) acc[6] = acc[6] - mri;
-}
-
-// The same pair term, instruction by instruction (so bitwise the same result), in the order
-// and with the s_nop that gfx950 runs fastest (see gravity_pair_timed).
+// One pair term, instruction by instruction, in the order and with the s_nop that gfx950 runs
+// fastest (see gravity_pair_timed): d, s^2 as an FMA chain and w; d.w; 1/s from the hardware
+// reciprocal square root; m/s, m/s^3 and 3 d.w/s^2; w - (3 d.w/s^2) d; the sums.  The engine
+// hands the j == i pair a massless record (null_j): with d and w exactly zero and m = 0 it
+// adds exactly zero to a, the jerk and phi.
 #define NBODY_JERK_PAIR(POT_INSTR)                                                            \
     asm("v_sub_f32 %[dx], %[jx], %[xi]\n\t"                                                   \
         "v_sub_f32 %[dy], %[jy], %[yi]\n\t"                                                   \
@@ -144,11 +113,6 @@ struct GravityJerk {
                                                       float (&acc)[kOut]) {
         jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
-    template <bool POT>
-    static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
-                                                float (&acc)[7]) {
-        jerk_pair<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
-    }
 };
 
 // FP64 state relative to the block's i-tile centres (mean position and mean velocity):
@@ -194,11 +158,6 @@ struct GravityJerkTile {
                                                       float (&acc)[kOut]) {
         jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
-    template <bool POT>
-    static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
-                                                float (&acc)[7]) {
-        jerk_pair<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
-    }
 };
 
 // Separate i- and j-sets (an active subset of a system against all of it, or two
@@ -240,11 +199,6 @@ struct GravityJerkIJ {
     static __device__ __forceinline__ void pair_timed(const float *j, const IState &i, float eps2,
                                                       float (&acc)[kOut]) {
         jerk_pair_timed<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
-    }
-    template <bool POT>
-    static __device__ __forceinline__ void pair(const float *j, const IState &i, float eps2,
-                                                float (&acc)[7]) {
-        jerk_pair<POT>(j, i.x, i.y, i.z, i.vx, i.vy, i.vz, eps2, acc);
     }
 };
 

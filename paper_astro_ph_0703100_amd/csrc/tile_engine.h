@@ -44,7 +44,14 @@
 //                                            // j == i pair then adds exactly zero
 //   template <bool FULL> static void pair(const float *jr, const IState&, float eps2,
 //                                         float (&acc)[kOut]);
-//   (FULL = false may skip the last output.)
+//   (FULL = false may skip the last output.)  For the engines that let the compiler order the
+//   pairs: split, symmetric, whole-set, and the wave engine where kLone.
+// For the wave engine:
+//   static constexpr int kMaxIpl;            // most i-records per lane
+//   static constexpr bool kLone;             // has a variant for launches of few waves
+//   template <bool FULL, bool MANY> static void pair_timed(...as pair...);
+//                                            // the pair in a fixed instruction order; MANY:
+//                                            // several i-records per lane
 #pragma once
 
 #include <type_traits>
