@@ -1,5 +1,4 @@
-// Adjoint pipelines for the tile engine (device code, included by the .hip files that
-// launch them): vector-Jacobian product of the softened accelerations and potentials
+// Adjoint pipelines (device code, included by the .hip files that launch them): vector-Jacobian product of the softened accelerations and potentials
 // (eq. (1) and the potential of Appendix A) with respect to positions and masses.
 //
 // With d = x_j - x_k, s^2 = |d|^2 + eps^2, cotangents g = dL/da and p = dL/dphi,

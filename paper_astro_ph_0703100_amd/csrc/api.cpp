@@ -298,10 +298,10 @@ nbody_status choose_cfg_ij(int kernel, int64_t ni, int64_t nj, int precision, co
     const int64_t jtiles = (nj + c.jt - 1) / c.jt;
     int64_t nseg = o.nseg ? o.nseg : (ni == nj ? t.nseg : 0);
     if (nseg <= 0 && c.itiles > 0) {
-        // Between 16 and 48 blocks per compute unit (8 resident per CU, so 2 to 6
-        // rounds: the last round stays short), and within that range segments of at
-        // least 8 j-tiles, so per-block start-up and the partial sums stay small when
-        // there are few i-tiles (an i-range of one system against all of it).
+        // 16 to 48 (i-tile, segment) pieces of 256 ipl i's per compute unit, and within that
+        // range segments of at least 8 j-tiles, so that the partial sums stay small when there
+        // are few i-tiles (an i-range of one system against all of it).  What PLAIN sums run;
+        // the upper limit of the others.
         const int64_t cus = device_info().cus;
         const int64_t hi = (cus * 48 + c.itiles - 1) / c.itiles;
         const int64_t lo = (cus * 16 + c.itiles - 1) / c.itiles;

@@ -1,4 +1,4 @@
-// Force evaluation of one system: the gravity pipeline on the tile engine (grid
+// Force evaluation of one system: the gravity pipeline on the wave engine (grid
 // launch), the FP64 finalize, and the FP64-position pre-pass (centre, conversion).
 #include "centre_sum.h"
 #include "gravity.h"

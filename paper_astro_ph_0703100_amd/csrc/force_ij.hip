@@ -1,6 +1,6 @@
 // Pair kernel with separate i- and j-sets (the paper's library interface, Sec. 3.1):
 // the GravityIJ pipeline on the wave engine.  The FP64 reduction is the single-set
-// finalize with the self-term removal switched off.
+// finalize without the self term.
 #include "gravity.h"
 #include "outputs.h"
 #include "wave_engine.h"

@@ -7,7 +7,7 @@
 namespace nbody {
 namespace {
 
-// Finalize arguments of the symmetric engine beyond the tile engine's.
+// Finalize arguments of the symmetric engine beyond the grid engine's.
 struct SymFinal {
     const void *jpart;  // rows 0 .. nb - 2 (sym::jrow_base), FP64 (PLAIN: FP32)
     int bi, jt, segt, nb;

@@ -1,4 +1,4 @@
-// Gravity pipeline for the tile engine: softened accelerations and potentials of
+// Gravity pipelines: softened accelerations and potentials of
 // eq. (1) of the paper (the potential as accumulated by the force-jerk-potential
 // pipeline of Appendix A).
 #pragma once

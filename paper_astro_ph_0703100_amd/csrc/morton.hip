@@ -32,7 +32,7 @@ constexpr int kBoxBlocks = 256;  // one slot of the final reduction each
 constexpr int kBoxThreads = 512;
 // One block sorts up to kSmall words in LDS (64 KB), up to kBitonic by a bitonic network
 // (N = 1000: 17.1 us, by radix passes 20.4; 2048: 24.6 and 23.8; 4096: 43.9 and 37.0; 8192:
-// 85.4 and 64.5 us; 8193, in 23 launches: 84.5 us).
+// 85.4 and 64.5 us; 8193, in 19 launches: 84.2 us).
 constexpr int kBitonic = 1024;
 constexpr int kSmall = 8192;
 constexpr int kSmallThreads = 1024;

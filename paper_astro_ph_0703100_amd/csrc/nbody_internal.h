@@ -22,8 +22,8 @@ struct nbody_graph {
 
 namespace nbody {
 
-// Threads per block of every pair kernel: four 64-wide wavefronts, one per SIMD of
-// a compute unit.
+// Threads per block of the split engine's kernels (four 64-wide wavefronts, one per SIMD of
+// a compute unit), and i-particles of an i-tile (times ipl).
 constexpr int kTPB = 256;
 // Most threads a launch can have along one dimension (the dispatch packet's grid size).
 constexpr int64_t kMaxThreads = UINT32_MAX;
@@ -383,10 +383,11 @@ int wave_ipl(int kernel, int precision, int64_t blocks, int64_t waves1, int ipl)
 // Records that a wave's pass takes per loop iteration (the last one is padded).
 constexpr int wave_unroll(int ipl) { return ipl == 1 ? 16 : 8; }
 // Waves up to which a launch counts as few (the wave engine's kLone, pipelines with Op::kLone):
-// one per SIMD.  One launch of the force on N = 1000 / 2000 / 3000 particles (0.1 / 0.5 / 1.1 waves per
-// SIMD): 6.9 / 7.1 / 8.8 us against 7.4 / 7.6 / 8.6 us; PLAIN, 431 particles against 3452:
-// 10.5 against 11.6 us.  The force-jerk gains under 3 % there and loses 20 % at 1.1 (its
-// interleaved pairs take too many registers), so it has no such variant.
+// one per SIMD.  Force on the grid engine, N = 300 / 1500 / 2500 (15 / 288 / 800 waves): 7.4 /
+// 10.0 / 10.7 us against 8.0 / 10.5 / 11.2; in blocks of 8 waves, which share SIMDs, it costs
+// (N = 1000: 10.1 against 8.9); PLAIN, 431 particles against 3452: 10.5 against 11.6 us.  The
+// force-jerk gains under 3 % there and loses 20 % at 1.1 waves per SIMD (its interleaved pairs
+// take too many registers), so it has no such variant.
 constexpr int64_t kLoneWaves = 1024;
 // Waves that fill the chip (about 4 per SIMD).
 constexpr int64_t kFullWaves = 4000;

@@ -1,15 +1,15 @@
 // Single-launch pair engine for systems too small to fill the chip with whole i-tiles
-// (device code, header-only).  Same pipelines (Op) as the tile engine, but the j-range
-// of each i-particle is split across lanes of one wavefront instead of across blocks:
+// (device code, header-only).  Same pipelines (Op) as the grid engine, but the j-range
+// of each i-particle is split across lanes of one wavefront instead of across waves and blocks:
 //
 //   * a wave holds G = 64 / Q i-groups; the Q lanes of a group share IPL i-records
 //     and take every Q-th j-record of each staged tile (lane q: slots q, q + Q, ...),
 //     so an i-particle's pairs are spread over Q lanes and the 4 waves of a block own
 //     different i's: TI = 4 * G * IPL i-particles per block, every j in every block;
-//   * j-tiles of JT records are staged in LDS exactly as in the tile engine (coalesced,
-//     double-buffered, one barrier per tile); a read instruction of a wave touches Q
+//   * j-tiles of JT records are staged in LDS (coalesced, double-buffered, one barrier per
+//     tile); a read instruction of a wave touches Q
 //     distinct records, each broadcast to the G lanes that hold different i's;
-//   * each lane accumulates its share like the tile engine (PLAIN: FP32; FP64RED: FP32
+//   * each lane accumulates its share as the grid engine does (PLAIN: FP32; FP64RED: FP32
 //     blocks added in FP64; COMP: FP32 blocks added into an FP32 (hi, lo) pair by a
 //     two-sum), the FP32 block being the lane's R = JT / Q pairs of one tile;
 //   * the Q partial sums of every (i, output) are then added across the lanes of the
@@ -18,7 +18,7 @@
 //     v_permlane32_swap for 16 and 32.  Both lanes of every exchange add the same two
 //     values, so all Q lanes end with bitwise the same sum, and the order is fixed;
 //   * the group's lanes then store the results through a Sink (lane q stores the slots
-//     c with c % Q == q), which also applies what the FP64 finalize of the tile engine
+//     c with c % Q == q), which also applies what the FP64 finalize of the grid engine
 //     applies (self potential, a fused leapfrog kick, the adjoint's own-cotangent term,
 //     accumulation).
 // No partial sums leave the chip and no second launch is needed; results are bitwise

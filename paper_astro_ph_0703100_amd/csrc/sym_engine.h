@@ -7,7 +7,7 @@
 //
 //   * particles are grouped in block rows of BI = 64 W IPL (W waves of 64 lanes, IPL
 //     per lane, lane-strided); row b's work is the one-sided pairs among its own
-//     particles (the diagonal, j == i left out as in the tile engine) and the
+//     particles (the diagonal, j == i left out as in the grid engine) and the
 //     symmetric pairs with every particle j >= (b + 1) BI, walked in LDS j-tiles of JT
 //     records;
 //   * a work item (one block) is (row b, segment s): segment s covers `segt` j-tiles
@@ -24,7 +24,7 @@
 //     passing them to the lane that meets column c - k next.  After step 15 each lane
 //     holds the sums of column c + 1 and stores them in that record's slot of the
 //     wave's LDS slice (the first record load of a chunk stores, the others add);
-//   * i-side sums as in the tile engine: FP32 over each 64-record chunk, added in
+//   * i-side sums as in the grid engine: FP32 over each 64-record chunk, added in
 //     FP64 (FP64RED) or into an FP32 (hi, lo) pair by a two-sum (COMP), or FP32
 //     throughout (PLAIN); written at the end of the item to the i-plane of segment s;
 //   * j-side sums: FP32 per wave (its 64 IPL terms per record), then, after the tile's
@@ -36,10 +36,10 @@
 // shape (W, IPL, JT, segt).
 //
 // Issue cost per unordered pair with the potential, in clocks per wavefront as measured
-// on gfx950 (two-operand operations 2, FMACs about 2.6, an FMA with a scalar addend and
-// any DPP-modified operation 4, v_rsq_f32 8): 3 separations, s^2 (one scalar-addend FMA,
-// two FMACs), rsq, r^2, and per side m r, m r^3, three FMACs and one addition: about 53,
-// against 2 x 39 for the two ordered pairs of the tile engine; the rotation of the
+// on gfx950 with long independent chains (two-operand operations 2, FMACs about 2.6, an FMA
+// with a scalar addend and any DPP-modified operation 4, v_rsq_f32 8): 3 separations, s^2 (one
+// scalar-addend FMA, two FMACs), rsq, r^2, and per side m r, m r^3, three FMACs and one
+// addition: about 53, against 2 x 39 for the two ordered pairs of the grid engine; the rotation of the
 // j-sums adds about 12 per step, shared by the lane's IPL pairs of that step.
 #pragma once
 
@@ -83,7 +83,7 @@ __device__ __forceinline__ void step(const float4 &jr, const IRegs<IPL> &is, flo
         s2 = __builtin_fmaf(dz, dz, s2);
         const float ri = __builtin_amdgcn_rsqf(s2);
         const float ri2 = ri * ri;
-        // i side: the ordered pair body of the tile engine (a += m_j d / s^3, phi -= m_j / s).
+        // i side: the ordered pair body (a += m_j d / s^3, phi -= m_j / s).
         const float mjr = jr.w * ri;
         const float mjr3 = mjr * ri2;
         bi[p][0] = __builtin_fmaf(mjr3, dx, bi[p][0]);
@@ -316,7 +316,7 @@ __global__ __launch_bounds__(64 * W) void sym_kernel(SymArgs a) {
         }
     }
 
-    // i-side partials of this item: plane s, words [s][word][npad] as in the tile engine.
+    // i-side partials of this item: plane s, words [s][word][npad] as in the grid engine.
     constexpr int WO = NO * engine::words_per_out<MODE>();
     const size_t plane = (size_t)a.npad;
     float *base = static_cast<float *>(a.ipart) + (size_t)s * WO * plane;

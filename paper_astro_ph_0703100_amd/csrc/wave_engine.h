@@ -8,7 +8,7 @@
 //     the next 64 already on their way to registers) and reads each one back with
 //     broadcast 16-byte reads, one record ahead of the pairs.  Nothing but the wave
 //     itself touches the slice, so there is no barrier in the loop;
-//   * accumulation as in the tile engine (PLAIN: one FP32 sum per segment; FP64RED:
+//   * accumulation (PLAIN: one FP32 sum per segment; FP64RED:
 //     FP32 blocks of BJ j's added in FP64; COMP: FP32 blocks added into an FP32 (hi, lo)
 //     pair by a two-sum).  A PLAIN segment is one chain of additions, so there each wave
 //     takes a segment of its own;
@@ -103,9 +103,9 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
 // instruction every 4.7 clocks whatever it depends on, so what counts is their number.  A
 // records are read ahead of their pairs and the compiler interleaves the A pair bodies, which
 // leaves no s_nop (a lone wave: 73 clocks per gravity pair instead of 86).  A = 8 for PLAIN
-// sums (N = 16384 in one segment: 565 us, with A = 4 612), whose waves are alone on their SIMD;
-// A = 4 where the waves of a block can meet on one (2048 i's and j's, separate sets: 13.5 us,
-// with A = 8 14.3).
+// sums (N = 16384 in one segment: 565 us, with A = 4 612), whose waves are alone on their SIMD.
+// The other modes take 4: of blocks of 5 to 8 waves two share a SIMD (N = 600 / 1000: 8.5 / 10.1
+// us, with A = 8 8.9 / 10.1; in blocks of 4, N = 1500 / 2500, 10.0 / 10.7 and 9.5 / 10.2).
 template <class Op, int A, bool FULL, bool SELF>
 __device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
                                           const typename Op::IState (&is)[1], float eps2,
