@@ -4,8 +4,8 @@
 //   * a wave holds 64 * IPL i-particles (IPL i-records per lane, lane-strided); the W
 //     waves of a block hold the same i's and share out the FP32 blocks of BJ j's of
 //     the block's j-segment in contiguous runs;
-//   * a wave stages 64 j-records at a time in its own LDS slice (one record per lane,
-//     the next 64 already on their way to registers) and reads each one back with
+//   * a wave stages 64 j-records at a time (kLongStage: 256) in its own LDS slice (one record
+//     per lane, the next 64 already on their way to registers) and reads each one back with
 //     broadcast 16-byte reads, one record ahead of the pairs.  Nothing but the wave
 //     itself touches the slice, so there is no barrier in the loop;
 //   * accumulation (PLAIN: one FP32 sum per segment; FP64RED:
@@ -23,7 +23,11 @@
 namespace nbody {
 namespace wave {
 
-constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
+// j-records a wave stages at a time: one per lane; four in PLAIN launches of few waves, where
+// nothing hides the way through LDS (separate sets, 1024 i's x 8192 j's: 12.7 us, with one 13.1;
+// N = 16384 in one segment: 539 and 562 us; with 1 to 5 waves per SIMD it costs, N = 8192: 29.1
+// and 25.9 us).
+constexpr int kStage = 64, kLongStage = 256;
 // Above kLoneWaves and up to this many (5 per SIMD, all there at once, with chains of 128 to 512
 // pairs), the waves of a launch should end together (kEven, one record per lane).  N = 4099 /
 // 5000 / 8192 / 9000 / 10007, with the finalize: force-jerk 22.7 / 27.5 / 47.4 / 54.0 / 69.3
@@ -35,25 +39,28 @@ constexpr int kStage = 64;  // j-records a wave stages at a time: one per lane
 // order (PLAIN force, N = 20011: 124 -> 132 us).
 constexpr int64_t kEvenWaves = 5120;
 enum Run { kMany, kLone, kEven };
+constexpr int stage_of(int mode, Run run) {
+    return mode == NBODY_PLAIN && run == kLone ? kLongStage : kStage;
+}
 
 // Bytes of LDS of a block of `waves` waves: staging, then the cross-wave sums.
 template <class Op>
-constexpr size_t lds_bytes(int waves) {
-    const size_t stage = (size_t)kStage * Op::kJWords * 4;
+constexpr size_t lds_bytes(int waves, int records = kStage) {
+    const size_t stage = (size_t)records * Op::kJWords * 4;
     const size_t sums = (size_t)64 * Op::kOut * 8;
     return waves * (stage > sums ? stage : sums);
 }
 
 // The records [0, cnt) of the wave's slice against the lane's IPL i-records, added into
 // acc.  With SELF, slot self[k] holds the lane's k-th own particle.
-template <class Op, int IPL, bool FULL, bool SELF>
+template <class Op, int IPL, int ST, bool FULL, bool SELF>
 __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
                                            const typename Op::IState (&is)[IPL], float eps2,
                                            float (&acc)[IPL][Op::kOut], int lane, int d0) {
     constexpr int W = Op::kJWords;
     constexpr int V = W / 4;
     constexpr int U = wave_unroll(IPL);  // (padding adds zero)
-    static_assert(kStage % U == 0, "whole iterations per stage");
+    static_assert(ST % U == 0, "whole iterations per stage");
     float4 cur[V], nxt[V];
 #pragma unroll
     for (int v = 0; v < V; ++v) cur[v] = tl[v];
@@ -63,7 +70,7 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
         for (int u = 0; u < U; ++u) {
             // The next record is read while this one's pairs run (past the last record of
             // the slice: the first one again, unused).
-            const int jn = u + 1 < U ? j0 + u + 1 : (j0 + U) & (kStage - 1);
+            const int jn = u + 1 < U ? j0 + u + 1 : (j0 + U) & (ST - 1);
 #pragma unroll
             for (int v = 0; v < V; ++v) nxt[v] = tl[jn * V + v];
             // Keeps the reads one record ahead: free to move, the scheduler hoists every
@@ -103,16 +110,17 @@ __device__ __forceinline__ void stage_pass(const float4 *tl, int cnt,
 // instruction every 4.7 clocks whatever it depends on, so what counts is their number.  A
 // records are read ahead of their pairs and the compiler interleaves the A pair bodies, which
 // leaves no s_nop (a lone wave: 73 clocks per gravity pair instead of 86).  A = 8 for PLAIN
-// sums (N = 16384 in one segment: 565 us, with A = 4 612), whose waves are alone on their SIMD.
+// sums (N = 16384 in one segment: 565 us, with A = 4 612, then 539 in long stages), whose waves
+// are alone on their SIMD.
 // The other modes take 4: of blocks of 5 to 8 waves two share a SIMD (N = 600 / 1000: 8.5 / 10.1
 // us, with A = 8 8.9 / 10.1; in blocks of 4, N = 1500 / 2500, 10.0 / 10.7 and 9.5 / 10.2).
-template <class Op, int A, bool FULL, bool SELF>
+template <class Op, int A, int ST, bool FULL, bool SELF>
 __device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
                                           const typename Op::IState (&is)[1], float eps2,
                                           float (&acc)[1][Op::kOut], int lane, int d0) {
     constexpr int W = Op::kJWords;
     constexpr int V = W / 4;
-    static_assert(kStage % (2 * A) == 0, "whole groups per stage");
+    static_assert(ST % (2 * A) == 0, "whole groups per stage");
     float jr[2][A][W];
     auto read = [&](int h, int j0) {
 #pragma unroll
@@ -138,7 +146,7 @@ __device__ __forceinline__ void lone_pass(const float4 *tl, int cnt,
         __builtin_amdgcn_sched_barrier(0);
         pairs(0, j0);
         __builtin_amdgcn_sched_barrier(0);
-        read(0, (j0 + 2 * A) & (kStage - 1));
+        read(0, (j0 + 2 * A) & (ST - 1));
         __builtin_amdgcn_sched_barrier(0);
         pairs(1, j0 + A);
         __builtin_amdgcn_sched_barrier(0);
@@ -170,8 +178,10 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
     constexpr int W = Op::kJWords;
     constexpr int V = W / 4;
     constexpr int NO = Op::kOut;
-    constexpr int PER = MODE == NBODY_PLAIN ? 1 : BJ / kStage;  // stages per FP32 block
-    static_assert(BJ % kStage == 0, "whole stages per FP32 block");
+    constexpr int ST = stage_of(MODE, RUN);
+    constexpr int RPL = ST / 64;  // records per lane and stage
+    constexpr int PER = MODE == NBODY_PLAIN ? 1 : BJ / ST;  // stages per FP32 block
+    static_assert(MODE == NBODY_PLAIN || BJ % ST == 0, "whole stages per FP32 block");
     const int lane = threadIdx.x & 63;
     const typename Op::Ctx ctx = Op::make_ctx(a, i0);
 
@@ -190,17 +200,20 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
             ds[k][c] = 0.0;
         }
 
-    float rec[W];
+    float rec[RPL][W];
     auto fetch = [&](int t) {
-        const int b = t * kStage;
-        if (b + kStage <= nj) {
-            Op::load_j(a, ctx, j0 + b, (unsigned)lane, rec);
-        } else {
-            Op::pad_j(rec);
-            if (b + lane < nj) Op::load_j(a, ctx, j0 + b, (unsigned)lane, rec);
+#pragma unroll
+        for (int r = 0; r < RPL; ++r) {
+            const int b = t * ST + r * 64;
+            if (b + 64 <= nj) {
+                Op::load_j(a, ctx, j0 + b, (unsigned)lane, rec[r]);
+            } else {
+                Op::pad_j(rec[r]);
+                if (b + lane < nj) Op::load_j(a, ctx, j0 + b, (unsigned)lane, rec[r]);
+            }
         }
     };
-    const int stages = (nj + kStage - 1) / kStage;
+    const int stages = (nj + ST - 1) / ST;
     if (stages > 0) fetch(0);
     for (int t0 = 0; t0 < stages; t0 += PER) {
         float bs[IPL][NO];
@@ -217,22 +230,24 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
             // as its last reads are issued; the fences keep the compiler to that order.
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
-            for (int v = 0; v < V; ++v)
-                tl[lane * V + v] =
-                    make_float4(rec[4 * v], rec[4 * v + 1], rec[4 * v + 2], rec[4 * v + 3]);
+            for (int r = 0; r < RPL; ++r)
+#pragma unroll
+                for (int v = 0; v < V; ++v)
+                    tl[(r * 64 + lane) * V + v] = make_float4(rec[r][4 * v], rec[r][4 * v + 1],
+                                                              rec[r][4 * v + 2], rec[r][4 * v + 3]);
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             if (t + 1 < stages) fetch(t + 1);
-            const int jt0 = j0 + t * kStage;
-            const int cnt = min(kStage, nj - t * kStage);
+            const int jt0 = j0 + t * ST;
+            const int cnt = min(ST, nj - t * ST);
             const int d0 = i0 - jt0;
             auto pass = [&](auto self) {
                 constexpr bool SELF = decltype(self)::value;
                 auto run = [&](float(&acc)[IPL][NO]) {
                     if constexpr (RUN == kLone)
-                        lone_pass<Op, MODE == NBODY_PLAIN ? 8 : 4, FULL, SELF>(
+                        lone_pass<Op, MODE == NBODY_PLAIN ? 8 : 4, ST, FULL, SELF>(
                             tl, cnt, is, eps2, acc, lane, d0);
                     else
-                        stage_pass<Op, IPL, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
+                        stage_pass<Op, IPL, ST, FULL, SELF>(tl, cnt, is, eps2, acc, lane, d0);
                 };
                 if constexpr (MODE == NBODY_PLAIN)
                     run(hs);
@@ -241,7 +256,7 @@ __device__ __forceinline__ void wave_work(const typename Op::Args &a, float4 *tl
             };
             if constexpr (Op::kSelf) {
                 // Does this stage hold any of the wave's own i's?
-                if (jt0 < i0 + 64 * IPL && i0 < jt0 + kStage)
+                if (jt0 < i0 + 64 * IPL && i0 < jt0 + ST)
                     pass(std::true_type{});
                 else
                     pass(std::false_type{});
@@ -362,7 +377,7 @@ __global__ __launch_bounds__(1024) void wave_kernel(typename Op::Args a, typenam
     const int nj = max(0, min(a.seg_len, Op::n_j(a) - j0));
     const size_t plane = (size_t)a.npad;
     float *part = static_cast<float *>(a.part) + (size_t)s * WO * plane;
-    float4 *tl = lds + wave * kStage * V;
+    float4 *tl = lds + wave * stage_of(MODE, RUN) * V;
     float hs[IPL][NO], ls[IPL][NO];
     double ds[IPL][NO];
     if constexpr (MODE == NBODY_PLAIN) {
@@ -428,17 +443,18 @@ nbody_status launch(const TileCfg &cfg, int precision, bool full, int64_t ni,
     int wpb = cfg.wpb;
     while (groups * 64 * wpb > kMaxThreads) wpb /= 2;  // from 2^28 i's on
     const int64_t waves = groups * cfg.nseg * (precision == NBODY_PLAIN ? 1 : wpb);
-    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full,
-                                  waves <= kLoneWaves   ? kLone
-                                  : waves <= kEvenWaves ? kEven
-                                                        : kMany);
+    const Run run = cfg.wi > 1                             ? kMany
+                    : waves <= kLoneWaves                  ? (Op::kLone ? kLone : kMany)
+                    : waves <= kEvenWaves                  ? kEven
+                                                           : kMany;
+    auto fn = pick_wave<Op, Sink>(cfg.wi, cfg.bj, precision, full, run);
     if (!fn) return set_error(NBODY_EUNSUPPORTED, "no pair kernel for this ipl/jtile/precision");
     if (ni <= 0 || cfg.nseg <= 0) return NBODY_OK;
     const int per_block = precision == NBODY_PLAIN ? wpb : 1;  // segments per block
     const dim3 grid((unsigned)groups,
                     (unsigned)((cfg.nseg + per_block - 1) / per_block));
-    hipLaunchKernelGGL(fn, grid, dim3(64 * wpb), lds_bytes<Op>(wpb), s, a, f, cfg.nseg,
-                       cfg.direct);
+    hipLaunchKernelGGL(fn, grid, dim3(64 * wpb), lds_bytes<Op>(wpb, stage_of(precision, run)), s,
+                       a, f, cfg.nseg, cfg.direct);
     NBODY_HIP_CHECK(hipGetLastError());
     return NBODY_OK;
 }
