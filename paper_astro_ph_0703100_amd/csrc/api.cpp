@@ -153,7 +153,10 @@ void choose_wave_shape(int kernel, int64_t ni, int64_t nj, int precision, int ip
         // (N = 10007, 40 segments: 33.0 us, with 4 waves per block 36.9 us).  Up to one wave per
         // SIMD, the waves of a block of 4 have a SIMD each, while single ones can meet on one
         // (separate sets, 1024 i's x 8192 j's, 512 waves: 13.9 us in ones, 13.3 us in fours).
-        c->wpb = groups * c->nseg <= kLoneWaves && c->nseg >= 4 ? 4 : 1;
+        // Force only: the other pipelines lose by it (force-jerk, 374 i's x 7703 j's 22.9 and
+        // 23.2 us, N = 1073 22.2 and 22.7; adjoint, N = 1140, 25.9 and 26.1 us).
+        const bool fours = kernel == KERNEL_FORCE && groups * c->nseg <= kLoneWaves;
+        c->wpb = fours && c->nseg >= 4 ? 4 : 1;
         return;
     }
     if (nseg_asked) {
